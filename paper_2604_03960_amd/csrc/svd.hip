@@ -8,10 +8,10 @@
 // disjoint pairs).  Per step three launches:
 //   gram   G = [B_p; B_q][B_p; B_q]^T (64 x 64) on the FP64 MFMA, K split
 //          across workgroups, partial sums in fixed order;
-//   eigen  the 64 x 64 symmetric G is diagonalised in LDS by cyclic two-sided
-//          Jacobi with a parallel (round-robin) pair order, eigenvectors sorted
-//          by eigenvalue (larger rows to the lower block); skipped when every
-//          off-diagonal already satisfies |g_ij| <= tol sqrt(g_ii g_jj);
+//   eigen  a two-sided Jacobi sweep of the 64 x 64 symmetric G in registers
+//          (odd-even transposition order), eigenvectors sorted by eigenvalue
+//          (larger rows to the lower block); skipped when every off-diagonal
+//          already satisfies |g_ij| <= tol sqrt(g_ii g_jj);
 //   apply  [B_p; B_q] <- Q^T [B_p; B_q] and [J_p; J_q] <- Q^T [J_p; J_q] on the
 //          MFMA, column slab by column slab, in place.
 // A sweep with no rotating pair ends the iteration (one 4-byte host read per
@@ -23,6 +23,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "dev_reduce.h"
 #include "internal.h"
@@ -83,6 +84,45 @@ __device__ inline void jacobi_rot(double a, double b, double g, double &c, doubl
   c = rsqrt_nr(fma(t, t, 1.0));
   s = c * t;
 }
+// The same rotation by its half angle (cos 2u = |b - a| / sqrt((b - a)^2 + 4 g^2), c = sqrt((1 + cos 2u) / 2)),
+// two reciprocal square roots long, with tg = (s / c) g for the new diagonal (a - tg, b + tg).  Identity
+// (c, s, tg = 1, 0, 0) where a row is at or below floor2 or the coupling is at the rounding level.  It is a
+// chain of dependent operations cut into eight stages, so that a caller can issue other work between them;
+// each reciprocal square root takes the hardware estimate y (relative error below 2^-22) and one third-order
+// step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2, which cubes the error.
+struct RotChain {
+  double a, b, g;  // inputs: the 2 x 2 block [[a, g], [g, b]]
+  double dl, x, y, e, ir, c2, ic, c, s, tg;
+  bool act;
+  template <int K>
+  __device__ __forceinline__ void stage(double floor2) {
+    constexpr double tol_in = 4.0 * 1.1102230246251565e-16;
+    if constexpr (K == 0) {
+      dl = b - a;
+      x = fma(dl, dl, 4.0 * g * g);
+    } else if constexpr (K == 1) {
+      y = __builtin_amdgcn_rsq(x);
+      act = a > floor2 && b > floor2 && g * g > tol_in * tol_in * fabs(a * b);
+    } else if constexpr (K == 2) {
+      e = fma(-(x * y), y, 1.0);
+    } else if constexpr (K == 3) {
+      ir = fma(y * e, fma(0.375, e, 0.5), y);
+    } else if constexpr (K == 4) {
+      c2 = fma(0.5 * fabs(dl), ir, 0.5);
+      s = (dl >= 0.0 ? g : -g) * ir;
+      y = __builtin_amdgcn_rsq(c2);
+    } else if constexpr (K == 5) {
+      e = fma(-(c2 * y), y, 1.0);
+    } else if constexpr (K == 6) {
+      ic = fma(y * e, fma(0.375, e, 0.5), y);
+    } else {
+      c = act ? c2 * ic : 1.0;
+      s = s * ic;
+      tg = act ? s * ic * g : 0.0;
+      s = act ? s : 0.0;
+    }
+  }
+};
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr double EPS53 = 1.1102230246251565e-16;
@@ -407,188 +447,235 @@ __device__ inline void eig_order(EigLds &L, int np, int nq) {
   __syncthreads();
 }
 
-// ---- the eigen step of the blocked method: a tournament on moving slots
-// The elements of the 64 x 64 Gram move between slots so that the pairs of every round are the
-// slot pairs (2t, 2t+1): each round reads its 2 x 2 blocks as contiguous 16-byte pairs, rotates,
-// and writes them to the slots of the next round in a second buffer (one barrier for the
-// rotations, one for the round).  The move is the circle method on 64 slots with slot 0 fixed:
-// every other element advances one place along 1 -> 2 -> 4 -> ... -> 62 -> 63 -> 61 -> ... -> 3
-// -> 1, which brings every pair of elements together once in 63 rounds and restores the starting
-// placement after the 63rd.  The eigenvector columns move with their elements, in registers.
-__device__ inline int tour_next(int s) {
-  if (s == 0) return 0;
-  if (s == 1) return 2;
-  if (s == 62) return 63;
-  return (s & 1) ? s - 2 : s + 2;
-}
-__device__ inline int tour_prev(int m) {
-  if (m == 0) return 0;
-  if (m == 2) return 1;
-  if (m == 63) return 62;
-  return (m & 1) ? m + 2 : m - 2;
+// ---- two-sided Jacobi sweep of an N x N Gram held in registers
+// Odd-even transposition order: the even rounds rotate the slot pairs (2t, 2t+1), the odd rounds the
+// pairs (2t+1, 2t+2), and the two elements of a pair change places after every rotation (also after
+// an identity one).  N rounds bring every pair of elements together once and leave the order of
+// the slots reversed.  The moves are between neighbours only, so nothing travels through LDS but
+// the rotations themselves and, in the odd rounds, the rows at the edges of the row groups.
+//
+// Layout: lane t of a group of N / 2 lanes holds columns 2t and 2t+1 of the HR rows HR rg ..
+// HR rg + HR - 1 of its row group rg, of G and of Q alike (Q's rows stay, its columns move).  An
+// even round's column pairs lie inside a lane, an odd round's in neighbouring lanes (two DPP moves
+// per value); row pairs lie in registers of one lane except those across two groups.  Every lane
+// also carries the diagonal elements of its columns (d0, d1), updated from the rotations (a - t g,
+// b + t g), so a round needs one coupling per pair, read in place by the lanes that hold it.  Per
+// round: the owners form their pairs' rotations and put them in LDS, one barrier, and every lane
+// reads its columns' and its rows' rotations and updates HR x 2 elements of G and of Q.
+// f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>): register arrays indexed by constants
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
 }
 
-struct EigTour {
-  double G[2][64][66];  // the matrix of the current round and of the next (rows 16-byte aligned)
-  double cs[32], sn[32];
-  int rot_any, need;
-  int slot_of[64];
-  int rank[64];
+constexpr int OE_QD = 4;  // of eight rows of Q, those updated behind a round's LDS reads (2, 6, 8: within 3 %)
+template <int N, int NW>
+struct OeShape {
+  static constexpr int LPG = N / 2, GPW = 64 / LPG, NG = NW * GPW, HR = N / NG, PH = HR / 2;
+  static_assert(64 % LPG == 0 && N % NG == 0 && HR >= 2 && HR % 2 == 0, "odd-even shape");
+};
+template <int N, int NW>
+struct OeLds {
+  // per parity: rotation (c, s) of pair t at [t + 1] and its new diagonal elements, lower slot first;
+  // lanes that own no pair write to the 64 entries behind
+  double2 cs[2][N / 2 + 1 + 64];
+  double2 nd[2][N / 2 + 1 + 64];
+  double edge[2][OeShape<N, NW>::NG][N];  // first and last row of every group
 };
 
-// Outer test on G[0] (rows above the floor only), as eig_needs_rotation
-template <int NTE>
-__device__ inline bool tour_needs_rotation(EigTour &L, double tol, double floor2) {
-  const int tid = threadIdx.x;
-  if (tid == 0) L.need = 0;
-  __syncthreads();
-  // the test squared (no square root on the path): g_ij^2 > tol^2 g_ii g_jj
-  const double tol2 = tol * tol;
-  int loc = 0;
-#pragma unroll
-  for (int m = 0; m < 4096 / NTE; ++m) {
-    const int e = tid + m * NTE, i = e >> 6, j = e & 63;
-    if (i < j) {
-      const double gii = L.G[0][i][i], gjj = L.G[0][j][j], gij = L.G[0][i][j];
-      if (gii > floor2 && gjj > floor2 && gii > 0.0 && gjj > 0.0 && gij * gij > tol2 * (gii * gjj)) loc = 1;
-    }
-  }
-  if (__any(loc) && (tid & 63) == 0) atomicOr(&L.need, 1);
-  __syncthreads();
-  return L.need != 0;
+// value of the next / previous lane (lanes at the ends of a group get another group's value or
+// zero, which their identity coefficients discard)
+__device__ inline double lane_next(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);  // wave_shl:1
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ inline double lane_prev(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);  // wave_shr:1
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
 }
 
-// Sweeps of 63 rounds until one rotates nothing (or inner_max).  Returns the buffer holding the
-// rotated matrix (eigenvalues on its diagonal, every element back on its starting slot); the
-// eigenvector matrix Q (column s for slot s) is left in the other buffer.  Rotation and tests as
-// in eig_inner; the 2 x 2 block (t, u) and its mirror (u, t) are computed by the same operations
-// on the same values, so the matrix stays exactly symmetric.
-template <int NTE>
-__device__ inline int eig_tour(EigTour &L, int inner_max, double floor2) {
-  constexpr int RPW = 64 / (NTE / 64);  // rows of Q per wave
-  constexpr int BPT = 1024 / NTE;       // 2 x 2 blocks per thread
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double q[RPW];
-#pragma unroll
-  for (int r = 0; r < RPW; ++r) q[r] = (wave * RPW + r == lane) ? 1.0 : 0.0;
-  const double tol_in = 4.0 * EPS53;
-  const int qsrc = tour_prev(lane), qpair = lane >> 1;
-  int cur = 0;
-  for (int sweep = 0; sweep < inner_max; ++sweep) {
-    __syncthreads();  // every thread has read rot_any of the previous sweep
-    if (tid == 0) L.rot_any = 0;
-    __syncthreads();
-    for (int rr = 0; rr < 63; ++rr) {
-      double (*Gi)[66] = L.G[cur];
-      double (*Go)[66] = L.G[cur ^ 1];
-      double x[BPT][4];
-#pragma unroll
-      for (int b = 0; b < BPT; ++b) {  // Gi does not change during the round: read before the rotations
-        const int e = tid + b * NTE, t = e >> 5, u = e & 31;
-        const double2 r0 = *reinterpret_cast<const double2 *>(&Gi[2 * t][2 * u]);
-        const double2 r1 = *reinterpret_cast<const double2 *>(&Gi[2 * t + 1][2 * u]);
-        x[b][0] = r0.x;
-        x[b][1] = r0.y;
-        x[b][2] = r1.x;
-        x[b][3] = r1.y;
-      }
-      if (tid < 32) {
-        // J = [[c, s], [-s, c]] on the slots (2t, 2t+1), zeroing their coupling
-        const int t = tid;
-        const double a = Gi[2 * t][2 * t], bb = Gi[2 * t + 1][2 * t + 1], g = Gi[2 * t][2 * t + 1];
-        double c = 1.0, sn = 0.0;
-        if (a > floor2 && bb > floor2 && g * g > tol_in * tol_in * fabs(a * bb)) {
-          jacobi_rot(a, bb, g, c, sn);
-          L.rot_any = 1;
-        }
-        L.cs[t] = c;
-        L.sn[t] = sn;
-      }
+// One sweep of N rounds by the whole workgroup (NW waves).  Rows at or below floor2 and pairs whose
+// coupling is at the rounding level are not rotated; returns whether this lane's pairs rotated.
+// A round's update first brings the couplings of the next round up to date and starts the next
+// rotations' dependent chain, whose stages are issued between the updates of the other elements.
+template <int N, int NW>
+__device__ inline int oe_sweep(OeLds<N, NW> &L, double (&g)[OeShape<N, NW>::HR][2],
+                               double (&q)[OeShape<N, NW>::HR][2], double &d0, double &d1, double floor2) {
+  using S = OeShape<N, NW>;
+  constexpr int HR = S::HR, PH = S::PH, LPG = S::LPG, NG = S::NG;
+  constexpr int NST = 8;  // stages of a rotation
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t = lane & (LPG - 1), rg = wave * S::GPW + lane / LPG;
+  const int rp = rg > 0 ? rg - 1 : 0, rn = rg < NG - 1 ? rg + 1 : NG - 1;  // neighbouring groups (clamped)
+  // even rounds: pair t = slots (2t, 2t+1), row 2t is row 2 (t % PH) of group t / PH;
+  // odd rounds: pair t = slots (2t+1, 2t+2), row 2t+2 is row 2 ((t+1) % PH) of group (t+1) / PH
+  const bool own0 = t / PH == rg, own1 = t < LPG - 1 && (t + 1) / PH == rg;
+  const int w0 = own0 ? t + 1 : N / 2 + 1 + lane, w1 = own1 ? t + 1 : N / 2 + 1 + lane;
+  const int k0 = t % PH, k1 = (t + 1) % PH;
+  if (threadIdx.x == 0) {  // the edge slots of an odd round sit it out: read after the first barrier below
+    L.cs[1][0] = make_double2(0.0, -1.0);
+    L.cs[1][N / 2] = make_double2(0.0, 1.0);
+  }
+  int rot = 0;
+  RotChain r;
+  // g[2 k][1], k per lane: selected word by word (a select of whole elements becomes a load at a
+  // selected address, and the array would leave the registers)
+  auto coupling = [&](int k) {
+    int lo = __double2loint(g[0][1]), hi = __double2hiint(g[0][1]);
+    static_for<1, PH>([&](auto m) {
+      lo = k == m ? __double2loint(g[2 * m][1]) : lo;
+      hi = k == m ? __double2hiint(g[2 * m][1]) : hi;
+    });
+    return __hiloint2double(hi, lo);
+  };
+  r.a = d0;
+  r.b = d1;
+  r.g = coupling(k0);
+  static_for<0, NST>([&](auto st) { r.stage<st>(floor2); });
+  // the first QD rows of Q take a round's column rotations in the next round, while its LDS reads
+  // are on their way; the others between the stages of the rotation
+  constexpr int QD = OE_QD * HR / 8, QI = HR - QD;
+  double2 C = make_double2(0.0, 0.0), Cu = make_double2(0.0, -1.0), Cl = make_double2(0.0, 1.0);
+  auto q_even = [&](auto i) {
+    const double x = q[i][0], y = q[i][1];
+    q[i][0] = C.x * y + C.y * x;
+    q[i][1] = C.x * x - C.y * y;
+  };
+  auto q_odd = [&](auto i) {
+    const double x = q[i][0], y = q[i][1];
+    q[i][0] = Cu.x * lane_prev(y) - Cu.y * x;
+    q[i][1] = Cl.x * lane_next(x) + Cl.y * y;
+  };
+#pragma unroll 1
+  for (int rr = 0; rr < N / 2; ++rr) {
+    {  // even round
+      L.cs[0][w0] = make_double2(r.c, r.s);
+      L.nd[0][w0] = make_double2(r.b + r.tg, r.a - r.tg);
+      rot |= own0 && r.act;
       __syncthreads();
+      const double2 Cn = L.cs[0][t + 1], nd = L.nd[0][t + 1];
+      double2 P[PH];
 #pragma unroll
-      for (int b = 0; b < BPT; ++b) {
-        const int e = tid + b * NTE, t = e >> 5, u = e & 31;
-        const bool up = t <= u;  // Z = J_lo^T X(lo, hi) J_hi, lo = min(t, u)
-        const int lo = up ? t : u, hi = up ? u : t;
-        const double cl = L.cs[lo], sl = L.sn[lo], ch = L.cs[hi], sh = L.sn[hi];
-        const double x00 = x[b][0], x01 = up ? x[b][1] : x[b][2], x10 = up ? x[b][2] : x[b][1], x11 = x[b][3];
-        const double y00 = cl * x00 - sl * x10, y01 = cl * x01 - sl * x11;
-        const double y10 = sl * x00 + cl * x10, y11 = sl * x01 + cl * x11;
-        double z00 = ch * y00 - sh * y01, z01 = sh * y00 + ch * y01;
-        double z10 = ch * y10 - sh * y11, z11 = sh * y10 + ch * y11;
-        if (t == u && sl != 0.0) {
-          z01 = 0.0;
-          z10 = 0.0;
-        }
-        const int r0 = tour_next(2 * t), r1 = tour_next(2 * t + 1);
-        const int c0 = tour_next(2 * u), c1 = tour_next(2 * u + 1);
-        Go[r0][c0] = z00;
-        Go[r0][c1] = up ? z01 : z10;
-        Go[r1][c0] = up ? z10 : z01;
-        Go[r1][c1] = z11;
-      }
-      {  // Q <- Q J on the lane's column, then the column moves with its element
-        const double c = L.cs[qpair], sn = L.sn[qpair];
-        const bool first = (lane & 1) == 0;
+      for (int k = 0; k < PH; ++k) P[k] = L.cs[0][rg * PH + k + 1];
+      static_for<0, QD>(q_odd);
+      __builtin_amdgcn_sched_barrier(0);
+      C = Cn;
+      d0 = nd.x;
+      d1 = nd.y;
+      double lo[PH][2];  // rows 2k+1 before the row rotation leaves
 #pragma unroll
-        for (int r = 0; r < RPW; ++r) {
-          const double pv = dpp_d<0xB1, 0xf>(q[r]);  // the pair partner's value (quad_perm [1,0,3,2])
-          const double nv = first ? c * q[r] - sn * pv : sn * pv + c * q[r];
-          q[r] = __shfl(nv, qsrc, 64);
+      for (int k = 0; k < PH; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const double x = g[2 * k][h], y = g[2 * k + 1][h];
+          g[2 * k][h] = P[k].x * y + P[k].y * x;
+          lo[k][h] = P[k].x * x - P[k].y * y;
         }
+#pragma unroll
+      for (int k = 0; k < PH; ++k) {  // columns of the rows 2k: the next couplings
+        const double x = g[2 * k][0], y = g[2 * k][1];
+        g[2 * k][0] = C.x * y + C.y * x;
+        g[2 * k][1] = C.x * x - C.y * y;
       }
+      r.a = d1;
+      r.b = lane_next(d0);
+      r.g = coupling(k1);
+      static_for<0, NST>([&](auto st) {
+        r.stage<st>(floor2);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<QD + st * QI / NST, QD + (st + 1) * QI / NST>(q_even);
+        static_for<st * PH / NST, (st + 1) * PH / NST>([&](auto k) {
+          const double x = lo[k][0], y = lo[k][1];
+          g[2 * k + 1][0] = C.x * y + C.y * x;
+          g[2 * k + 1][1] = C.x * x - C.y * y;
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    {  // odd round
+      L.cs[1][w1] = make_double2(r.c, r.s);
+      L.nd[1][w1] = make_double2(r.b + r.tg, r.a - r.tg);
+      rot |= own1 && r.act;
+      *reinterpret_cast<double2 *>(&L.edge[0][rg][2 * t]) = make_double2(g[0][0], g[0][1]);
+      *reinterpret_cast<double2 *>(&L.edge[1][rg][2 * t]) = make_double2(g[HR - 1][0], g[HR - 1][1]);
       __syncthreads();
-      cur ^= 1;
-    }
-    const int any = L.rot_any;
-    if (!any) break;
-  }
-  double (*Qb)[66] = L.G[cur ^ 1];
+      const double2 Cun = L.cs[1][t], Cln = L.cs[1][t + 1];
+      const double2 nu = L.nd[1][t], nl = L.nd[1][t + 1];
+      double2 P[PH + 1];
 #pragma unroll
-  for (int r = 0; r < RPW; ++r) Qb[wave * RPW + r][lane] = q[r];
-  __syncthreads();
-  return cur;
-}
-
-// slot_of as eig_order, from the diagonal of G: the rank of slot r (eigenvalues descending, ties
-// by slot) counted by NTE / 64 thread groups over slices of the other slots
-template <int NTE>
-__device__ inline void tour_order(const double (*G)[66], int *slot_of, int *rank, int np, int nq) {
-  constexpr int NG = NTE / 64, PER = 64 / NG;
-  const int r = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  auto valid = [&](int x) { return x < 32 ? (x < np) : (x - 32 < nq); };
-  if (threadIdx.x < 64) rank[r] = 0;
-  __syncthreads();
-  if (valid(r)) {
-    const double lr_ = G[r][r];
-    int cnt = 0;
+      for (int k = 0; k <= PH; ++k) P[k] = L.cs[1][rg * PH + k];
+      const double2 ep = *reinterpret_cast<const double2 *>(&L.edge[1][rp][2 * t]);
+      const double2 en = *reinterpret_cast<const double2 *>(&L.edge[0][rn][2 * t]);
+      static_for<0, QD>(q_even);
+      __builtin_amdgcn_sched_barrier(0);
+      Cu = Cun;
+      Cl = Cln;
+      d0 = t > 0 ? nu.y : d0;
+      d1 = t < LPG - 1 ? nl.x : d1;
 #pragma unroll
-    for (int m = 0; m < PER; ++m) {
-      const int o = grp * PER + m;
-      if (o != r && valid(o)) {
-        const double lo = G[o][o];
-        cnt += (lo > lr_ || (lo == lr_ && o < r)) ? 1 : 0;
+      for (int h = 0; h < 2; ++h) {
+        const double first = P[0].x * (h ? ep.y : ep.x) - P[0].y * g[0][h];
+        const double last = P[PH].x * (h ? en.y : en.x) + P[PH].y * g[HR - 1][h];
+#pragma unroll
+        for (int k = 0; k + 1 < PH; ++k) {
+          const double x = g[2 * k + 1][h], y = g[2 * k + 2][h];
+          g[2 * k + 1][h] = P[k + 1].x * y + P[k + 1].y * x;
+          g[2 * k + 2][h] = P[k + 1].x * x - P[k + 1].y * y;
+        }
+        g[0][h] = first;
+        g[HR - 1][h] = last;
       }
+#pragma unroll
+      for (int k = 0; k < PH; ++k) {
+        const double x = g[2 * k][0], y = g[2 * k][1];
+        g[2 * k][0] = Cu.x * lane_prev(y) - Cu.y * x;
+        g[2 * k][1] = Cl.x * lane_next(x) + Cl.y * y;
+      }
+      r.a = d0;
+      r.b = d1;
+      r.g = coupling(k0);
+      static_for<0, NST>([&](auto st) {
+        r.stage<st>(floor2);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<QD + st * QI / NST, QD + (st + 1) * QI / NST>(q_odd);
+        static_for<st * PH / NST, (st + 1) * PH / NST>([&](auto k) {
+          const double x = g[2 * k + 1][0], y = g[2 * k + 1][1];
+          g[2 * k + 1][0] = Cu.x * lane_prev(y) - Cu.y * x;
+          g[2 * k + 1][1] = Cl.x * lane_next(x) + Cl.y * y;
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
     }
-    if (cnt) atomicAdd(&rank[r], cnt);
   }
-  __syncthreads();
-  if (threadIdx.x < 64 && valid(r)) {
-    const int k = rank[r];
-    slot_of[k < np ? k : 32 + (k - np)] = r;
-  }
-  __syncthreads();
+  static_for<0, QD>(q_odd);
+  return rot;
 }
 
+// The eigen step of a block pair: the K-split partial Grams summed, the outer test, one odd-even sweep
+// (or inner_max) and the pair's rotation Qt with its rows in decreasing order of the eigenvalues.
+// Bound by the chain of 64 rounds on one compute unit: about 0.5 us a round, of which the FP64
+// instructions of the four waves (one per SIMD, 64 values a lane) issue for about 0.37 us and the
+// rotations' way through LDS and the barrier take the rest.  Four waves: with eight the rotation chain
+// and its LDS reads are repeated by twice as many waves (41.0 against 39.3 us a launch).  Measured at 331 x 517
+// (six pairs): 84 us a launch with the matrix in LDS, 41 us in this form.
 // grid (pairs, matrices)
-constexpr int EIG_NT = 512;
-constexpr int KS_MAX = 16;  // K splits of the Gram: at most ceil(4096 / 256)
-__global__ __launch_bounds__(EIG_NT) void eigen_kernel(const SvdMat *mats, int step) {
-  __shared__ EigTour L;
+constexpr int EIG_NW = 4, EIG_NT = 64 * EIG_NW;
+static_assert(EIG_NT / 64 == 4, "the ranking below takes four lanes per element");
+__global__ __launch_bounds__(EIG_NT) __attribute__((amdgpu_waves_per_eu(1, 2))) void eigen_kernel(const SvdMat *mats, int step) {
+  using S = OeShape<64, EIG_NW>;
+  __shared__ OeLds<64, EIG_NW> L;
+  __shared__ double diag[64];   // by slot while testing, by element while ranking
+  __shared__ int rank[64];
   const SvdMat &a = mats[blockIdx.y];
   const int pair = blockIdx.x;
   if (!a.active || a.fused || step >= a.nb - 1 || pair >= a.nb / 2) return;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int t = lane & (S::LPG - 1), rg = wave * S::GPW + lane / S::LPG;
   int p, q;
   rr_pair(a.nb, step, pair, p, q);
   const int np = block_rows(a.Ra, p), nq = block_rows(a.Ra, q);
@@ -598,47 +685,108 @@ __global__ __launch_bounds__(EIG_NT) void eigen_kernel(const SvdMat *mats, int s
     return;
   }
   auto valid = [&](int r) { return r < 32 ? (r < np) : (r - 32 < nq); };
-  // the K-split partial Grams (at most KS_MAX), summed in split order; only the upper triangle
-  // is read (rows along the lanes, so every load is one contiguous segment) and mirrored, and
-  // all partials of a thread's elements are loaded before the first sum
-  const double *Gp = a.gram + (int64_t)pair * a.ksplit * 4096;
+  // the K-split partial Grams summed in split order; this lane's elements are 16-byte pairs of HR rows
+  const double *Gp = a.gram + (int64_t)pair * a.ksplit * 4096 + (int64_t)S::HR * rg * 64 + 2 * t;
   const int nks = a.ksplit;
-  constexpr int EPP = 4;  // elements per thread and pass: EPP x KS_MAX loads in flight
-  for (int e0 = tid; e0 < 4096; e0 += EPP * EIG_NT) {
-    double part[EPP][KS_MAX];
+  double g[S::HR][2], v[S::HR][2];
 #pragma unroll
-    for (int h = 0; h < EPP; ++h) {
-      const int e = e0 + h * EIG_NT, i = e >> 6, j = e & 63;
+  for (int i = 0; i < S::HR; ++i) g[i][0] = g[i][1] = 0.0;
+  int ks = 0;
+  for (; ks + 4 <= nks; ks += 4) {
+    double2 part[4][S::HR];
 #pragma unroll
-      for (int ks = 0; ks < KS_MAX; ++ks) part[h][ks] = (ks < nks && i <= j) ? Gp[(int64_t)ks * 4096 + e] : 0.0;
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < S::HR; ++i)
+        part[u][i] = *reinterpret_cast<const double2 *>(Gp + (int64_t)(ks + u) * 4096 + 64 * i);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < S::HR; ++i) {
+        g[i][0] += part[u][i].x;
+        g[i][1] += part[u][i].y;
+      }
+  }
+  for (; ks < nks; ++ks)
+#pragma unroll
+    for (int i = 0; i < S::HR; ++i) {
+      const double2 x = *reinterpret_cast<const double2 *>(Gp + (int64_t)ks * 4096 + 64 * i);
+      g[i][0] += x.x;
+      g[i][1] += x.y;
     }
+  const double floor2 = row_floor2(a, *a.fro2);
 #pragma unroll
-    for (int h = 0; h < EPP; ++h) {
-      const int e = e0 + h * EIG_NT, i = e >> 6, j = e & 63;
-      if (i > j) continue;
-      double v = 0.0;
+  for (int i = 0; i < S::HR; ++i) {
+    const int r = S::HR * rg + i;
+    if (r == 2 * t) diag[r] = g[i][0];
+    if (r == 2 * t + 1) diag[r] = g[i][1];
+  }
+  __syncthreads();
+  double d0 = diag[2 * t], d1 = diag[2 * t + 1];
+  // outer test |g_ij| <= tol sqrt(g_ii g_jj) on the rows above the floor, squared
+  int need = 0;
+  const double tol2 = a.tol * a.tol, lo2 = fmax(floor2, 0.0);
 #pragma unroll
-      for (int ks = 0; ks < KS_MAX; ++ks)
-        if (ks < nks) v += part[h][ks];
-      v = (valid(i) && valid(j)) ? v : 0.0;
-      L.G[0][i][j] = v;
-      L.G[0][j][i] = v;
+  for (int i = 0; i < S::HR; ++i) {
+    const int r = S::HR * rg + i;
+    const double dr = diag[r];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double dc = h ? d1 : d0;
+      need |= (int)(r != 2 * t + h) & (int)(dr > lo2) & (int)(dc > lo2) & (int)(g[i][h] * g[i][h] > tol2 * (dr * dc));
+      v[i][h] = r == 2 * t + h ? 1.0 : 0.0;
     }
   }
-  const double floor2 = row_floor2(a, *a.fro2);
-  if (!tour_needs_rotation<EIG_NT>(L, a.tol, floor2)) {
+  if (!__syncthreads_or(need)) {
     if (tid == 0) *skip = 1;
     return;
   }
   if (tid == 0) atomicAdd(a.ctr, 1);
-  const int cur = eig_tour<EIG_NT>(L, a.inner_max, floor2);
-  tour_order<EIG_NT>(L.G[cur], L.slot_of, L.rank, np, nq);
-  const double(*Q)[66] = L.G[cur ^ 1];
-  double *Qt = a.qt + (int64_t)pair * 4096;
-  for (int e = tid; e < 4096; e += EIG_NT) {
-    const int so = e >> 6, ri = e & 63;
-    Qt[e] = (valid(so) && valid(ri)) ? Q[ri][L.slot_of[so]] : 0.0;
+  int rev = 0;  // the slots hold the elements in reversed order
+  for (int sweep = 0; sweep < a.inner_max; ++sweep) {
+    const int rot = oe_sweep<64, EIG_NW>(L, g, v, d0, d1, floor2);
+    rev ^= 1;
+    if (a.inner_max > 1 && !__syncthreads_or(rot)) break;
   }
+  // output rows in decreasing order of the eigenvalues (ties: lower element first), the np largest
+  // to block p; element e of the pair sits in slot e, or 63 - e after an odd number of sweeps
+  const int e0 = rev ? 63 - 2 * t : 2 * t, e1 = rev ? e0 - 1 : e0 + 1;
+  if (rg == 0) {
+    diag[e0] = d0;
+    diag[e1] = d1;
+  }
+  __syncthreads();
+  {  // four lanes per element, each counting a quarter of the others
+    constexpr int PER = 64 / (EIG_NT / 64);
+    const int e = tid / (EIG_NT / 64), o0 = (tid % (EIG_NT / 64)) * PER;
+    const double mine = diag[e];
+    int cnt = 0;
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+      const int o = o0 + m;
+      const double x = diag[o];
+      cnt += (int)valid(o) & ((int)(x > mine) | ((int)(x == mine) & (int)(o < e)));
+    }
+    cnt += __shfl_xor(cnt, 1, 64);
+    cnt += __shfl_xor(cnt, 2, 64);
+    if (o0 == 0) rank[e] = cnt < np ? cnt : 32 + (cnt - np);
+  }
+  __syncthreads();
+  // Qt row rank[e] <- column of element e: this lane's HR consecutive entries of it
+  double *Qt = a.qt + (int64_t)pair * 4096;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = h ? e1 : e0;
+    const bool ve = valid(e);
+    double *row = Qt + (ve ? rank[e] : 0) * 64 + S::HR * rg;
+    if (ve)
+#pragma unroll
+      for (int i = 0; i < S::HR; i += 2)
+        *reinterpret_cast<double2 *>(row + i) = make_double2(v[i][h], v[i + 1][h]);
+  }
+  // rows and columns of the slots without a row are zero
+  for (int e = tid; e < 4096; e += EIG_NT)
+    if (!valid(e >> 6)) Qt[e] = 0.0;
   if (tid == 0) *skip = 0;
 }
 
