@@ -7,10 +7,12 @@
 
 namespace tna {
 
+// (with every row written and bound control on, the old value is never used: no move to set it)
 template <int CTRL, int ROWS>
 __device__ inline double dpp_d(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  constexpr bool all = ROWS == 0xf;
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, all);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, all);
   return __hiloint2double(hi, lo);
 }
 
@@ -21,6 +23,23 @@ __device__ inline double row16_sum(double v) {
   v += dpp_d<0x141, 0xf>(v);  // row_half_mirror
   v += dpp_d<0x140, 0xf>(v);  // row_mirror
   return v;
+}
+
+// the same for three values, their steps taken in turn (a DPP move reads its source two wait states
+// after it was written)
+__device__ inline void row16_sum3(double &a, double &b, double &c) {
+#define TNA_SUM3(CTRL)                                                                          \
+  {                                                                                             \
+    const double x = dpp_d<CTRL, 0xf>(a), y = dpp_d<CTRL, 0xf>(b), z = dpp_d<CTRL, 0xf>(c);      \
+    a += x;                                                                                     \
+    b += y;                                                                                     \
+    c += z;                                                                                     \
+  }
+  TNA_SUM3(0xB1)
+  TNA_SUM3(0x4E)
+  TNA_SUM3(0x141)
+  TNA_SUM3(0x140)
+#undef TNA_SUM3
 }
 
 // sum over the whole wavefront; the total lands in lane 63

@@ -187,11 +187,18 @@ struct SvdMat {
 };
 struct SvdGroup {
   DevBuf desc, work_d, work_i;
-  void *host = nullptr;
-  size_t host_cap = 0;
+  // pinned staging of the descriptors, used in turn; done: the last copy out of it
+  static constexpr int NSTAGE = 4;
+  struct Stage {
+    void *host = nullptr;
+    size_t cap = 0;
+    hipEvent_t done = nullptr;
+  };
+  Stage stage[NSTAGE];
+  int next_stage = 0;
+  // pinned, written by status_kernel: two counters and (|A|_F^2, largest trailing row norm^2) per matrix
   int *host_ctr = nullptr;
-  double *host_fro = nullptr;  // pinned: squared Frobenius norms of the inputs (finiteness check), then
-                               // (|A|_F^2, largest trailing row norm^2) pairs during a QR start
+  double *host_fro = nullptr;
   void release();
 };
 // orient (square matrices only): 0 by shape (rows of A), 1 rows of A, 2 rows of A^T (columns of A)

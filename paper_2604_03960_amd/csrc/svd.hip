@@ -94,7 +94,8 @@ struct RotChain {
   double a, b, g;  // inputs: the 2 x 2 block [[a, g], [g, b]]
   double dl, x, y, e, ir, c2, ic, c, s, tg;
   bool act;
-  template <int K>
+  // (TEST off: the caller decides whether the rotation acts)
+  template <int K, bool TEST = true>
   __device__ __forceinline__ void stage(double floor2) {
     constexpr double tol_in = 4.0 * 1.1102230246251565e-16;
     if constexpr (K == 0) {
@@ -102,7 +103,7 @@ struct RotChain {
       x = fma(dl, dl, 4.0 * g * g);
     } else if constexpr (K == 1) {
       y = __builtin_amdgcn_rsq(x);
-      act = a > floor2 && b > floor2 && g * g > tol_in * tol_in * fabs(a * b);
+      act = TEST ? (a > floor2 && b > floor2 && g * g > tol_in * tol_in * fabs(a * b)) : true;
     } else if constexpr (K == 2) {
       e = fma(-(x * y), y, 1.0);
     } else if constexpr (K == 3) {
@@ -253,20 +254,6 @@ __global__ __launch_bounds__(256) void gram_kernel(const SvdMat *mats, int step)
 }
 
 // -------------------------------------------------------------- eigen
-// Two-sided cyclic Jacobi on the 64 x 64 Gram of a block pair, in LDS.
-struct EigLds {
-  double G[64][65];
-  double Q[64][65];
-  double cs[32], sn[32];
-  int pi[32], pj[32];
-  int rot_any, need;
-  int slot_of[64];
-  int vs[64];                   // valid slots in order
-  unsigned short sched[63][32]; // round-robin pairs (i | j << 8) of one sweep
-  unsigned short pcol[63][64];  // per round and column: partner | pair << 6 | (first of its pair) << 11
-  double rc[63][32], rs[63][32];  // the rotations of one inner sweep, applied to Q after it
-};
-
 // Rows whose squared norm is at or below row_floor2 = (0.1 eps C)^2 |A|_F^2 are at the
 // rounding level of the rotations: their directions are noise, so pairs with such a
 // row are neither tested nor rotated (the relative test could never settle on them).
@@ -281,170 +268,6 @@ __device__ inline double row_floor2(const SvdMat &a, double fro2) {
   if (a.precond && !a.rows_scaled) return 0.0;
   const double f = fmax(0.1 * EPS53 * (double)a.C, a.rows_scaled ? a.noise_rel : 0.0);
   return f * f * fro2;
-}
-
-// Outer test: does any pair of rows above the floor fail |g_ij| <= tol sqrt(g_ii g_jj)?
-template <int NTE>
-__device__ inline bool eig_needs_rotation(EigLds &L, double tol, double floor2) {
-  const int tid = threadIdx.x;
-  if (tid == 0) L.need = 0;
-  __syncthreads();
-  int loc = 0;
-  for (int e = tid; e < 4096; e += NTE) {
-    const int i = e >> 6, j = e & 63;
-    if (i < j) {
-      const double gii = L.G[i][i], gjj = L.G[j][j], gij = L.G[i][j];
-      if (gii > floor2 && gjj > floor2 && gii > 0.0 && gjj > 0.0 && fabs(gij) > tol * sqrt(gii * gjj)) loc = 1;
-    }
-  }
-  if (__any(loc) && (tid & 63) == 0) atomicOr(&L.need, 1);
-  __syncthreads();
-  return L.need != 0;
-}
-
-// Q <- Q J_1 ... J_nr for the rotations logged over one inner sweep: each wave holds 64 / waves rows
-// of Q in registers, lane l column l; a rotation on columns (i, j) takes Q[k][i] <- c Q[k][i] - s Q[k][j]
-// and Q[k][j] <- s Q[k][i] + c Q[k][j], the partner's value arriving by a lane shuffle.
-template <int NTE>
-__device__ inline void eig_apply_log(EigLds &L, int nr) {
-  constexpr int RPW = 64 / (NTE / 64);  // rows per wave
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double q[RPW];
-#pragma unroll
-  for (int r = 0; r < RPW; ++r) q[r] = L.Q[wave * RPW + r][lane];
-  for (int rr = 0; rr < nr; ++rr) {
-    const unsigned pc = L.pcol[rr][lane];
-    const int partner = pc & 63, t = (pc >> 6) & 31;
-    const bool first = (pc >> 11) & 1;
-    const double c = L.rc[rr][t], sn = partner == lane ? 0.0 : L.rs[rr][t];
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-      const double pv = __shfl(q[r], partner, 64);
-      if (sn != 0.0) q[r] = first ? c * q[r] - sn * pv : sn * pv + c * q[r];
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < RPW; ++r) L.Q[wave * RPW + r][lane] = q[r];
-  __syncthreads();
-}
-
-// Q <- Q J over sweeps of a round-robin ordering of the nv valid slots (np of block p at
-// 0.., nq of block q at 32..) until a sweep rotates nothing (or inner_max sweeps); the
-// diagonal of G ends as the eigenvalues.  With nv odd a dummy index sits out each round.
-// The slot pairs of every round are tabulated in LDS once per call.
-template <int NTE>
-__device__ inline void eig_inner(EigLds &L, int inner_max, double floor2, int np, int nq) {
-  const int tid = threadIdx.x;
-  const int nv = np + nq, nvp = nv + (nv & 1), P = nvp / 2;
-  if (tid < 64) L.vs[tid] = tid < np ? tid : 32 + (tid - np);  // entries >= nv unused
-  __syncthreads();
-  // pair table: (i, j) with i <= j; a pair with the dummy becomes (x, x) and rotates nothing,
-  // but its row still takes the partner pairs' column rotations
-  for (int e = tid; e < (nvp - 1) * P; e += NTE) {
-    const int rr = e / P, t = e - rr * P;
-    int ia, ib;
-    if (t == 0) { ia = rr % (nvp - 1); ib = nvp - 1; }
-    else { ia = (rr + t) % (nvp - 1); ib = (rr - t + nvp - 1) % (nvp - 1); }
-    int i = ia < nv ? L.vs[ia] : -1, j = ib < nv ? L.vs[ib] : -1;
-    if (i < 0) i = j;
-    if (j < 0) j = i;
-    L.sched[rr][t] = (unsigned short)((i < j ? i : j) | ((i < j ? j : i) << 8));
-  }
-  // column view of the same table (columns outside the valid slots are their own partner)
-  for (int e = tid; e < (nvp - 1) * 64; e += NTE) L.pcol[e >> 6][e & 63] = (unsigned short)(e & 63);
-  __syncthreads();
-  for (int e = tid; e < (nvp - 1) * P; e += NTE) {
-    const int rr = e / P, t = e - rr * P;
-    const unsigned pr = L.sched[rr][t];
-    const int i = pr & 0xff, j = pr >> 8;
-    if (i != j) {
-      L.pcol[rr][i] = (unsigned short)(j | (t << 6) | (1 << 11));
-      L.pcol[rr][j] = (unsigned short)(i | (t << 6));
-    }
-  }
-  const double tol_in = 4.0 * EPS53;
-  for (int sweep = 0; sweep < inner_max; ++sweep) {
-    __syncthreads();  // every thread has read rot_any of the previous sweep (and the table is set)
-    if (tid == 0) L.rot_any = 0;
-    __syncthreads();
-    for (int rr = 0; rr < nvp - 1; ++rr) {
-      // rotation J = [[c, s], [-s, c]] on (i, j), i < j, zeroing g_ij:
-      // t = sign(d) 2 g_ij / (|d| + sqrt(d^2 + 4 g_ij^2)), d = g_jj - g_ii; c = 1 / sqrt(1 + t^2)
-      if (tid < P) {
-        const unsigned pr = L.sched[rr][tid];
-        const int i = pr & 0xff, j = pr >> 8;
-        double c = 1.0, s = 0.0;
-        if (i != j) {
-          const double gii = L.G[i][i], gjj = L.G[j][j], gij = L.G[i][j];
-          if (gii > floor2 && gjj > floor2 && gij * gij > tol_in * tol_in * fabs(gii * gjj)) {
-            jacobi_rot(gii, gjj, gij, c, s);
-            L.rot_any = 1;
-          }
-        }
-        L.cs[tid] = c; L.sn[tid] = s; L.pi[tid] = i; L.pj[tid] = j;
-        L.rc[rr][tid] = c; L.rs[rr][tid] = s;
-      }
-      __syncthreads();
-      // G <- J^T G J one 2 x 2 block (pair t rows, pair u columns) at a time, t <= u, and
-      // the mirror block written from the same values so G stays exactly symmetric.  For
-      // even P, rows t and P - 1 - t of the block triangle go together (P + 1 blocks per
-      // row pair); for odd P the square is walked and its lower half skipped.
-      const int nblk = (P & 1) ? P * P : (P / 2) * (P + 1);
-      for (int e = tid; e < nblk; e += NTE) {
-        int t, u;
-        if (P & 1) {
-          t = e / P;
-          u = e - t * P;
-          if (u < t) continue;
-        } else {
-          const int rp = e / (P + 1), off = e - rp * (P + 1);
-          if (off < P - rp) { t = rp; u = rp + off; }
-          else { t = P - 1 - rp; u = t + (off - (P - rp)); }
-        }
-        const double st = L.sn[t], su = L.sn[u];
-        if (st == 0.0 && su == 0.0) continue;
-        const double ct = L.cs[t], cu = L.cs[u];
-        const int a0 = L.pi[t], a1 = L.pj[t], b0 = L.pi[u], b1 = L.pj[u];
-        const double x00 = L.G[a0][b0], x01 = L.G[a0][b1], x10 = L.G[a1][b0], x11 = L.G[a1][b1];
-        const double y00 = ct * x00 - st * x10, y01 = ct * x01 - st * x11;
-        const double y10 = st * x00 + ct * x10, y11 = st * x01 + ct * x11;
-        const double z00 = cu * y00 - su * y01, z01 = su * y00 + cu * y01;
-        const double z10 = cu * y10 - su * y11, z11 = su * y10 + cu * y11;
-        if (t == u) {
-          L.G[a0][a0] = z00; L.G[a1][a1] = z11; L.G[a0][a1] = 0.0; L.G[a1][a0] = 0.0;
-        } else {
-          // a dummy pair has a0 == a1 (identity rotation): both writes carry the same value
-          L.G[a0][b0] = z00; L.G[a0][b1] = z01; L.G[a1][b0] = z10; L.G[a1][b1] = z11;
-          L.G[b0][a0] = z00; L.G[b1][a0] = z01; L.G[b0][a1] = z10; L.G[b1][a1] = z11;
-        }
-      }
-      __syncthreads();
-    }
-    eig_apply_log<NTE>(L, nvp - 1);
-    const int any = L.rot_any;
-    if (!any) break;
-  }
-}
-
-// slot_of[so] = eigen-slot whose vector becomes output row so: eigenvalues descending
-// (ties: lower slot first), the np largest to block p, the rest to block q
-__device__ inline void eig_order(EigLds &L, int np, int nq) {
-  const int r = threadIdx.x;
-  if (r < 64) {
-    const bool vr = r < 32 ? (r < np) : (r - 32 < nq);
-    if (vr) {
-      const double lr_ = L.G[r][r];
-      int rank = 0;
-      for (int o = 0; o < 64; ++o) {
-        const bool vo = o < 32 ? (o < np) : (o - 32 < nq);
-        if (o == r || !vo) continue;
-        const double lo = L.G[o][o];
-        if (lo > lr_ || (lo == lr_ && o < r)) ++rank;
-      }
-      L.slot_of[rank < np ? rank : 32 + (rank - np)] = r;
-    }
-  }
-  __syncthreads();
 }
 
 // ---- two-sided Jacobi sweep of an N x N Gram held in registers
@@ -656,6 +479,86 @@ __device__ inline int oe_sweep(OeLds<N, NW> &L, double (&g)[OeShape<N, NW>::HR][
   return rot;
 }
 
+// The parts of the eigen step around the sweeps, for a workgroup of EIG_NW waves.
+constexpr int EIG_NW = 4, EIG_NT = 64 * EIG_NW;
+using EigShape = OeShape<64, EIG_NW>;
+using EigRegs = double[EigShape::HR][2];
+__device__ inline int eig_t() { return threadIdx.x & (EigShape::LPG - 1); }
+__device__ inline int eig_rg() { return threadIdx.x / EigShape::LPG; }
+
+// From G in registers: its diagonal (through diag[64]), Q = I, and whether any pair of rows above the
+// floor fails the outer test |g_ij| <= tol sqrt(g_ii g_jj), taken squared.  Contains a barrier.
+__device__ inline int oe_start(const EigRegs &g, EigRegs &q, double &d0, double &d1, double *diag, double tol,
+                               double floor2) {
+  const int t = eig_t(), rg = eig_rg();
+#pragma unroll
+  for (int i = 0; i < EigShape::HR; ++i) {
+    const int r = EigShape::HR * rg + i;
+    if (r == 2 * t) diag[r] = g[i][0];
+    if (r == 2 * t + 1) diag[r] = g[i][1];
+  }
+  __syncthreads();
+  d0 = diag[2 * t];
+  d1 = diag[2 * t + 1];
+  int need = 0;
+  const double tol2 = tol * tol, lo2 = fmax(floor2, 0.0);
+#pragma unroll
+  for (int i = 0; i < EigShape::HR; ++i) {
+    const int r = EigShape::HR * rg + i;
+    const double dr = diag[r];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double dc = h ? d1 : d0;
+      need |= (int)(r != 2 * t + h) & (int)(dr > lo2) & (int)(dc > lo2) & (int)(g[i][h] * g[i][h] > tol2 * (dr * dc));
+      q[i][h] = r == 2 * t + h ? 1.0 : 0.0;
+    }
+  }
+  return need;
+}
+
+// Sweeps until one rotates nothing (or inner_max); e0, e1: the elements left in the lane's slots (a
+// sweep reverses their order).
+__device__ inline void oe_sweeps(OeLds<64, EIG_NW> &L, EigRegs &g, EigRegs &q, double &d0, double &d1, int inner_max,
+                                 double floor2, int &e0, int &e1) {
+  int rev = 0;
+  for (int sweep = 0; sweep < inner_max; ++sweep) {
+    const int rot = oe_sweep<64, EIG_NW>(L, g, q, d0, d1, floor2);
+    rev ^= 1;
+    if (inner_max > 1 && !__syncthreads_or(rot)) break;
+  }
+  const int t = eig_t();
+  e0 = rev ? 63 - 2 * t : 2 * t;
+  e1 = rev ? e0 - 1 : e0 + 1;
+}
+
+// rank[e]: the output row of element e, eigenvalues in decreasing order (ties: lower element first),
+// the np largest to block p (rows 0..), the others to block q (rows 32..).  Four lanes per element,
+// each counting a quarter of the others.
+__device__ inline void oe_rank(double d0, double d1, int e0, int e1, double *diag, int *rank, int np, int nq) {
+  const int tid = threadIdx.x;
+  auto valid = [&](int r) { return r < 32 ? (r < np) : (r - 32 < nq); };
+  if (eig_rg() == 0) {
+    diag[e0] = d0;
+    diag[e1] = d1;
+  }
+  __syncthreads();
+  constexpr int LPE = EIG_NT / 64, PER = 64 / LPE;
+  static_assert(LPE == 4, "the shuffles below sum four lanes");
+  const int e = tid / LPE, o0 = (tid % LPE) * PER;
+  const double mine = diag[e];
+  int cnt = 0;
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int o = o0 + m;
+    const double x = diag[o];
+    cnt += (int)valid(o) & ((int)(x > mine) | ((int)(x == mine) & (int)(o < e)));
+  }
+  cnt += __shfl_xor(cnt, 1, 64);
+  cnt += __shfl_xor(cnt, 2, 64);
+  if (o0 == 0) rank[e] = cnt < np ? cnt : 32 + (cnt - np);
+  __syncthreads();
+}
+
 // The eigen step of a block pair: the K-split partial Grams summed, the outer test, one odd-even sweep
 // (or inner_max) and the pair's rotation Qt with its rows in decreasing order of the eigenvalues.
 // Bound by the chain of 64 rounds on one compute unit: about 0.5 us a round, of which the FP64
@@ -664,18 +567,15 @@ __device__ inline int oe_sweep(OeLds<N, NW> &L, double (&g)[OeShape<N, NW>::HR][
 // and its LDS reads are repeated by twice as many waves (41.0 against 39.3 us a launch).  Measured at 331 x 517
 // (six pairs): 84 us a launch with the matrix in LDS, 41 us in this form.
 // grid (pairs, matrices)
-constexpr int EIG_NW = 4, EIG_NT = 64 * EIG_NW;
-static_assert(EIG_NT / 64 == 4, "the ranking below takes four lanes per element");
 __global__ __launch_bounds__(EIG_NT) __attribute__((amdgpu_waves_per_eu(1, 2))) void eigen_kernel(const SvdMat *mats, int step) {
-  using S = OeShape<64, EIG_NW>;
+  using S = EigShape;
   __shared__ OeLds<64, EIG_NW> L;
   __shared__ double diag[64];   // by slot while testing, by element while ranking
   __shared__ int rank[64];
   const SvdMat &a = mats[blockIdx.y];
   const int pair = blockIdx.x;
   if (!a.active || a.fused || step >= a.nb - 1 || pair >= a.nb / 2) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int t = lane & (S::LPG - 1), rg = wave * S::GPW + lane / S::LPG;
+  const int tid = threadIdx.x, t = eig_t(), rg = eig_rg();
   int p, q;
   rr_pair(a.nb, step, pair, p, q);
   const int np = block_rows(a.Ra, p), nq = block_rows(a.Ra, q);
@@ -715,63 +615,16 @@ __global__ __launch_bounds__(EIG_NT) __attribute__((amdgpu_waves_per_eu(1, 2))) 
       g[i][1] += x.y;
     }
   const double floor2 = row_floor2(a, *a.fro2);
-#pragma unroll
-  for (int i = 0; i < S::HR; ++i) {
-    const int r = S::HR * rg + i;
-    if (r == 2 * t) diag[r] = g[i][0];
-    if (r == 2 * t + 1) diag[r] = g[i][1];
-  }
-  __syncthreads();
-  double d0 = diag[2 * t], d1 = diag[2 * t + 1];
-  // outer test |g_ij| <= tol sqrt(g_ii g_jj) on the rows above the floor, squared
-  int need = 0;
-  const double tol2 = a.tol * a.tol, lo2 = fmax(floor2, 0.0);
-#pragma unroll
-  for (int i = 0; i < S::HR; ++i) {
-    const int r = S::HR * rg + i;
-    const double dr = diag[r];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const double dc = h ? d1 : d0;
-      need |= (int)(r != 2 * t + h) & (int)(dr > lo2) & (int)(dc > lo2) & (int)(g[i][h] * g[i][h] > tol2 * (dr * dc));
-      v[i][h] = r == 2 * t + h ? 1.0 : 0.0;
-    }
-  }
+  double d0, d1;
+  const int need = oe_start(g, v, d0, d1, diag, a.tol, floor2);
   if (!__syncthreads_or(need)) {
     if (tid == 0) *skip = 1;
     return;
   }
   if (tid == 0) atomicAdd(a.ctr, 1);
-  int rev = 0;  // the slots hold the elements in reversed order
-  for (int sweep = 0; sweep < a.inner_max; ++sweep) {
-    const int rot = oe_sweep<64, EIG_NW>(L, g, v, d0, d1, floor2);
-    rev ^= 1;
-    if (a.inner_max > 1 && !__syncthreads_or(rot)) break;
-  }
-  // output rows in decreasing order of the eigenvalues (ties: lower element first), the np largest
-  // to block p; element e of the pair sits in slot e, or 63 - e after an odd number of sweeps
-  const int e0 = rev ? 63 - 2 * t : 2 * t, e1 = rev ? e0 - 1 : e0 + 1;
-  if (rg == 0) {
-    diag[e0] = d0;
-    diag[e1] = d1;
-  }
-  __syncthreads();
-  {  // four lanes per element, each counting a quarter of the others
-    constexpr int PER = 64 / (EIG_NT / 64);
-    const int e = tid / (EIG_NT / 64), o0 = (tid % (EIG_NT / 64)) * PER;
-    const double mine = diag[e];
-    int cnt = 0;
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-      const int o = o0 + m;
-      const double x = diag[o];
-      cnt += (int)valid(o) & ((int)(x > mine) | ((int)(x == mine) & (int)(o < e)));
-    }
-    cnt += __shfl_xor(cnt, 1, 64);
-    cnt += __shfl_xor(cnt, 2, 64);
-    if (o0 == 0) rank[e] = cnt < np ? cnt : 32 + (cnt - np);
-  }
-  __syncthreads();
+  int e0, e1;
+  oe_sweeps(L, g, v, d0, d1, a.inner_max, floor2, e0, e1);
+  oe_rank(d0, d1, e0, e1, diag, rank, np, nq);
   // Qt row rank[e] <- column of element e: this lane's HR consecutive entries of it
   double *Qt = a.qt + (int64_t)pair * 4096;
 #pragma unroll
@@ -896,15 +749,21 @@ __global__ __launch_bounds__(256) void apply_kernel(const SvdMat *mats, int step
 
 // -------------------------------------------------------------- whole Jacobi, one workgroup
 // Matrices with at most 64 rows to orthogonalise (one block pair) run every
-// sweep inside one workgroup: Gram on MFMA into LDS, the outer test, the inner
-// Jacobi, then the rotation of B and Jt, until a sweep needs no rotation.
+// sweep inside one workgroup: Gram on MFMA into LDS, the outer test, the Jacobi
+// sweep in registers, then the rotation of B and Jt, until a sweep needs no
+// rotation.  Bound by the 64 rounds of the sweep (about 33 us) and the walk over
+// B's column tiles; 64 rows of 64 to 128: 370 us, 1000 us with the Gram in LDS.
 // ctr[0] = 0 when converged (1 otherwise), ctr[1] = sweeps.  grid (matrices)
-__global__ __launch_bounds__(256) void jacobi_fused_kernel(const SvdMat *mats, int max_sweeps) {
-  __shared__ EigLds L;
+__global__ __launch_bounds__(EIG_NT) __attribute__((amdgpu_waves_per_eu(1, 2))) void jacobi_fused_kernel(
+    const SvdMat *mats, int max_sweeps) {
+  __shared__ OeLds<64, EIG_NW> L;
+  __shared__ double diag[64];
+  __shared__ int rank[64];
+  __shared__ double Gs[64][65];  // the Gram, then Qt's columns
   __shared__ double Xs[64][65];  // Gram staging, then apply tiles
   const SvdMat &a = mats[blockIdx.x];
   if (!a.active || a.fused != 1) return;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, t = eig_t(), rg = eig_rg();
   const int np = block_rows(a.R, 0), nq = block_rows(a.R, 1);
   auto valid = [&](int r) { return r < 32 ? (r < np) : (r - 32 < nq); };
   auto grow = [](int r) { return r; };  // blocks 0 and 1: slot r is row r
@@ -912,35 +771,42 @@ __global__ __launch_bounds__(256) void jacobi_fused_kernel(const SvdMat *mats, i
   int sw = 0, conv = 0;
   while (sw < max_sweeps) {
     ++sw;
-    v4d acc[2][2];
-    gram_acc(a, 0, 1, np, nq, 0, a.C, reinterpret_cast<double (*)[65]>(&Xs[0][0]), acc);
-    gram_store(acc, &L.Q[0][0], 65);  // raw Gram, then the symmetric copy below
-    __syncthreads();
-    for (int e = tid; e < 4096; e += 256) {
-      const int i = e >> 6, j = e & 63;
-      const int lo = i < j ? i : j, hi = i < j ? j : i;
-      L.G[i][j] = (valid(i) && valid(j)) ? L.Q[lo][hi] : 0.0;
+    {
+      v4d acc[2][2];
+      gram_acc(a, 0, 1, np, nq, 0, a.C, Xs, acc);
+      gram_store(acc, &Gs[0][0], 65);
     }
     __syncthreads();
-    for (int e = tid; e < 4096; e += 256) L.Q[e >> 6][e & 63] = ((e >> 6) == (e & 63)) ? 1.0 : 0.0;
-    if (!eig_needs_rotation<256>(L, a.tol, floor2)) {
+    double g[EigShape::HR][2], v[EigShape::HR][2], d0, d1;
+#pragma unroll
+    for (int i = 0; i < EigShape::HR; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) g[i][h] = Gs[EigShape::HR * rg + i][2 * t + h];
+    const int need = oe_start(g, v, d0, d1, diag, a.tol, floor2);
+    if (!__syncthreads_or(need)) {
       conv = 1;
       break;
     }
-    eig_inner<256>(L, a.inner_max, floor2, np, nq);
-    eig_order(L, np, nq);
-    // As[k][i] = Qt[i][k] = Q[k][slot_of[i]], written over G
-    for (int e = tid; e < 4096; e += 256) {
-      const int k = e >> 6, i = e & 63;
-      L.G[k][i] = (valid(i) && valid(k)) ? L.Q[k][L.slot_of[i]] : 0.0;
+    int e0, e1;
+    oe_sweeps(L, g, v, d0, d1, a.inner_max, floor2, e0, e1);
+    oe_rank(d0, d1, e0, e1, diag, rank, np, nq);
+    // Gs[k][i] = Qt[i][k], over the Gram
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = h ? e1 : e0;
+      if (valid(e)) {
+        const int col = rank[e];
+#pragma unroll
+        for (int i = 0; i < EigShape::HR; ++i) Gs[EigShape::HR * rg + i][col] = v[i][h];
+      }
     }
     __syncthreads();
     const int ntile_b = (a.C + 63) / 64;
-    for (int t = 0; t < ntile_b; ++t) {
-      apply_tile(a.bw, a.C, 64 * t, L.G, Xs, valid, grow);
+    for (int tl = 0; tl < ntile_b; ++tl) {
+      apply_tile(a.bw, a.C, 64 * tl, Gs, Xs, valid, grow);
       __syncthreads();
     }
-    apply_tile(a.jt, a.R, 0, L.G, Xs, valid, grow);
+    apply_tile(a.jt, a.R, 0, Gs, Xs, valid, grow);
     __syncthreads();
   }
   if (tid == 0) {
@@ -950,98 +816,199 @@ __global__ __launch_bounds__(256) void jacobi_fused_kernel(const SvdMat *mats, i
 }
 
 // -------------------------------------------------------------- one-sided Jacobi, tiny matrices
-// At most 32 rows of at most 64 columns: the cyclic one-sided (Hestenes) method directly on
-// the rows, held in LDS with Jt.  Round-robin rounds of at most 16 disjoint row pairs; the 16
-// lanes of a pair's lane group each hold 4 columns of B and 2 of Jt, the three dot products
-// are reduced with shuffles inside the group, and every round ends with one barrier.
-// Rotation and tests as in the blocked method: J = [[c, s], [-s, c]] on rows (i, j), i < j,
-// outer tolerance a.tol, rows at the rounding floor left alone.  ctr[0] = 0 when converged,
-// ctr[1] = sweeps.  grid (matrices), 256 threads.
-__global__ __launch_bounds__(256) void jacobi_tiny_kernel(const SvdMat *mats, int max_sweeps) {
-  __shared__ double Bs[32][65];
-  __shared__ double Js[32][33];
-  __shared__ int vs_dummy;
-  const SvdMat &a = mats[blockIdx.x];
-  if (!a.active || a.fused != 2) return;
+// At most 32 rows of at most 64 columns: the one-sided (Hestenes) method directly on the rows, held
+// in registers with Jt.  Odd-even transposition order as in oe_sweep: group t of 16 lanes (one DPP row)
+// holds the rows in the slots 2t and 2t+1, a lane up to 4 columns of B and 2 of Jt of each; a rotation
+// leaves its two rows exchanged.  Between the rounds one row of every group moves to its neighbour
+// through LDS: the lower one down before an odd round (pairs (2t+1, 2t+2)), the upper one up after it,
+// one barrier each.  Rotation and tests as in the blocked method, outer tolerance a.tol, rows at
+// the rounding floor left alone.  ctr[0] = 0 when converged, ctr[1] = sweeps.
+// It reads A itself (its Frobenius norm is formed on the way) and ends with the spectrum record, so such a
+// matrix takes one launch up to its spectrum.  Bound by the chain of R rounds a sweep on one compute
+// unit: dot products, their sums over 16 lanes, the rotation and the move, about 120 instructions and
+// two trips through LDS a round, 0.35 us.  64 matrices of 32 x 32 (10 sweeps): 122 us; with the rows in LDS
+// and the norm and spectrum in launches of their own 214 + 35 us.  grid (matrices), 256 threads.
+constexpr int TINY_NV = 3;  // 16-byte values of a row that a lane passes on
+struct TinyLds {
+  double2 down[17][16][TINY_NV], up[17][16][TINY_NV];
+  double red[4];
+  double sig[32], key[32];
+};
+
+// CU columns of B and JU of Jt per lane: C <= 16 CU, R <= 16 JU.  Leaves bw, jt and sig[r] = |row r|.
+template <int CU, int JU>
+__device__ __forceinline__ void jacobi_tiny_rows(const SvdMat &a, int max_sweeps, TinyLds &L, int &sw, int &conv) {
+  constexpr int NR = CU + JU, NV = (NR + 1) / 2;
+  static_assert(NV <= TINY_NV, "row in LDS");
   const int tid = threadIdx.x, t = tid >> 4, l = tid & 15;
-  const int R = a.R, C = a.C;
-  for (int e = tid; e < 32 * 64; e += 256) {
-    const int r = e >> 6, c = e & 63;
-    Bs[r][c] = (r < R && c < C) ? a.bw[(int64_t)r * C + c] : 0.0;
-  }
-  for (int e = tid; e < 32 * 32; e += 256) {
-    const int r = e >> 5, c = e & 31;
-    Js[r][c] = (r < R && c < R) ? a.jt[(int64_t)r * R + c] : 0.0;
-  }
-  (void)vs_dummy;
-  const double floor2 = row_floor2(a, *a.fro2);
-  const double tol2 = a.tol * a.tol;  // read once: inside the rounds a descriptor load is a memory round trip
-  const int nvp = R + (R & 1), P = nvp / 2;
-  int sw = 0, conv = 0;
-  __syncthreads();
+  const int R = a.R, C = a.C, P = (R + 1) >> 1;
+  double x[2 * NV], y[2 * NV];  // lower and upper row: B values, then Jt values
+  auto load = [&](int r, double(&z)[2 * NV]) {  // row r of A (of A^T when trans), Jt = I
+    static_for<0, 2 * NV>([&](auto u) {
+      z[u] = 0.0;
+      if constexpr (u < CU) {
+        const int c = l + 16 * u;
+        if (r < R && c < C) {
+          const int e = a.trans ? c * a.n + r : r * a.n + c;
+          z[u] = a.dtype == TNA_F64 ? static_cast<const double *>(a.A)[e]
+                                    : (double)static_cast<const float *>(a.A)[e];
+        }
+      } else if constexpr (u < NR) {
+        z[u] = (r < R && l + 16 * (u - CU) == r) ? 1.0 : 0.0;
+      }
+    });
+  };
+  auto put = [&](double2(*to)[TINY_NV], const double(&z)[2 * NV]) {
+    static_for<0, NV>([&](auto v) { to[l][v] = make_double2(z[2 * v], z[2 * v + 1]); });
+  };
+  auto get = [&](double2(*from)[TINY_NV], double(&z)[2 * NV]) {
+    static_for<0, NV>([&](auto v) {
+      const double2 w = from[l][v];
+      z[2 * v] = w.x;
+      z[2 * v + 1] = w.y;
+    });
+  };
+  load(2 * t, x);
+  load(2 * t + 1, y);
+  if (tid < 16) static_for<0, NV>([&](auto v) { L.down[16][l][v] = make_double2(0.0, 0.0); });
+  double ss = 0.0;
+  static_for<0, CU>([&](auto u) { ss += x[u] * x[u] + y[u] * y[u]; });
+  const double fro2 = bsum256(ss, L.red);
+  if (tid == 0) a.fro2[0] = fro2;
+  const double floor2 = row_floor2(a, fro2);
+  const double tol2 = a.tol * a.tol;
+  // rotates x against y if their coupling fails the test, and exchanges them; `idle` leaves x and
+  // zeroes y (the last slot's odd round: y is the empty row)
+  auto rotate = [&](int &rot, bool idle) {
+    double al = 0.0, be = 0.0, ga = 0.0;
+    static_for<0, CU>([&](auto u) {
+      al = fma(x[u], x[u], al);
+      be = fma(y[u], y[u], be);
+      ga = fma(x[u], y[u], ga);
+    });
+    row16_sum3(al, be, ga);
+    RotChain r;
+    r.a = al;
+    r.b = be;
+    r.g = ga;
+    static_for<0, 8>([&](auto st) { r.template stage<st, false>(floor2); });
+    const bool act = al > floor2 && be > floor2 && ga * ga > tol2 * (al * be);
+    const double c = act ? r.c : idle ? 0.0 : 1.0, s = act ? r.s : idle ? 1.0 : 0.0;
+    rot |= act;
+    static_for<0, NR>([&](auto u) {
+      const double p = x[u], q = y[u];
+      x[u] = c * q + s * p;
+      y[u] = c * p - s * q;
+    });
+  };
+  // what a group reads in place of a neighbour it lacks: the empty row above the last slot, and the
+  // first group its own lower row back
+  double2(*const from_above)[TINY_NV] = L.down[t + 1 < P ? t + 1 : 16];
+  double2(*const from_below)[TINY_NV] = t > 0 ? L.up[t] : L.down[0];
+  const bool last = t + 1 >= P;
+  sw = conv = 0;
   while (sw < max_sweeps) {
     ++sw;
     int rot = 0;
-    for (int rr = 0; rr < nvp - 1; ++rr) {
-      int i = -1, j = -1;
-      if (t < P) {  // round rr of the round-robin: 0 <= rr + t, rr - t + nvp - 1 < 2 (nvp - 1)
-        const int m1 = nvp - 1;
-        if (t == 0) { i = rr; j = m1; }
-        else {
-          i = rr + t >= m1 ? rr + t - m1 : rr + t;
-          j = rr - t + m1 >= m1 ? rr - t : rr - t + m1;
-        }
-        if (i > j) { const int q = i; i = j; j = q; }
-        if (j >= R) i = -1;  // the dummy of an odd R
-      }
-      double xa[4], ya[4], xj[2], yj[2];
-      double al = 0.0, be = 0.0, ga = 0.0;
-      if (i >= 0) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          xa[u] = Bs[i][l + 16 * u];
-          ya[u] = Bs[j][l + 16 * u];
-          al += xa[u] * xa[u];
-          be += ya[u] * ya[u];
-          ga += xa[u] * ya[u];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          xj[u] = Js[i][l + 16 * u];
-          yj[u] = Js[j][l + 16 * u];
-        }
-      }
-      // the 16 lanes of a pair are one DPP row
-      al = row16_sum(al);
-      be = row16_sum(be);
-      ga = row16_sum(ga);
-      if (i >= 0 && al > floor2 && be > floor2 && al > 0.0 && be > 0.0 && ga * ga > tol2 * (al * be)) {
-        double c, s;
-        jacobi_rot(al, be, ga, c, s);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          Bs[i][l + 16 * u] = c * xa[u] - s * ya[u];
-          Bs[j][l + 16 * u] = s * xa[u] + c * ya[u];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          Js[i][l + 16 * u] = c * xj[u] - s * yj[u];
-          Js[j][l + 16 * u] = s * xj[u] + c * yj[u];
-        }
-        rot = 1;
-      }
+#pragma unroll 1
+    for (int rr = 0; rr < P; ++rr) {
+      rotate(rot, false);
+      put(L.down[t], x);
       __syncthreads();
+      static_for<0, 2 * NV>([&](auto u) { x[u] = y[u]; });
+      get(from_above, y);
+      rotate(rot, last);
+      put(L.up[t + 1], y);
+      __syncthreads();
+      static_for<0, 2 * NV>([&](auto u) { y[u] = x[u]; });
+      get(from_below, x);
     }
-    if (!__syncthreads_or(rot)) {
+    if (!__syncthreads_or(rot && t < P)) {
       conv = 1;
       break;
     }
   }
-  for (int e = tid; e < R * C; e += 256) a.bw[e] = Bs[e / C][e % C];
-  for (int e = tid; e < R * R; e += 256) a.jt[e] = Js[e / R][e % R];
+  // an odd number of sweeps leaves the slots reversed: with an odd R the empty slot is then the first
+  const int shift = R & sw & 1;
+  auto store = [&](int r, const double(&z)[2 * NV]) {
+    double n2 = 0.0;
+    static_for<0, CU>([&](auto u) { n2 = fma(z[u], z[u], n2); });
+    n2 = row16_sum(n2);
+    if (r < 0 || r >= R) return;
+    if (l == 0) L.sig[r] = sqrt(n2);
+    static_for<0, NR>([&](auto u) {
+      if constexpr (u < CU) {
+        if (l + 16 * u < C) a.bw[r * C + l + 16 * u] = z[u];
+      } else {
+        if (l + 16 * (u - CU) < R) a.jt[r * R + l + 16 * (u - CU)] = z[u];
+      }
+    });
+  };
+  store(2 * t - shift, x);
+  store(2 * t + 1 - shift, y);
+}
+
+__global__ __launch_bounds__(256) void jacobi_tiny_kernel(const SvdMat *mats, int max_sweeps) {
+  __shared__ TinyLds L;
+  const SvdMat &a = mats[blockIdx.x];
+  if (!a.active || a.fused != 2) return;
+  const int tid = threadIdx.x, R = a.R;
+  int sw, conv;
+  if (R <= 16) {
+    if (a.C <= 16) jacobi_tiny_rows<1, 1>(a, max_sweeps, L, sw, conv);
+    else jacobi_tiny_rows<4, 1>(a, max_sweeps, L, sw, conv);
+  } else {
+    if (a.C <= 32) jacobi_tiny_rows<2, 2>(a, max_sweeps, L, sw, conv);
+    else jacobi_tiny_rows<4, 2>(a, max_sweeps, L, sw, conv);
+  }
+  double *const sig = L.sig, *const key = L.key;
   if (tid == 0) {
     a.ctr[0] = conv ? 0 : 1;
     a.ctr[1] = sw;
+  }
+  __syncthreads();
+  // the spectrum record of sort_kernel, for at most 32 values: ranks counted, sums by the first wave.
+  // With a NaN among them nothing is ranked (the caller stops at the NaN sums).
+  if (tid < 64) {
+    const double mine = tid < R ? sig[tid] : 0.0;
+    const bool nan = __any(!(mine == mine));
+    int k = 0;
+    for (int o = 0; o < R; ++o) k += (sig[o] > mine || (sig[o] == mine && o < tid)) ? 1 : 0;
+    if (tid < R) {
+      key[nan ? tid : k] = mine;
+      a.perm[nan ? tid : k] = tid;
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const double s0 = key[0], v = tid < R ? key[tid] : 0.0;
+    if (tid < R) a.S[tid] = v;
+    const double Z = wave_sum_d(v * v);
+    const double p = v * v / Z;
+    const double ent = wave_sum_d(tid < R && p > 0.0 ? -p * log(p) : 0.0);
+    if (tid == 0) {
+      a.spec[0] = Z;
+      a.spec[1] = Z == Z ? ent : Z;
+      a.spec[7] = conv ? (double)sw : -(double)sw;
+    }
+    if (tid < 16) a.spec[8 + tid] = v;
+    const unsigned long long above = __ballot(tid < R && v > a.thr);
+    const unsigned long long rank = __ballot(tid < R && v > (a.noise_rel > 0.0 ? a.noise_rel : 1e-12) * s0);
+    if (tid == 0) {
+      if (a.thr > 0.0) a.spec[24] = (double)__popcll(above);
+      a.spec[25] = (double)__popcll(rank);
+    }
+    if (a.eps_target > 0.0) {
+      double tail = v * v;  // sum over this value and the later ones
+#pragma unroll
+      for (int off = 1; off < 32; off <<= 1) {
+        const double o = __shfl_down(tail, off, 64);
+        tail += tid + off < 32 ? o : 0.0;
+      }
+      const unsigned long long meets = __ballot(tid < R && tail <= a.eps_target * a.eps_target);
+      const int first = meets ? __ffsll((unsigned long long)meets) - 1 : R;
+      if (tid == 0) a.spec[6] = (double)(first < 1 ? 1 : first);
+    }
   }
 }
 
@@ -1050,6 +1017,7 @@ __global__ __launch_bounds__(256) void jacobi_tiny_kernel(const SvdMat *mats, in
 __global__ __launch_bounds__(256) void load_kernel(const SvdMat *mats) {
   __shared__ double tile[32][33];
   const SvdMat &a = mats[blockIdx.z];
+  if (a.fused == 2) return;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int ntj = (a.n + 31) / 32, nti = (a.m + 31) / 32;
   const int t = blockIdx.x;
@@ -1084,14 +1052,21 @@ __global__ __launch_bounds__(256) void load_kernel(const SvdMat *mats) {
   }
 }
 
-// |A|_F^2 of the loaded rows in two fixed-order stages: block partials into the Gram
-// area (free until the first sweep), then one block per matrix sums them
+// |A|_F^2 of the loaded rows in two fixed-order stages: partials of 4096 elements or more by up to
+// FRO_BLOCKS blocks into the Gram area (free until the first sweep), then one block per matrix
+// sums them
 constexpr int FRO_BLOCKS = 256;
+__host__ __device__ inline int fro_blocks(int R, int C) {
+  const int64_t b = ((int64_t)R * C + 4095) / 4096;
+  return b < 1 ? 1 : b > FRO_BLOCKS ? FRO_BLOCKS : (int)b;
+}
 __global__ __launch_bounds__(256) void fro_partial_kernel(const SvdMat *mats) {
   __shared__ double red[4];
   const SvdMat &a = mats[blockIdx.z];
+  const int nb = fro_blocks(a.R, a.C);
+  if (a.fused == 2 || (int)blockIdx.x >= nb) return;
   const int64_t tot = (int64_t)a.R * a.C;
-  const int64_t chunk = (tot + FRO_BLOCKS - 1) / FRO_BLOCKS;
+  const int64_t chunk = (tot + nb - 1) / nb;
   const int64_t beg = chunk * blockIdx.x, end = beg + chunk < tot ? beg + chunk : tot;
   double v = 0.0;
   for (int64_t e = beg + threadIdx.x; e < end; e += 256) v += a.bw[e] * a.bw[e];
@@ -1101,14 +1076,28 @@ __global__ __launch_bounds__(256) void fro_partial_kernel(const SvdMat *mats) {
 __global__ __launch_bounds__(256) void fro_kernel(const SvdMat *mats) {
   __shared__ double red[4];
   const SvdMat &a = mats[blockIdx.x];
-  double v = threadIdx.x < FRO_BLOCKS ? a.gram[threadIdx.x] : 0.0;
+  if (a.fused == 2) return;
+  double v = (int)threadIdx.x < fro_blocks(a.R, a.C) ? a.gram[threadIdx.x] : 0.0;
   v = bsum256(v, red);
   if (threadIdx.x == 0) *a.fro2 = v;
 }
 
-__global__ void zero_ctr_kernel(const SvdMat *mats, int nmat) {
+// What the host decides on, written straight into its pinned memory (one store each instead of one
+// copy command per matrix): counters at hctr[2 z], hctr[2 z + 1], the two norms at hfro[2 z],
+// hfro[2 z + 1].  With reset, the counter of rotating pairs is cleared for the next sweep.
+__global__ void status_kernel(const SvdMat *mats, int nmat, int *hctr, double *hfro, int reset) {
   const int z = blockIdx.x * blockDim.x + threadIdx.x;
-  if (z < nmat && mats[z].active && !mats[z].fused) *mats[z].ctr = 0;
+  if (z >= nmat) return;
+  const SvdMat &a = mats[z];
+  if (hctr) {
+    hctr[2 * z] = a.ctr[0];
+    hctr[2 * z + 1] = a.ctr[1];
+  }
+  if (hfro) {
+    hfro[2 * z] = a.fro2[0];
+    hfro[2 * z + 1] = a.fro2[1];
+  }
+  if (reset && a.active && !a.fused) a.ctr[0] = 0;
 }
 
 // -------------------------------------------------------------- QR start
@@ -1548,7 +1537,7 @@ __global__ __launch_bounds__(256) void qr_pinv_kernel(const SvdMat *mats) {
 __global__ __launch_bounds__(256) void norms_kernel(const SvdMat *mats) {
   const SvdMat &a = mats[blockIdx.z];
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (r >= a.R) return;
+  if (a.fused == 2 || r >= a.R) return;
   const double *row = a.bw + (int64_t)r * a.C;
   double s = 0.0;
   for (int c = lane; c < a.C; c += 64) s += row[c] * row[c];
@@ -1563,6 +1552,7 @@ __global__ __launch_bounds__(1024) void sort_kernel(const SvdMat *mats) {
   __shared__ int idx[4096];
   __shared__ double red[16];
   const SvdMat &a = mats[blockIdx.x];
+  if (a.fused == 2) return;
   int P = 1;
   while (P < a.R) P <<= 1;
   for (int i = threadIdx.x; i < P; i += 1024) {
@@ -1688,7 +1678,7 @@ __global__ __launch_bounds__(1024) void sort_kernel(const SvdMat *mats) {
 __global__ __launch_bounds__(256) void trunc_kernel(const SvdMat *mats) {
   __shared__ double red[4];
   const SvdMat &a = mats[blockIdx.x];
-  if (a.k < 1) return;
+  if (a.k < 1 || a.fused == 2) return;
   const double *s = a.S;
   const int R = a.R, k = a.k, t = threadIdx.x;
   double tl = 0.0, hd = 0.0;
@@ -1749,7 +1739,7 @@ __device__ inline void write_factors(const SvdMat &a, int which, int64_t e0, int
 
 __global__ __launch_bounds__(256) void write_kernel(const SvdMat *mats) {
   const SvdMat &a = mats[blockIdx.z];
-  if (a.k < 1) return;
+  if (a.k < 1 || a.fused == 2) return;
   const int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
   if (a.out_type == TNA_F64) write_factors<double>(a, blockIdx.y, e0, stride);
   else write_factors<float>(a, blockIdx.y, e0, stride);
@@ -1804,7 +1794,7 @@ __global__ __launch_bounds__(256) void complete_kernel(const SvdMat *mats) {
   __shared__ double red[4];
   __shared__ int ok;
   const SvdMat &a = mats[blockIdx.x];
-  if (a.k < 1 || a.rows_scaled) return;  // the factor to complete leaves scaled by (near-)zero values
+  if (a.k < 1 || a.fused == 2 || a.rows_scaled) return;  // the factor to complete leaves scaled by (near-)zero values
   // only matrices with a kept null vector do any work
   const double thr = null_threshold(a);
   if (a.S[a.k - 1] > thr && a.S[a.k - 1] > 0.0) return;
@@ -1857,9 +1847,95 @@ __global__ __launch_bounds__(256) void gauge_kernel(const SvdMat *mats) {
   __shared__ double sgn;
   const SvdMat &a = mats[blockIdx.z];
   const int j = blockIdx.x;
-  if (j >= a.k) return;
+  if (j >= a.k || a.fused == 2) return;
   if (a.out_type == TNA_F64) gauge_one<double>(a, j, bv, bi, &sgn);
   else gauge_one<float>(a, j, bv, bi, &sgn);
+}
+
+// The outputs of a matrix of at most 32 rows and 64 columns (fused == 2) in one workgroup: truncation sums,
+// U and Vt through LDS, gauge and scaling; the rare matrix with kept null vectors to complete goes
+// through the general steps on its outputs instead.
+template <typename T>
+__device__ void finish_small(const SvdMat &a, double (*Us)[33], double (*Vs)[65], double *sc, double *red, double *vec,
+                             int *ok) {
+  const int tid = threadIdx.x, m = a.m, n = a.n, k = a.k, R = a.R, C = a.C;
+  T *U = static_cast<T *>(a.U);
+  T *Vt = static_cast<T *>(a.Vt);
+  const double thr = null_threshold(a);
+  if (tid < 64) {
+    const double s = tid < R ? a.S[tid] : 0.0;
+    const double tail = wave_sum_d(tid >= k ? s * s : 0.0), head = wave_sum_d(tid < k ? s * s : 0.0);
+    const double s0 = __shfl(s, 0, 64), sk1 = __shfl(s, k - 1, 64), sk = __shfl(s, k < 64 ? k : 63, 64);
+    if (tid == 0) {
+      a.spec[2] = sqrt(tail);
+      a.spec[3] = tail / a.spec[0];
+      a.spec[4] = sqrt(head);
+      a.spec[5] = (k < R && s0 > 0.0) ? (sk1 - sk) / s0 : 1.0;
+      sc[0] = sqrt(head);
+    }
+  }
+  // the rotations give one factor, the rows over their norms the other
+  auto from_rows = [&](int j, int c) {
+    const double s = a.S[j];
+    return (s > thr && s > 0.0) ? a.bw[a.perm[j] * C + c] / s : 0.0;
+  };
+  auto from_rot = [&](int j, int c) { return a.jt[a.perm[j] * R + c]; };
+  for (int e = tid; e < k * m; e += 256) {
+    const int j = e / m, i = e - j * m;
+    Us[i][j] = a.trans ? from_rows(j, i) : from_rot(j, i);
+  }
+  for (int e = tid; e < k * n; e += 256) {
+    const int j = e / n, c = e - j * n;
+    Vs[j][c] = a.trans ? from_rot(j, c) : from_rows(j, c);
+  }
+  __syncthreads();
+  const bool complete = !a.rows_scaled && !(a.S[k - 1] > thr && a.S[k - 1] > 0.0);
+  if (complete) {
+    for (int e = tid; e < m * k; e += 256) U[e] = (T)Us[e / k][e % k];
+    for (int e = tid; e < k * n; e += 256) Vt[e] = (T)Vs[e / n][e % n];
+    __syncthreads();
+    complete_one<T>(a, vec, red, ok);
+    __syncthreads();
+    for (int e = tid; e < m * k; e += 256) Us[e / k][e % k] = (double)U[e];
+    for (int e = tid; e < k * n; e += 256) Vs[e / n][e % n] = (double)Vt[e];
+    __syncthreads();
+  }
+  {  // eight lanes per column of U: its largest entry, ties to the lowest row
+    const int j = tid >> 3;
+    double best = -1.0;
+    int at = 0x7fffffff;
+    if (j < k)
+      for (int i = tid & 7; i < m; i += 8) {
+        const double v = fabs((double)(T)Us[i][j]);
+        if (v > best) { best = v; at = i; }
+      }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) {
+      const double ov = __shfl_xor(best, off, 64);
+      const int oi = __shfl_xor(at, off, 64);
+      if (ov > best || (ov == best && oi < at)) { best = ov; at = oi; }
+    }
+    if (j < k && (tid & 7) == 0) {
+      const double sg = at < m && Us[at][j] < 0.0 ? -1.0 : 1.0;
+      const double f = (a.scale_mode != 0 && sc[0] > 0.0) ? a.S[j] / sc[0] : 1.0;
+      sc[1 + j] = sg * (a.scale_mode == 2 ? f : 1.0);
+      sc[33 + j] = sg * (a.scale_mode == 1 ? f : 1.0);
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < m * k; e += 256) U[e] = (T)((double)(T)Us[e / k][e % k] * sc[1 + e % k]);
+  for (int e = tid; e < k * n; e += 256) Vt[e] = (T)((double)(T)Vs[e / n][e % n] * sc[33 + e / n]);
+}
+
+// grid (matrices)
+__global__ __launch_bounds__(256) void finish_small_kernel(const SvdMat *mats) {
+  __shared__ double Us[64][33], Vs[32][65];
+  __shared__ double sc[1 + 2 * 32], red[4], vec[64];
+  __shared__ int ok;
+  const SvdMat &a = mats[blockIdx.x];
+  if (a.k < 1 || a.fused != 2) return;
+  if (a.out_type == TNA_F64) finish_small<double>(a, Us, Vs, sc, red, vec, &ok);
+  else finish_small<float>(a, Us, Vs, sc, red, vec, &ok);
 }
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
@@ -1954,20 +2030,25 @@ void svd_bind_work(SvdMat *a, double *dw, int *iw) {
   }
 }
 
+// The descriptors through one of SvdGroup::NSTAGE pinned buffers in turn: a buffer is written again only
+// when its last copy is done, which with several of them costs no wait in the course of a group.
 static tna_status upload(const std::vector<SvdMat> &mats, SvdGroup &g, hipStream_t s) {
   const size_t bytes = sizeof(SvdMat) * mats.size();
   TNA_TRY(g.desc.ensure(bytes));
-  if (g.host_cap < bytes) {
-    if (g.host) (void)hipHostFree(g.host);
-    g.host = nullptr;
-    g.host_cap = 0;
-    TNA_HIP(hipHostMalloc(&g.host, bytes * 2, hipHostMallocDefault));
-    g.host_cap = bytes * 2;
+  SvdGroup::Stage &st = g.stage[g.next_stage];
+  g.next_stage = (g.next_stage + 1) % SvdGroup::NSTAGE;
+  if (!st.done) TNA_HIP(hipEventCreateWithFlags(&st.done, hipEventDisableTiming));
+  else TNA_HIP(hipEventSynchronize(st.done));
+  if (st.cap < bytes) {
+    if (st.host) (void)hipHostFree(st.host);
+    st.host = nullptr;
+    st.cap = 0;
+    TNA_HIP(hipHostMalloc(&st.host, bytes * 2, hipHostMallocDefault));
+    st.cap = bytes * 2;
   }
-  // the previous upload may still be in flight from this staging buffer
-  TNA_HIP(hipStreamSynchronize(s));
-  std::memcpy(g.host, mats.data(), bytes);
-  TNA_HIP(hipMemcpyAsync(g.desc.ptr, g.host, bytes, hipMemcpyHostToDevice, s));
+  std::memcpy(st.host, mats.data(), bytes);
+  TNA_HIP(hipMemcpyAsync(g.desc.ptr, st.host, bytes, hipMemcpyHostToDevice, s));
+  TNA_HIP(hipEventRecord(st.done, s));
   return TNA_OK;
 }
 
@@ -2043,29 +2124,55 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     max_steps = std::max(max_steps, a.nb - 1);
     max_r4 = std::max(max_r4, ceil_div(a.R, 4));
   }
-  TNA_TRY(upload(mats, g, s));
-  const SvdMat *d = g.desc.as<SvdMat>();
-  hipLaunchKernelGGL(load_kernel, dim3(max_tiles_load, 1, nm), dim3(256), 0, s, d);
-  hipLaunchKernelGGL(fro_partial_kernel, dim3(FRO_BLOCKS, 1, nm), dim3(256), 0, s, d);
-  hipLaunchKernelGGL(fro_kernel, dim3(nm), dim3(256), 0, s, d);
-  TNA_LAUNCHED("svd.load");
-  if (!g.host_ctr) TNA_HIP(hipHostMalloc((void **)&g.host_ctr, sizeof(int) * 8192, hipHostMallocDefault));
   if (nm > 4096) {
     set_error("svd: at most 4096 matrices per group");
     return TNA_ERR_ARG;
   }
+  if (!g.host_ctr) TNA_HIP(hipHostMalloc((void **)&g.host_ctr, sizeof(int) * 2 * 4096, hipHostMallocDefault));
+  if (!g.host_fro) TNA_HIP(hipHostMalloc((void **)&g.host_fro, sizeof(double) * 2 * 4096, hipHostMallocDefault));
+  TNA_TRY(upload(mats, g, s));
+  const SvdMat *d = g.desc.as<SvdMat>();
+  int n_two = 0, n_tiny = 0;
+  for (auto &a : mats) {
+    n_two += a.fused == 1;
+    n_tiny += a.fused == 2;
+  }
+  const int nfused = n_two + n_tiny;
+  auto read_status = [&](bool ctr, bool fro, int reset) -> tna_status {
+    hipLaunchKernelGGL(status_kernel, dim3(ceil_div(nm, 64)), dim3(64), 0, s, d, nm, ctr ? g.host_ctr : nullptr,
+                       fro ? g.host_fro : nullptr, reset);
+    TNA_LAUNCHED("svd.status");
+    TNA_HIP(hipStreamSynchronize(s));
+    return TNA_OK;
+  };
   // a NaN or Inf anywhere in an input shows in its squared Frobenius norm; the callers that defer
   // their reads (the sweep engine) check the spectrum sums they read anyway
-  if (!defer_fused) {
-    if (!g.host_fro) TNA_HIP(hipHostMalloc((void **)&g.host_fro, sizeof(double) * 3 * 4096, hipHostMallocDefault));
+  auto check_finite_norms = [&]() -> tna_status {
     for (int z = 0; z < nm; ++z)
-      TNA_HIP(hipMemcpyAsync(g.host_fro + z, mats[z].fro2, sizeof(double), hipMemcpyDeviceToHost, s));
-    TNA_HIP(hipStreamSynchronize(s));
-    for (int z = 0; z < nm; ++z)
-      if (!std::isfinite(g.host_fro[z])) {
+      if (!std::isfinite(g.host_fro[2 * z])) {
         set_error("svd: non-finite entry in input matrix " + std::to_string(z));
         return TNA_ERR_NONFINITE;
       }
+    return TNA_OK;
+  };
+  if (n_tiny < nm) {
+    int fro_b = 1;
+    for (auto &a : mats) fro_b = std::max(fro_b, fro_blocks(a.R, a.C));
+    hipLaunchKernelGGL(load_kernel, dim3(max_tiles_load, 1, nm), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(fro_partial_kernel, dim3(fro_b, 1, nm), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(fro_kernel, dim3(nm), dim3(256), 0, s, d);
+    TNA_LAUNCHED("svd.load");
+  }
+  // with every matrix on a single-workgroup path the norms are read with the sweep counts below
+  if (!defer_fused && nfused < nm) {
+    if (n_tiny > 0) {  // these form their norms in their only launch
+      timer_begin("svd.fused", s);
+      hipLaunchKernelGGL(jacobi_tiny_kernel, dim3(nm), dim3(256), 0, s, d, max_sweeps);
+      timer_end("svd.fused", 0.0, 0.0, s);
+      TNA_LAUNCHED("svd.fused");
+    }
+    TNA_TRY(read_status(false, true, 0));
+    TNA_TRY(check_finite_norms());
   }
   // QR start for the larger matrices
   int qr_rows = 0, qr_cblk = 0;
@@ -2104,8 +2211,6 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
         watch[z] = 1;
         ++nwatch;
       }
-    if (nwatch > 0 && !g.host_fro)
-      TNA_HIP(hipHostMalloc((void **)&g.host_fro, sizeof(double) * 3 * 4096, hipHostMallocDefault));
     // the panel factorisation: one cooperative launch per panel where the runtime admits the
     // grid (all workgroups resident), else one launch per column.  TNA_QR_PANEL=col forces the
     // per-column launches; TNA_QR_PANEL=coop makes a refused cooperative launch an error.
@@ -2142,18 +2247,14 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
         if (watch[z] && k1 < mats[z].R) tail = std::max(tail, mats[z].R - k1);
       if (tail == 0) continue;
       hipLaunchKernelGGL(qr_tail_kernel, dim3(ceil_div(tail, 4), 1, nm), dim3(256), 0, s, d, k1);
-      for (int z = 0; z < nm; ++z)
-        if (watch[z])
-          TNA_HIP(hipMemcpyAsync(g.host_fro + 4096 + 2 * z, mats[z].fro2, 2 * sizeof(double), hipMemcpyDeviceToHost,
-                                 s));
-      TNA_HIP(hipStreamSynchronize(s));
+      TNA_TRY(read_status(false, true, 0));
       bool stopped = false;
       for (int z = 0; z < nm; ++z) {
         if (!watch[z]) continue;
         SvdMat &a = mats[z];
         const double f = std::fmax(0.1 * EPS53 * (double)a.C, a.noise_rel);
-        const double floor2 = f * f * g.host_fro[4096 + 2 * z];
-        if (g.host_fro[4096 + 2 * z + 1] <= floor2) {
+        const double floor2 = f * f * g.host_fro[2 * z];
+        if (g.host_fro[2 * z + 1] <= floor2) {
           a.Ra = k1;
           stopped = true;
         }
@@ -2205,16 +2306,11 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     apply_bytes += 16.0 * ((double)a.Ra * a.C + (double)a.Ra * a.R);
   }
   // one block pair: every sweep inside one workgroup, no host round trip per sweep
-  int nfused = 0, n_two = 0, n_tiny = 0;
-  for (auto &a : mats) {
-    nfused += a.fused != 0;
-    n_two += a.fused == 1;
-    n_tiny += a.fused == 2;
-  }
-  if (nfused > 0) {
+  const bool tiny_done = !defer_fused && nfused < nm;
+  if (n_two > 0 || (n_tiny > 0 && !tiny_done)) {
     timer_begin("svd.fused", s);
-    if (n_two) hipLaunchKernelGGL(jacobi_fused_kernel, dim3(nm), dim3(256), 0, s, d, max_sweeps);
-    if (n_tiny) hipLaunchKernelGGL(jacobi_tiny_kernel, dim3(nm), dim3(256), 0, s, d, max_sweeps);
+    if (n_two) hipLaunchKernelGGL(jacobi_fused_kernel, dim3(nm), dim3(EIG_NT), 0, s, d, max_sweeps);
+    if (n_tiny && !tiny_done) hipLaunchKernelGGL(jacobi_tiny_kernel, dim3(nm), dim3(256), 0, s, d, max_sweeps);
     timer_end("svd.fused", 0.0, 0.0, s);
     TNA_LAUNCHED("svd.fused");
   }
@@ -2226,8 +2322,10 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     active += live[z];
     if (live[z]) max_steps = std::max(max_steps, mats[z].nb - 1);
   }
+  if (active > 0)
+    hipLaunchKernelGGL(status_kernel, dim3(ceil_div(nm, 64)), dim3(64), 0, s, d, nm, (int *)nullptr,
+                       (double *)nullptr, 1);
   for (int sw = 1; sw <= max_sweeps && active > 0; ++sw) {
-    hipLaunchKernelGGL(zero_ctr_kernel, dim3(ceil_div(nm, 64)), dim3(64), 0, s, d, nm);
     for (int step = 0; step < max_steps; ++step) {
       timer_begin("svd.gram", s);
       hipLaunchKernelGGL(gram_kernel, dim3(max_pairs, max_ks, nm), dim3(256), 0, s, d, step);
@@ -2241,9 +2339,7 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
       timer_end("svd.apply", apply_flops, apply_bytes, s);
     }
     TNA_LAUNCHED("svd.sweep");
-    for (int z = 0; z < nm; ++z)
-      if (live[z]) TNA_HIP(hipMemcpyAsync(g.host_ctr + z, mats[z].ctr, sizeof(int), hipMemcpyDeviceToHost, s));
-    TNA_HIP(hipStreamSynchronize(s));
+    TNA_TRY(read_status(true, false, 1));
     static const int dbg = [] {
       const char *e = std::getenv("TNA_DEBUG_SVD");
       return e && e[0] == '1';
@@ -2253,7 +2349,7 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     for (int z = 0; z < nm; ++z) {
       if (!live[z]) continue;
       sweeps[z] = sw;
-      if (g.host_ctr[z] == 0) {
+      if (g.host_ctr[2 * z] == 0) {
         mats[z].active = 0;
         live[z] = 0;
         --active;
@@ -2270,10 +2366,8 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
   // with defer_fused the caller takes the sweep counts and convergence of the single-workgroup
   // paths from spec[7] after its own read of the spectra (no synchronisation here)
   if (nfused > 0 && !defer_fused) {
-    for (int z = 0; z < nm; ++z)
-      if (mats[z].fused)
-        TNA_HIP(hipMemcpyAsync(g.host_ctr + 2 * z, mats[z].ctr, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-    TNA_HIP(hipStreamSynchronize(s));
+    TNA_TRY(read_status(true, nfused == nm, 0));
+    if (nfused == nm) TNA_TRY(check_finite_norms());
     double fl = 0.0, by = 0.0;
     for (int z = 0; z < nm; ++z)
       if (mats[z].fused) {
@@ -2293,28 +2387,34 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     a.active = 1;
   }
   if (reup) TNA_TRY(upload(mats, g, s));
-  hipLaunchKernelGGL(norms_kernel, dim3(max_r4, 1, nm), dim3(256), 0, s, d);
-  hipLaunchKernelGGL(sort_kernel, dim3(nm), dim3(1024), 0, s, d);
-  TNA_LAUNCHED("svd.finish");
+  if (n_tiny < nm) {
+    hipLaunchKernelGGL(norms_kernel, dim3(max_r4, 1, nm), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(sort_kernel, dim3(nm), dim3(1024), 0, s, d);
+    TNA_LAUNCHED("svd.finish");
+  }
   return active > 0 ? TNA_ERR_NOCONV : TNA_OK;
 }
 
 tna_status svd_group_outputs(std::vector<SvdMat> &mats, SvdGroup &g, hipStream_t s) {
   const int nm = (int)mats.size();
   if (nm == 0) return TNA_OK;
-  int max_k = 1;
+  int max_k = 1, n_tiny = 0;
   int64_t max_el = 1;
   for (auto &a : mats) {
+    n_tiny += a.fused == 2;
     max_k = std::max(max_k, a.k);
     max_el = std::max<int64_t>(max_el, std::max<int64_t>((int64_t)a.m * a.k, (int64_t)a.k * a.n));
   }
   TNA_TRY(upload(mats, g, s));
   const SvdMat *d = g.desc.as<SvdMat>();
-  hipLaunchKernelGGL(trunc_kernel, dim3(nm), dim3(256), 0, s, d);
-  hipLaunchKernelGGL(write_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(max_el, 256), 2048), 2, nm), dim3(256),
-                     0, s, d);
-  hipLaunchKernelGGL(complete_kernel, dim3(nm), dim3(256), 0, s, d);
-  hipLaunchKernelGGL(gauge_kernel, dim3(max_k, 1, nm), dim3(256), 0, s, d);
+  if (n_tiny > 0) hipLaunchKernelGGL(finish_small_kernel, dim3(nm), dim3(256), 0, s, d);
+  if (n_tiny < nm) {
+    hipLaunchKernelGGL(trunc_kernel, dim3(nm), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(write_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(max_el, 256), 2048), 2, nm),
+                       dim3(256), 0, s, d);
+    hipLaunchKernelGGL(complete_kernel, dim3(nm), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(gauge_kernel, dim3(max_k, 1, nm), dim3(256), 0, s, d);
+  }
   TNA_LAUNCHED("svd.outputs");
   return TNA_OK;
 }
@@ -2323,13 +2423,15 @@ void SvdGroup::release() {
   desc.release();
   work_d.release();
   work_i.release();
-  if (host) (void)hipHostFree(host);
+  for (Stage &st : stage) {
+    if (st.host) (void)hipHostFree(st.host);
+    if (st.done) (void)hipEventDestroy(st.done);
+    st = Stage{};
+  }
   if (host_ctr) (void)hipHostFree(host_ctr);
   if (host_fro) (void)hipHostFree(host_fro);
-  host = nullptr;
   host_ctr = nullptr;
   host_fro = nullptr;
-  host_cap = 0;
 }
 
 }  // namespace tna
