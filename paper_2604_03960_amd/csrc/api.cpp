@@ -151,13 +151,8 @@ tna_status heff_device(const HeffOp &h, const double *x, double *out, hipStream_
   m.n0 = chl; m.n1 = chr;
   m.is0 = (int64_t)D * d * d * chr; m.is1 = 1;
   m.os0 = (int64_t)d * d * D * chr; m.os1 = 1;
-  m.I = D * d * d; m.J = d * d * D;
-  for (int w = 0; w < D; ++w)
-    for (int sp = 0; sp < d; ++sp)
-      for (int tp = 0; tp < d; ++tp) m.ioff[(w * d + sp) * d + tp] = w * d * d * chr + sp * d * chr + tp * chr;
-  for (int s_ = 0; s_ < d; ++s_)
-    for (int t = 0; t < d; ++t)
-      for (int wq = 0; wq < D; ++wq) m.ooff[(s_ * d + t) * D + wq] = s_ * d * D * chr + t * D * chr + wq * chr;
+  m.I1 = D; m.I2 = d * d; m.J1 = d * d; m.J2 = D;
+  m.ich1 = d * d * chr; m.ich2 = chr; m.och1 = D * chr; m.och2 = chr;
   m.in = h.X; m.type_in = tc; m.out = h.Z; m.type_out = tc; m.M = h.M12;
   TNA_TRY(mix(m, s));
   // S4: out[(a,s,t)][c] = sum_{(w'',c')} Z[(a,s,t)][(w'',c')] R[c][(w'',c')]
@@ -182,11 +177,8 @@ tna_status env_left(int chl, int k, int d, int D, const double *L, const double 
   m.n0 = chl; m.n1 = k;
   m.is0 = (int64_t)D * d * k; m.is1 = 1;
   m.os0 = (int64_t)d * D * k; m.os1 = 1;
-  m.I = D * d; m.J = d * D;
-  for (int w = 0; w < D; ++w)
-    for (int sp = 0; sp < d; ++sp) m.ioff[w * d + sp] = w * d * k + sp * k;
-  for (int s_ = 0; s_ < d; ++s_)
-    for (int wp = 0; wp < D; ++wp) m.ooff[s_ * D + wp] = s_ * D * k + wp * k;
+  m.I1 = D; m.I2 = d; m.J1 = d; m.J2 = D;
+  m.ich1 = d * k; m.ich2 = k; m.och1 = D * k; m.och2 = k;
   m.in = T1; m.type_in = G_F64; m.out = T2; m.type_out = G_F64; m.M = Ml;
   TNA_TRY(mix(m, s));
   g = GemmArgs{};
@@ -208,11 +200,8 @@ tna_status env_right(int k, int chr, int d, int D, const double *R, const double
   m.n0 = chr; m.n1 = k;
   m.is0 = (int64_t)D * k * d; m.is1 = d;
   m.os0 = (int64_t)D * k; m.os1 = 1;
-  m.I = D * d; m.J = d * D;
-  for (int wq = 0; wq < D; ++wq)
-    for (int tp = 0; tp < d; ++tp) m.ioff[wq * d + tp] = wq * k * d + tp;
-  for (int t = 0; t < d; ++t)
-    for (int w = 0; w < D; ++w) m.ooff[t * D + w] = t * chr * D * k + w * k;
+  m.I1 = D; m.I2 = d; m.J1 = d; m.J2 = D;
+  m.ich1 = k * d; m.ich2 = 1; m.och1 = chr * D * k; m.och2 = k;
   m.in = T1; m.type_in = G_F64; m.out = T2; m.type_out = G_F64; m.M = Mr;
   TNA_TRY(mix(m, s));
   g = GemmArgs{};
@@ -654,6 +643,8 @@ tna_status tna_heff_apply(tna_ctx c, int chi_l, int chi_r, int d, int D, const d
   TNA_TRY(heff_check_args(c, chi_l, chi_r, d, D, L, W1, W2, R, theta, out, prec));
   hipStream_t s = c->stream;
   TNA_TRY(bind_scratch(c, heff_scratch(c, chi_l, chi_r, d, D, prec)));
+  if (heff_small_takes(chi_l, chi_r, d, D, L, W1, W2, R, theta, out, prec))
+    return heff_small(chi_l, chi_r, D, L, W1, W2, R, theta, out, prec, s);
   TNA_TRY(build_mix_matrix(0, d, D, W1, W2, c->m12.as<double>(), s));
   HeffOp op{chi_l, chi_r, d, D, L, R, c->m12.as<double>(), c->x.ptr, c->z.ptr, prec};
   if (prec != TNA_HEFF_F64) {

@@ -111,14 +111,14 @@ int gemm_group_tiles(std::vector<GemmProb> &probs, int tile, int *pairs = nullpt
 tna_status gemm_grouped(const GemmGroup &g, const GemmProb *d, int nprob, int total, hipStream_t s);
 
 // ------------------------------------------------------------------ MPO mixing
-// out[o0*os0 + o1*os1 + ooff[j]] = sum_i M[j*I + i] * in[o0*is0 + o1*is1 + ioff[i]]
-// for o0 < n0, o1 < n1.  I, J <= 32.  in/out double or float.
+// out[o0*os0 + o1*os1 + out channel j] = sum_i M[j*I + i] * in[o0*is0 + o1*is1 + in channel i]
+// for o0 < n0, o1 < n1.  I, J <= 32.  in/out double or float.  Channel i = (i1, i2), i2 < I2, sits at
+// i1 * ich1 + i2 * ich2, channel j = (j1, j2) at j1 * och1 + j2 * och2.
 struct MixArgs {
   int n0, n1;
   int64_t is0, is1, os0, os1;
-  int I, J;
-  int ioff[32];
-  int ooff[32];
+  int I1, I2, J1, J2;
+  int ich1, ich2, och1, och2;
   const void *in; int type_in;
   void *out; int type_out;
   const double *M;  // device, J x I
@@ -305,6 +305,15 @@ struct HeffOp {
   int prec;
 };
 tna_status heff_device(const HeffOp &h, const double *x, double *out, hipStream_t s);
+// One-launch form for short bonds (heff.hip): whether it takes a call, and the call.
+// Longest bonds it takes: its time grows with chr (the mixing and the last product run on few waves a
+// workgroup), the general path's four launches cost about the same up to there (D = 5, FP64: 33 against
+// 49 us at chi 80, 40 against 50 at 96; D = 3: 24 against 31 and 30 against 31).
+constexpr int HEFF_SMALL_CHL = 192, HEFF_SMALL_CHR = 80;
+bool heff_small_takes(int chl, int chr, int d, int D, const double *L, const double *W1, const double *W2,
+                      const double *R, const double *theta, const double *out, int prec);
+tna_status heff_small(int chl, int chr, int D, const double *L, const double *W1, const double *W2, const double *R,
+                      const double *theta, double *out, int prec, hipStream_t s);
 tna_status heff_check_args(tna_ctx c, int chi_l, int chi_r, int d, int D, const double *L, const double *W1,
                            const double *W2, const double *R, const double *theta, double *out, int prec);
 // noalloc.cpp: records the calling device's address of the fixed scratch array (device current)

@@ -84,6 +84,8 @@ tna_status tna_heff_apply_noalloc(tna_ctx c, int chi_l, int chi_r, int d, int D,
     set_error("heff_apply_noalloc: no scratch address for this device (context not created on it)");
     return TNA_ERR_DEVICE;
   }
+  if (heff_small_takes(chi_l, chi_r, d, D, L, W1, W2, R, theta, out, prec))
+    return heff_small(chi_l, chi_r, D, L, W1, W2, R, theta, out, prec, c->stream);
   const size_t nx = (size_t)D * d * d * chi_l * chi_r;
   const size_t el = prec == TNA_HEFF_F64 ? sizeof(double) : sizeof(float);
   size_t off = 0;

@@ -37,36 +37,41 @@ int n_parts(int64_t n) {
 
 // ------------------------------------------------------------------ mixing
 struct MixDev {
-  int n0, n1, I, J;
+  int n0, n1, I1, I2, J1, J2, ich1, ich2, och1, och2;
   int64_t is0, is1, os0, os1;
-  int ioff[32];
-  int ooff[32];
   const void *in;
   void *out;
   const double *M;
 };
 
-template <typename TI, typename TO>
+// One thread per (o0, o1).  Every thread of the launch reads M at the same addresses: through the
+// constant address space those are scalar loads shared by the wave.  The channel counts are template
+// constants for the MPOs in use (CI1 = 0: runtime counts, at most 32 channels): with runtime counts the
+// 32 x 32 guarded products and their loads of M took 34 us for the 256 elements of a chi = 16 bond.
+template <typename T, int CI1, int CI2, int CJ1, int CJ2>
 __global__ __launch_bounds__(NT) void mix_kernel(MixDev a) {
+  constexpr bool fixed = CI1 > 0;
+  const int I2 = fixed ? CI2 : a.I2, J2 = fixed ? CJ2 : a.J2;
+  const int I = fixed ? CI1 * CI2 : a.I1 * a.I2, J = fixed ? CJ1 * CJ2 : a.J1 * a.J2;
+  constexpr int IM = fixed ? CI1 * CI2 : 32, JM = fixed ? CJ1 * CJ2 : 32;
   const int64_t idx = (int64_t)blockIdx.x * NT + threadIdx.x;
   const int64_t total = (int64_t)a.n0 * a.n1;
   if (idx >= total) return;
   const int64_t o0 = idx / a.n1, o1 = idx - o0 * a.n1;
-  const TI *in = static_cast<const TI *>(a.in) + o0 * a.is0 + o1 * a.is1;
-  TO *out = static_cast<TO *>(a.out) + o0 * a.os0 + o1 * a.os1;
-  typedef typename std::conditional<sizeof(TI) == 8 || sizeof(TO) == 8, double, float>::type T;
-  T x[32];
+  const T *in = static_cast<const T *>(a.in) + o0 * a.is0 + o1 * a.is1;
+  T *out = static_cast<T *>(a.out) + o0 * a.os0 + o1 * a.os1;
+  const double __attribute__((address_space(4))) *M = (const double __attribute__((address_space(4))) *)a.M;
+  T x[IM];
 #pragma unroll
-  for (int i = 0; i < 32; ++i) x[i] = (i < a.I) ? (T)in[a.ioff[i]] : T(0);
+  for (int i = 0; i < IM; ++i) x[i] = (fixed || i < I) ? in[(i / I2) * a.ich1 + (i % I2) * a.ich2] : T(0);
 #pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    if (j < a.J) {
+  for (int j = 0; j < JM; ++j) {
+    if (fixed || j < J) {
       T acc = T(0);
-      const double *Mj = a.M + j * a.I;
 #pragma unroll
-      for (int i = 0; i < 32; ++i)
-        if (i < a.I) acc += (T)Mj[i] * x[i];
-      out[a.ooff[j]] = (TO)acc;
+      for (int i = 0; i < IM; ++i)
+        if (fixed || i < I) acc += (T)M[j * I + i] * x[i];
+      out[(j / J2) * a.och1 + (j % J2) * a.och2] = acc;
     }
   }
 }
@@ -245,30 +250,40 @@ int grid_for(int64_t n) {
 
 // ---------------------------------------------------------------------- API
 tna_status mix(const MixArgs &a, hipStream_t s) {
-  if (a.I < 1 || a.I > 32 || a.J < 1 || a.J > 32 || a.n0 < 0 || a.n1 < 0) {
+  const int I = a.I1 * a.I2, J = a.J1 * a.J2;
+  if (I < 1 || I > 32 || J < 1 || J > 32 || a.n0 < 0 || a.n1 < 0) {
     set_error("mix: bad channel count");
     return TNA_ERR_ARG;
   }
   int64_t total = (int64_t)a.n0 * a.n1;
   if (total == 0) return TNA_OK;
-  MixDev d;
-  d.n0 = a.n0; d.n1 = a.n1; d.I = a.I; d.J = a.J;
-  d.is0 = a.is0; d.is1 = a.is1; d.os0 = a.os0; d.os1 = a.os1;
-  for (int i = 0; i < 32; ++i) { d.ioff[i] = a.ioff[i]; d.ooff[i] = a.ooff[i]; }
-  d.in = a.in; d.out = a.out; d.M = a.M;
+  const MixDev d{a.n0, a.n1, a.I1, a.I2, a.J1, a.J2, a.ich1, a.ich2, a.och1, a.och2, a.is0, a.is1, a.os0, a.os1,
+                 a.in, a.out, a.M};
   dim3 grid((unsigned)((total + NT - 1) / NT));
   const char *name = a.type_in == G_F64 ? "mix.f64" : "mix.f32";
   timer_begin(name, s);
-  if (a.type_in == G_F64 && a.type_out == G_F64)
-    hipLaunchKernelGGL((mix_kernel<double, double>), grid, dim3(NT), 0, s, d);
-  else if (a.type_in == G_F32 && a.type_out == G_F32)
-    hipLaunchKernelGGL((mix_kernel<float, float>), grid, dim3(NT), 0, s, d);
-  else {
+  if (a.type_in != a.type_out) {
     set_error("mix: type combination not built");
     return TNA_ERR_UNSUPPORTED;
   }
+  auto launch = [&](auto kd, auto kf) {
+    if (a.type_in == G_F64) hipLaunchKernelGGL(kd, grid, dim3(NT), 0, s, d);
+    else hipLaunchKernelGGL(kf, grid, dim3(NT), 0, s, d);
+  };
+#define TNA_MIX_CASE(b, c, e, f)                                                              \
+  if (a.I1 == b && a.I2 == c && a.J1 == e && a.J2 == f)                                     \
+    launch(mix_kernel<double, b, c, e, f>, mix_kernel<float, b, c, e, f>);                  \
+  else
+  TNA_MIX_CASE(5, 4, 4, 5)
+  TNA_MIX_CASE(5, 2, 2, 5)
+  TNA_MIX_CASE(8, 4, 4, 8)
+  TNA_MIX_CASE(8, 2, 2, 8)
+  TNA_MIX_CASE(3, 4, 4, 3)
+  TNA_MIX_CASE(3, 2, 2, 3)
+  launch(mix_kernel<double, 0, 0, 0, 0>, mix_kernel<float, 0, 0, 0, 0>);
+#undef TNA_MIX_CASE
   const int es = a.type_in == G_F64 ? 8 : 4;
-  timer_end(name, 2.0 * a.I * a.J * (double)total, (double)total * (a.I + a.J) * es, s);
+  timer_end(name, 2.0 * I * J * (double)total, (double)total * (I + J) * es, s);
   TNA_LAUNCHED("vec.hip:1");
   return TNA_OK;
 }
