@@ -58,22 +58,36 @@ struct ArenaBlock {
   void *dev = nullptr;
   size_t cap = 0;
 };
+// Pushes only stage their bytes; arena_flush copies what was staged since the last flush in one
+// transfer, before the launch that reads it.
 struct Arena {
   std::vector<ArenaBlock> blocks;
-  size_t cur = 0, off = 0;
+  size_t cur = 0, off = 0, flushed = 0;
 };
 
 void arena_begin(Arena &a) {
   a.cur = 0;
   a.off = 0;
+  a.flushed = 0;
+}
+
+tna_status arena_flush(Arena &a, hipStream_t s) {
+  if (a.cur < a.blocks.size() && a.flushed < a.off) {
+    const ArenaBlock &b = a.blocks[a.cur];
+    TNA_HIP(hipMemcpyAsync(static_cast<char *>(b.dev) + a.flushed, b.host + a.flushed, a.off - a.flushed,
+                           hipMemcpyHostToDevice, s));
+    a.flushed = a.off;
+  }
+  return TNA_OK;
 }
 
 // reserves `bytes` (256-byte aligned) in the current block, or in a new one
-tna_status arena_reserve(Arena &a, size_t bytes, char **host, char **dev) {
+tna_status arena_reserve(Arena &a, size_t bytes, char **host, char **dev, hipStream_t s) {
   const size_t need = (bytes + 255) & ~(size_t)255;
   while (a.cur < a.blocks.size() && a.off + need > a.blocks[a.cur].cap) {
+    TNA_TRY(arena_flush(a, s));
     ++a.cur;
-    a.off = 0;
+    a.off = a.flushed = 0;
   }
   if (a.cur == a.blocks.size()) {
     ArenaBlock b;
@@ -85,7 +99,7 @@ tna_status arena_reserve(Arena &a, size_t bytes, char **host, char **dev) {
       return TNA_ERR_NOMEM;
     }
     a.blocks.push_back(b);
-    a.off = 0;
+    a.off = a.flushed = 0;
   }
   ArenaBlock &b = a.blocks[a.cur];
   *host = b.host + a.off;
@@ -94,14 +108,13 @@ tna_status arena_reserve(Arena &a, size_t bytes, char **host, char **dev) {
   return TNA_OK;
 }
 
-// host values -> the arena's device half (descriptors read by kernels)
+// host values -> the arena's device half (descriptors read by kernels), there after the next flush
 template <class T>
 tna_status arena_push(Arena &a, const T *src, size_t n, hipStream_t s, const T **dev_out) {
   const size_t bytes = sizeof(T) * n;
   char *h = nullptr, *d = nullptr;
-  TNA_TRY(arena_reserve(a, bytes, &h, &d));
+  TNA_TRY(arena_reserve(a, bytes, &h, &d, s));
   if (bytes) std::memcpy(h, src, bytes);
-  if (bytes) TNA_HIP(hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, s));
   *dev_out = reinterpret_cast<const T *>(d);
   return TNA_OK;
 }
@@ -113,7 +126,7 @@ tna_status put_dev(Arena &a, const T *src, size_t n, T *dst, hipStream_t s) {
   if (n == 0) return TNA_OK;
   const size_t bytes = sizeof(T) * n;
   char *h = nullptr, *d = nullptr;
-  TNA_TRY(arena_reserve(a, bytes, &h, &d));
+  TNA_TRY(arena_reserve(a, bytes, &h, &d, s));
   std::memcpy(h, src, bytes);
   TNA_HIP(hipMemcpyAsync(dst, h, bytes, hipMemcpyHostToDevice, s));
   return TNA_OK;
@@ -125,7 +138,7 @@ void arena_release(Arena &a) {
     if (b.host) (void)hipHostFree(b.host);
   }
   a.blocks.clear();
-  a.cur = a.off = 0;
+  a.cur = a.off = a.flushed = 0;
 }
 
 double group_flops(const std::vector<GemmProb> &probs) {
@@ -157,6 +170,7 @@ tna_status tuned_gemm(int kind, GemmGroup g, std::vector<GemmProb> probs, Arena 
       const int total = gemm_group_tiles(pr, cand, &g.pairs);
       const GemmProb *d = nullptr;
       TNA_TRY(arena_push(ar, pr.data(), pr.size(), s, &d));
+      TNA_TRY(arena_flush(ar, s));
       g.tile = cand;
       hipEvent_t a, b;
       TNA_HIP(hipEventCreate(&a));
@@ -183,6 +197,7 @@ tna_status tuned_gemm(int kind, GemmGroup g, std::vector<GemmProb> probs, Arena 
   const int total = gemm_group_tiles(probs, tile, &g.pairs);
   const GemmProb *d = nullptr;
   TNA_TRY(arena_push(ar, probs.data(), probs.size(), s, &d));
+  TNA_TRY(arena_flush(ar, s));
   return gemm_grouped(g, d, (int)probs.size(), total, s);
 }
 
@@ -191,12 +206,13 @@ int parts_for(int64_t n) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(g, 512));
 }
 
-constexpr int SPEC = 32;                    // doubles per spectrum record (the SVD writes 0..24)
+constexpr int SPEC = 32;                    // doubles per spectrum record (the SVD writes 0..26)
+constexpr int IDENT_G = 256;                // most partial maxima per identity channel
 constexpr double IDENT_TOL = 1e-10;         // largest deviation of an identity channel that is used as one
 constexpr int LZ_SMALL_N = 4096;            // longest theta of the single-workgroup Lanczos path
 constexpr int NT_SMALL = 512;               // its workgroup size
-constexpr size_t LZ_SLOT = 128;             // per-chain h1/h2/y/nrm2 slots
-constexpr size_t LZ_PER = 3 * LZ_SLOT + 8;  // doubles per chain before the partials
+constexpr size_t LZ_SLOT = 128;             // per-chain h1/h2/nrm2 slots
+constexpr size_t LZ_PER = 2 * LZ_SLOT + 8;  // doubles per chain before the partials
 constexpr size_t LZ_PART = 128 * 512;       // partial-sum slots per chain and array
 constexpr double LZ_TOL_F32 = 1e-6;         // least Lanczos residual tolerance with the FP32 operator
 
@@ -209,14 +225,16 @@ struct tna_engine_s {
   hipStream_t stream = nullptr;
   int nslot = 0;
   std::vector<DevBuf> V, X, Z, Lf, Rf, T1, T2;
-  DevBuf ints, dbl, lzst, feat_d, y_d, recs;
+  DevBuf ints, dbl, lzst, feat_d, y_d;
   Arena ar;
   SvdGroup svd;
   DevBuf svd_wd, svd_wi, spec, S;
   std::vector<int> hflags;  // j (nslot) then active (nslot) of the last upload
   double *h_dbl = nullptr;
   float *h_feat = nullptr;
-  double *h_rec = nullptr;  // per slot 2 LZ_HMAX: alpha_j, beta_j^2 of the single-workgroup path
+  double *h_rec = nullptr;  // pinned, per slot 2 LZ_HMAX: alpha_j, beta_j^2 of the single-workgroup path, stored
+                            // there by its kernel
+  double *h_ident = nullptr;  // pinned, per slot 2 IDENT_G: identity-channel deviations, stored by their kernel
   int *h_j = nullptr;
   std::vector<int> lz_last;  // per slot: Lanczos iterations of the previous visit (launch sizing)
   long small_launches = 0;
@@ -242,7 +260,7 @@ tna_status engine_create(int nslot, tna_engine *out) {
   e->T1.resize(nslot);
   e->T2.resize(nslot);
   TNA_TRY(e->ints.ensure(sizeof(int) * 2 * nslot));
-  TNA_TRY(e->dbl.ensure(sizeof(double) * 4 * nslot));  // Lanczos records, then identity-channel deviations
+  TNA_TRY(e->dbl.ensure(sizeof(double) * 2 * nslot));  // Lanczos records
   TNA_TRY(e->lzst.ensure(sizeof(double) * (LZ_PER + 2 * LZ_PART) * nslot));
   TNA_TRY(e->spec.ensure(sizeof(double) * SPEC * nslot));
   TNA_TRY(e->feat_d.ensure(sizeof(float) * 32 * nslot));
@@ -251,7 +269,7 @@ tna_status engine_create(int nslot, tna_engine *out) {
   e->lz_last.assign(nslot, 0);
   TNA_HIP(hipHostMalloc((void **)&e->h_dbl, sizeof(double) * (SPEC * nslot + 2 * nslot + 16), hipHostMallocDefault));
   TNA_HIP(hipHostMalloc((void **)&e->h_feat, sizeof(float) * 32 * nslot, hipHostMallocDefault));
-  TNA_TRY(e->recs.ensure(sizeof(double) * 2 * LZ_HMAX * nslot));
+  TNA_HIP(hipHostMalloc((void **)&e->h_ident, sizeof(double) * 2 * IDENT_G * nslot, hipHostMallocDefault));
   TNA_HIP(hipHostMalloc((void **)&e->h_rec, sizeof(double) * 2 * LZ_HMAX * nslot, hipHostMallocDefault));
   TNA_HIP(hipHostMalloc((void **)&e->h_j, sizeof(int) * nslot, hipHostMallocDefault));
   *out = e.release();
@@ -263,7 +281,7 @@ void engine_destroy(tna_engine e) {
   (void)hipStreamSynchronize(e->stream);
   for (auto *vec : {&e->V, &e->X, &e->Z, &e->Lf, &e->Rf, &e->T1, &e->T2})
     for (auto &b : *vec) b.release();
-  for (DevBuf *b : {&e->ints, &e->dbl, &e->lzst, &e->feat_d, &e->y_d, &e->recs, &e->svd_wd, &e->svd_wi, &e->spec,
+  for (DevBuf *b : {&e->ints, &e->dbl, &e->lzst, &e->feat_d, &e->y_d, &e->svd_wd, &e->svd_wi, &e->spec,
                     &e->S})
     b->release();
   arena_release(e->ar);
@@ -271,6 +289,7 @@ void engine_destroy(tna_engine e) {
   if (e->h_dbl) (void)hipHostFree(e->h_dbl);
   if (e->h_feat) (void)hipHostFree(e->h_feat);
   if (e->h_rec) (void)hipHostFree(e->h_rec);
+  if (e->h_ident) (void)hipHostFree(e->h_ident);
   if (e->h_j) (void)hipHostFree(e->h_j);
   if (e->stream) (void)hipStreamDestroy(e->stream);
   delete e;
@@ -376,6 +395,7 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     }
     const CvtProb *dc = nullptr;
     TNA_TRY(arena_push(en->ar, cv.data(), cv.size(), s, &dc));
+    TNA_TRY(arena_flush(en->ar, s));
     TNA_TRY(convert_grouped(dc, (int)cv.size(), s));
   }
   // ---- Lanczos descriptors (slot-indexed j/active flags)
@@ -395,8 +415,8 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     p.active = act_dev + sl;
     p.h1 = base;
     p.h2 = base + LZ_SLOT;
-    p.y = base + 2 * LZ_SLOT;
-    p.nrm2 = base + 3 * LZ_SLOT;
+    p.y = nullptr;
+    p.nrm2 = base + 2 * LZ_SLOT;
     p.part1 = base + LZ_PER;
     p.part2 = base + LZ_PER + LZ_PART;
     p.rec = rec_dev + 2 * sl;
@@ -413,32 +433,61 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
   // a fifth less of both products for D = 5.  Otherwise (a stopped SVD, a hand-made state) the
   // full products run.
   bool ident = true;
+  int ident_g = 1;
   {
-    double *dev = rec_dev + 2 * en->nslot;
-    TNA_HIP(hipMemsetAsync(dev, 0, sizeof(double) * 2 * en->nslot, s));
+    std::vector<IdentProb> ip;
+    int maxc = 1;
     for (int q = 0; q < nc; ++q) {
       const Visit &v = vs[q];
-      const int sl = slot[q];
-      TNA_TRY(ident_deviation(ch[q]->Le[v.b].as<double>(), v.chl, D, D - 1, dev + 2 * sl, s));
-      TNA_TRY(ident_deviation(ch[q]->Re[v.b + 1].as<double>(), v.chr, D, 0, dev + 2 * sl + 1, s));
+      ip.push_back(IdentProb{ch[q]->Le[v.b].as<double>(), v.chl, D - 1});
+      ip.push_back(IdentProb{ch[q]->Re[v.b + 1].as<double>(), v.chr, 0});
+      maxc = std::max(maxc, std::max(v.chl, v.chr));
     }
-    double *hd = en->h_dbl + SPEC * en->nslot;
-    TNA_HIP(hipMemcpyAsync(hd, dev, sizeof(double) * 2 * en->nslot, hipMemcpyDeviceToHost, s));
-    TNA_HIP(hipStreamSynchronize(s));
+    ident_g = (int)std::max<int64_t>(1, std::min<int64_t>(IDENT_G, (int64_t)maxc * maxc / 8192));
+    const IdentProb *di = nullptr;
+    TNA_TRY(arena_push(en->ar, ip.data(), ip.size(), s, &di));
+    TNA_TRY(arena_flush(en->ar, s));
+    TNA_TRY(ident_deviation(di, 2 * nc, ident_g, D, en->h_ident, s));
+  }
+  // the deviations, after a synchronisation: at once where the grouped products need the answer
+  auto read_ident = [&]() {
     en->ident_dev = 0.0;
+    for (int i = 0; i < 2 * nc * ident_g; ++i) {
+      if (!(en->h_ident[i] <= IDENT_TOL)) ident = false;
+      en->ident_dev = std::max(en->ident_dev, en->h_ident[i]);
+    }
+    en->ident_steps += ident ? 1 : 0;
+  };
+  // ---- which visits run whole Lanczos iterations inside one workgroup (short theta, all of
+  // H_eff's operands in LDS); the rest go through the grouped GEMM/mixing/CGS2 launches
+  std::vector<int> small(nc, 0), sm_ac(nc, 1);
+  int nsmall = 0;
+  size_t lds_small = 0;
+  if (d == 2 && D * d * d <= 64) {
     for (int q = 0; q < nc; ++q) {
-      const int sl = slot[q];
-      if (!(hd[2 * sl] <= IDENT_TOL && hd[2 * sl + 1] <= IDENT_TOL)) ident = false;
-      en->ident_dev = std::max(en->ident_dev, std::max(hd[2 * sl], hd[2 * sl + 1]));
+      const Visit &v = vs[q];
+      if (v.nv > LZ_SMALL_N) continue;
+      int ac = std::max(1, std::min(v.chl, NT_SMALL / std::max(1, v.chr)));
+      while (ac > 1 && lz_small_lds(v.chl, v.chr, d, D, ac, f32) > LZ_SMALL_LDS_MAX) ac /= 2;
+      const size_t need = lz_small_lds(v.chl, v.chr, d, D, ac, f32);
+      if (need > LZ_SMALL_LDS_MAX) continue;
+      small[q] = 1;
+      sm_ac[q] = ac;
+      lds_small = std::max(lds_small, need);
+      ++nsmall;
     }
   }
-  en->ident_steps += ident ? 1 : 0;
+  const int nbig = nc - nsmall;
+  if (nbig > 0) {
+    TNA_HIP(hipStreamSynchronize(s));
+    read_ident();
+  }
   std::vector<GemmProb> s1, s4;
   std::vector<int> s1_chain, s4_chain;  // chain of each problem
   std::vector<MixProb> mx;
   int64_t max_mix = 1;
   const size_t el = f32 ? sizeof(float) : sizeof(double);
-  for (int q = 0; q < nc; ++q) {
+  for (int q = 0; q < nc && nbig > 0; ++q) {
     tna_dmrg dm = ch[q];
     const Visit &v = vs[q];
     const int sl = slot[q];
@@ -500,27 +549,8 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
   TNA_TRY(put_dev(en->ar, en->hflags.data(), 2 * (size_t)en->nslot, j_dev, s));
   const LzProb *dlp = nullptr;
   TNA_TRY(arena_push(en->ar, lp.data(), nc, s, &dlp));
+  TNA_TRY(arena_flush(en->ar, s));
   TNA_TRY(lz_start(dlp, nc, maxG, s));
-  // ---- which visits run whole Lanczos iterations inside one workgroup (short theta, all of
-  // H_eff's operands in LDS); the rest go through the grouped GEMM/mixing/CGS2 launches
-  std::vector<int> small(nc, 0), sm_ac(nc, 1);
-  int nsmall = 0;
-  size_t lds_small = 0;
-  if (d == 2 && D * d * d <= 64) {
-    for (int q = 0; q < nc; ++q) {
-      const Visit &v = vs[q];
-      if (v.nv > LZ_SMALL_N) continue;
-      int ac = std::max(1, std::min(v.chl, NT_SMALL / std::max(1, v.chr)));
-      while (ac > 1 && lz_small_lds(v.chl, v.chr, d, D, ac, f32) > LZ_SMALL_LDS_MAX) ac /= 2;
-      const size_t need = lz_small_lds(v.chl, v.chr, d, D, ac, f32);
-      if (need > LZ_SMALL_LDS_MAX) continue;
-      small[q] = 1;
-      sm_ac[q] = ac;
-      lds_small = std::max(lds_small, need);
-      ++nsmall;
-    }
-  }
-  const int nbig = nc - nsmall;
   int tile1 = 64, tile4 = 64;
   const MixProb *dmx = nullptr;
   const GemmProb *dp1 = nullptr, *dp4 = nullptr;
@@ -565,6 +595,7 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     tot4 = gemm_group_tiles(p4, tile4, &g4.pairs);
     TNA_TRY(arena_push(en->ar, p1.data(), n1, s, &dp1));
     TNA_TRY(arena_push(en->ar, p4.data(), n4, s, &dp4));
+    TNA_TRY(arena_flush(en->ar, s));
     // capture one Lanczos iteration (H_eff + CGS2 + record + normalise + advance); with
     // kernel timing on, the iteration is launched directly so that events can bracket
     // single kernels
@@ -678,11 +709,12 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     for (int q = 0; q < nc; ++q) {
       en->hflags[en->nslot + slot[q]] = rs[q];
       lp[q].nkeep = rs[q] ? nkeep[q] : 0;
-      if (rs[q]) TNA_TRY(put_dev(en->ar, yv[q].data(), (size_t)nkeep[q], lp[q].y, s));
+      if (rs[q]) TNA_TRY(arena_push(en->ar, yv[q].data(), (size_t)nkeep[q], s, &lp[q].y));
     }
     TNA_TRY(push_act());
     const LzProb *dr = nullptr;
     TNA_TRY(arena_push(en->ar, lp.data(), nc, s, &dr));
+    TNA_TRY(arena_flush(en->ar, s));
     TNA_TRY(lz_ritz(dr, nc, maxG, s));
     TNA_TRY(lz_start(dr, nc, maxG, s));
     for (int q = 0; q < nc; ++q) {
@@ -701,7 +733,7 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
   if (nsmall > 0) {
     std::vector<LzSmall> sp;
     std::vector<int> sq;  // chain of each descriptor
-    double *rec_small = en->recs.as<double>();
+    double *rec_small = en->h_rec;
     for (int q = 0; q < nc; ++q) {
       if (!small[q]) continue;
       const Visit &v = vs[q];
@@ -715,6 +747,7 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     }
     const LzSmall *dsp = nullptr;
     TNA_TRY(arena_push(en->ar, sp.data(), sp.size(), s, &dsp));
+    TNA_TRY(arena_flush(en->ar, s));
     std::vector<int> start(nc, 0), jdev(nc, 0);
     // algorithmic work of one iteration at index t: H_eff products + CGS2 (two dot and two
     // update passes over V_0..V_t) ; bytes: theta in, V_{t+1} out, the four passes over V
@@ -739,8 +772,6 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
       TNA_TRY(push_act());
       TNA_TRY(lz_small(dsp, (int)sp.size(), D, d * d, chunk, lds_small, f32, s));
       en->small_launches += 1;
-      TNA_HIP(hipMemcpyAsync(en->h_rec, rec_small, sizeof(double) * 2 * LZ_HMAX * en->nslot, hipMemcpyDeviceToHost,
-                             s));
       TNA_HIP(hipStreamSynchronize(s));
       for (int q : sq) en->h_j[slot[q]] = (int)en->h_rec[(size_t)2 * LZ_HMAX * slot[q] + 2 * LZ_HMAX - 1];
       const char *tname = f32 ? "lz.small.f32" : "lz.small";
@@ -840,15 +871,16 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     en->hflags[en->nslot + slot[q]] = 1;
     en->lanczos_iters += iters[q];
     if (!conv[q] && *worst == TNA_OK) *worst = TNA_ERR_NOCONV;
-    TNA_TRY(put_dev(en->ar, yv[q].data(), (size_t)nkeep[q], lp[q].y, s));
+    TNA_TRY(arena_push(en->ar, yv[q].data(), (size_t)nkeep[q], s, &lp[q].y));
   }
   TNA_TRY(push_act());
   {
     const LzProb *dr = nullptr;
     TNA_TRY(arena_push(en->ar, lp.data(), nc, s, &dr));
+    TNA_TRY(arena_flush(en->ar, s));
     TNA_TRY(lz_ritz(dr, nc, maxG, s));
   }
-  TNA_HIP(hipStreamSynchronize(s));  // yv (pageable) copies done
+  if (nbig == 0) read_ident();
   auto t1 = std::chrono::steady_clock::now();
   // ---- SVD of every theta, entropy of the full spectra, needed ranks
   std::vector<SvdMat> mats(nc);
@@ -870,7 +902,6 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
   TNA_TRY(en->svd_wd.ensure(sizeof(double) * nd));
   TNA_TRY(en->svd_wi.ensure(sizeof(int) * ni));
   TNA_TRY(en->S.ensure(sizeof(double) * ns));
-  std::vector<double *> Sq(nc);
   {
     double *dw = en->svd_wd.as<double>(), *sp = en->S.as<double>();
     int *iw = en->svd_wi.as<int>();
@@ -881,7 +912,6 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
       iw += svd_work_ints(a);
       a.A = lp[q].theta;
       a.S = sp;
-      Sq[q] = sp;
       sp += a.R;
       a.spec = en->spec.as<double>() + SPEC * q;
       a.eps_target = ch[q]->opts.eps_target > 0 ? ch[q]->opts.eps_target : 1e-8;
@@ -1024,25 +1054,22 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     GemmGroup nt{0, 1, G_F64, G_F64, G_F64, G_F64, 64, 1.0, 0.0, 0.0, 0.0};
     GemmGroup tn{1, 0, G_F64, G_F64, G_F64, G_F64, 64, 1.0, 0.0, 0.0, 0.0};
     if (!l1.empty()) {
-      TNA_TRY(tuned_gemm(3, nn, l1, en->ar, s, true));
-      const MixProb *dm_ = nullptr;
+      const MixProb *dm_ = nullptr;  // staged before the first product's descriptors: one transfer
       TNA_TRY(arena_push(en->ar, lm.data(), lm.size(), s, &dm_));
+      TNA_TRY(tuned_gemm(3, nn, l1, en->ar, s, true));
       TNA_TRY(mix_grouped(dm_, (int)lm.size(), maxl, D, d, d, D, 0, s));
       TNA_TRY(tuned_gemm(4, tn, l3, en->ar, s, true));
     }
     if (!r1.empty()) {
-      TNA_TRY(tuned_gemm(5, nt, r1, en->ar, s, true));
       const MixProb *dm_ = nullptr;
       TNA_TRY(arena_push(en->ar, rm.data(), rm.size(), s, &dm_));
+      TNA_TRY(tuned_gemm(5, nt, r1, en->ar, s, true));
       TNA_TRY(mix_grouped(dm_, (int)rm.size(), maxr, D, d, d, D, 0, s));
       TNA_TRY(tuned_gemm(6, nn, r3, en->ar, s, true));
     }
   }
   // per-visit records: truncation sums of the outputs pass and the last kept value
   TNA_HIP(hipMemcpyAsync(en->h_dbl, en->spec.ptr, sizeof(double) * SPEC * nc, hipMemcpyDeviceToHost, s));
-  std::vector<double> slast(nc, 0.0);
-  for (int q = 0; q < nc; ++q)
-    TNA_HIP(hipMemcpyAsync(en->h_dbl + SPEC * nc + q, Sq[q] + (kk[q] - 1), sizeof(double), hipMemcpyDeviceToHost, s));
   TNA_HIP(hipStreamSynchronize(s));
   auto t3 = std::chrono::steady_clock::now();
   const double mL = std::chrono::duration<double, std::milli>(t1 - t0).count();
@@ -1063,7 +1090,7 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     r.k = kk[q]; r.chi_ctrl = chi_next[q]; r.lanczos_iters = iters[q]; r.svd_sweeps = sweeps[q];
     r.lanczos_ok = conv[q]; r.E = Ec[q]; r.S = h[1]; r.S_ema = tm[4]; r.eps = h[2]; r.wdisc = h[3];
     r.gap = h[5]; r.P = tm[0]; r.I = tm[1]; r.D = tm[2]; r.u = tm[3]; r.sigma0 = h[8];
-    r.sigma_last = en->h_dbl[SPEC * nc + q];
+    r.sigma_last = h[26];
     r.ms_lanczos = mL; r.ms_svd = mS; r.ms_other = mE;
     r.k_needed = kneed[q]; r.chi_sched = chs[q]; r.fallback = fb[q];
     for (int i = 0; i < 25; ++i) r.feat[i] = en->h_feat[32 * q + i];

@@ -81,17 +81,24 @@ __global__ __launch_bounds__(NT) void mix_grouped_kernel(const MixProb *probs, i
   }
 }
 
-__global__ __launch_bounds__(NT) void ident_dev_kernel(const double *E, int chi, int D, int w, double *out) {
+// grid (G, problems)
+__global__ __launch_bounds__(NT) void ident_dev_kernel(const IdentProb *probs, int D, double *out) {
+  __shared__ double sh[NT / 64];
+  const IdentProb &p = probs[blockIdx.y];
+  const int chi = p.chi;
+  const gptr<const double> E = (gptr<const double>)p.E;
   double m = 0.0;
   const int64_t n = (int64_t)chi * chi;
   for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < n; e += (int64_t)gridDim.x * NT) {
     const int64_t a = e / chi, b = e - a * chi;
-    m = fmax(m, fabs(E[(a * D + w) * chi + b] - (a == b ? 1.0 : 0.0)));
+    m = fmax(m, fabs(E[(a * D + p.w) * chi + b] - (a == b ? 1.0 : 0.0)));
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0)
-    atomicMax(reinterpret_cast<unsigned long long *>(out), (unsigned long long)__double_as_longlong(m));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    out[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
 }
 
 // ------------------------------------------------------------------ Lanczos
@@ -816,10 +823,8 @@ __global__ __launch_bounds__(NT) void convert_grouped_kernel(const CvtProb *prob
 
 }  // namespace
 
-tna_status ident_deviation(const double *E, int chi, int D, int w, double *out, hipStream_t s) {
-  const int64_t n = (int64_t)chi * chi;
-  const unsigned grid = (unsigned)std::min<int64_t>((n + NT - 1) / NT, 1024);
-  hipLaunchKernelGGL(ident_dev_kernel, dim3(grid), dim3(NT), 0, s, E, chi, D, w, out);
+tna_status ident_deviation(const IdentProb *d, int nprob, int G, int D, double *out, hipStream_t s) {
+  hipLaunchKernelGGL(ident_dev_kernel, dim3(G, nprob), dim3(NT), 0, s, d, D, out);
   TNA_LAUNCHED("ident.check");
   return TNA_OK;
 }

@@ -89,7 +89,7 @@ struct tna_circuit_s {
   std::vector<int> chi;               // N-1 bond dimensions
   std::vector<tna_pid_state> st;      // N-1 controllers
   std::vector<DevBuf> B, Bn, lam;     // site tensors, the layer's new ones, Schmidt values per bond
-  DevBuf C, Cp, Th, Uw, S, spec, gates, desc;
+  DevBuf C, Cp, Th, Uw, S, spec, desc;
   DevBuf svd_wd, svd_wi;
   SvdGroup svd;
   char *stage = nullptr;              // pinned upload staging
@@ -144,11 +144,11 @@ tna_status run_group(tna_circuit c, const std::vector<int> &bs, const double *G,
   TNA_TRY(c->Th.ensure(sizeof(double) * off2[ng]));
   TNA_TRY(c->Uw.ensure(sizeof(double) * offu[ng]));
   TNA_TRY(c->spec.ensure(sizeof(double) * SPEC * ng));
-  TNA_TRY(c->gates.ensure(sizeof(double) * 16 * ng));
   TNA_TRY(c->desc.ensure(c->stage_cap));
   double *Cd = c->C.as<double>(), *Cpd = c->Cp.as<double>(), *Thd = c->Th.as<double>();
-  TNA_HIP(hipMemcpyAsync(c->gates.ptr, G, sizeof(double) * 16 * ng, hipMemcpyHostToDevice, s));
   size_t so = 0;
+  const double *gates = nullptr;
+  TNA_TRY(upload(c, c->desc, so, std::vector<double>(G, G + 16 * (size_t)ng), &gates, s));
   // ---- C = B_b B_{b+1}
   {
     std::vector<GemmProb> pr;
@@ -169,7 +169,7 @@ tna_status run_group(tna_circuit c, const std::vector<int> &bs, const double *G,
     int64_t maxe = 1;
     for (int q = 0; q < ng; ++q) {
       const int b = bs[q];
-      gp.push_back(GateProb{cl[q], cr[q], Cd + off2[q], Cpd + off2[q], Thd + off2[q], c->gates.as<double>() + 16 * q,
+      gp.push_back(GateProb{cl[q], cr[q], Cd + off2[q], Cpd + off2[q], Thd + off2[q], gates + 16 * q,
                             b == 0 ? nullptr : c->lam[b - 1].as<double>()});
       maxe = std::max<int64_t>(maxe, (int64_t)cl[q] * cr[q]);
     }
@@ -269,11 +269,8 @@ tna_status run_group(tna_circuit c, const std::vector<int> &bs, const double *G,
                        0, s, df);
     TNA_LAUNCHED("circuit.finish");
   }
-  // ---- records: truncation sums of the outputs pass, the last kept value
+  // ---- records: truncation sums of the outputs pass and the last kept value
   TNA_HIP(hipMemcpyAsync(c->h_spec, c->spec.ptr, sizeof(double) * SPEC * ng, hipMemcpyDeviceToHost, s));
-  std::vector<double> slast(ng);
-  for (int q = 0; q < ng; ++q)
-    TNA_HIP(hipMemcpyAsync(&slast[q], Sq[q] + (k[q] - 1), sizeof(double), hipMemcpyDeviceToHost, s));
   TNA_HIP(hipStreamSynchronize(s));
   for (int q = 0; q < ng; ++q) {
     const int b = bs[q];
@@ -288,7 +285,7 @@ tna_status run_group(tna_circuit c, const std::vector<int> &bs, const double *G,
     r.layer = c->layers; r.bond = b; r.m = m[q]; r.n = n[q]; r.k = k[q]; r.chi_ctrl = chi_next[q];
     r.svd_sweeps = mats[q].fused ? (int)std::fabs(h[7]) : sweeps[q];
     r.S = h[1]; r.S_ema = tm[4]; r.eps = h[2]; r.wdisc = h[3]; r.gap = h[5]; r.sigma0 = h[8];
-    r.sigma_last = slast[q]; r.u = tm[3];
+    r.sigma_last = h[26]; r.u = tm[3];
   }
   c->gates_done += ng;
   return worst;
@@ -329,7 +326,7 @@ tna_status tna_circuit_create(tna_ctx ctx, int N, const tna_pid_params *pid, con
     TNA_TRY(c->lam[b].ensure(sizeof(double)));
     TNA_HIP(hipMemcpyAsync(c->lam[b].ptr, &one, sizeof(double), hipMemcpyHostToDevice, s));
   }
-  c->stage_cap = (size_t)1 << 20;
+  c->stage_cap = (size_t)2 << 20;
   TNA_HIP(hipHostMalloc((void **)&c->stage, c->stage_cap, hipHostMallocDefault));
   TNA_HIP(hipHostMalloc((void **)&c->h_spec, sizeof(double) * SPEC * (N / 2 + 1), hipHostMallocDefault));
   TNA_HIP(hipStreamSynchronize(s));
@@ -395,7 +392,7 @@ void tna_circuit_destroy(tna_circuit c) {
   (void)hipStreamSynchronize(s);
   for (auto *v : {&c->B, &c->Bn, &c->lam})
     for (auto &b : *v) b.release();
-  for (DevBuf *b : {&c->C, &c->Cp, &c->Th, &c->Uw, &c->S, &c->spec, &c->gates, &c->desc, &c->svd_wd, &c->svd_wi})
+  for (DevBuf *b : {&c->C, &c->Cp, &c->Th, &c->Uw, &c->S, &c->spec, &c->desc, &c->svd_wd, &c->svd_wi})
     b->release();
   c->svd.release();
   if (c->stage) (void)hipHostFree(c->stage);

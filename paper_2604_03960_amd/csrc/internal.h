@@ -168,7 +168,7 @@ struct SvdMat {
   double *bw, *jt, *gram, *qt, *sig;           // work
   double *S;                                   // R sorted values (output)
   double *spec;                                // 32 doubles: Z, S_vN, eps, eps^2/Z, |S_k|, gap, k_needed, sweeps,
-                                               // S_0..S_15, [24] values above thr, [25] values above 1e-12 S_0
+                                               // S_0..S_15, [24] values above thr, [25] values above 1e-12 S_0, [26] S_{k-1}
   int *skip, *perm, *ctr;                      // work
   void *U, *Vt;                                // m x k, k x n (out_type)
   double *fro2;                                // work: [0] |A|_F^2, [1] largest squared row norm below a QR stop
@@ -216,7 +216,7 @@ void svd_bind_work(SvdMat *a, double *dw, int *iw);
 tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps, std::vector<int> &sweeps,
                          hipStream_t s,
                          bool defer_fused = false);
-// For each matrix's k: spec[2..5], U and Vt (completion of null vectors,
+// For each matrix's k: spec[2..5] and [26], U and Vt (completion of null vectors,
 // sign gauge, scaling).
 tna_status svd_group_outputs(std::vector<SvdMat> &mats, SvdGroup &g, hipStream_t s);
 
@@ -242,9 +242,13 @@ struct MixProb {
   const int *jout;
   int64_t jout_stride;
 };
-// max |E[a][w][a'] - delta(a, a')| over a, a' < chi into *out as the bit pattern of a non-negative
-// double (*out zeroed beforehand); E is chi x D x chi.  grid-stride.
-tna_status ident_deviation(const double *E, int chi, int D, int w, double *out, hipStream_t s);
+// Partial maxima of |E[a][w][a'] - delta(a, a')| over a, a' < chi (E is chi x D x chi), G per problem,
+// problem-major, stored into out (pinned host memory).
+struct IdentProb {
+  const double *E;
+  int chi, w;
+};
+tna_status ident_deviation(const IdentProb *d, int nprob, int G, int D, double *out, hipStream_t s);
 tna_status mix_grouped(const MixProb *d, int nprob, int64_t max_elems, int I1, int I2, int J1, int J2, int f32,
                        hipStream_t s);
 // One chain's Lanczos state for the current sweep step (device pointers).
@@ -254,7 +258,8 @@ struct LzProb {
   double *V;      // (kmax+1) x n Krylov basis (V_{j+1} doubles as w)
   double *theta;  // start vector in, normalised Ritz vector out
   int *j, *active;
-  double *h1, *h2, *part1, *part2, *nrm2, *rec, *y;  // rec: {alpha_j, beta_j^2}
+  double *h1, *h2, *part1, *part2, *nrm2, *rec;  // rec: {alpha_j, beta_j^2}
+  const double *y;  // Ritz coefficients (nkeep)
 };
 // bytes_hint: algorithmic bytes of one dot (or update) pass, for kernel timing
 tna_status lz_iteration(const LzProb *d, int nch, int maxG, int kmax, double bytes_hint, hipStream_t s);

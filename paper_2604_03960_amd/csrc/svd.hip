@@ -1694,6 +1694,7 @@ __global__ __launch_bounds__(256) void trunc_kernel(const SvdMat *mats) {
     a.spec[3] = tail / Z;
     a.spec[4] = sqrt(head);
     a.spec[5] = (k < R && s[0] > 0.0) ? (s[k - 1] - s[k]) / s[0] : 1.0;
+    a.spec[26] = s[k - 1];
   }
 }
 
@@ -1871,6 +1872,7 @@ __device__ void finish_small(const SvdMat &a, double (*Us)[33], double (*Vs)[65]
       a.spec[3] = tail / a.spec[0];
       a.spec[4] = sqrt(head);
       a.spec[5] = (k < R && s0 > 0.0) ? (sk1 - sk) / s0 : 1.0;
+      a.spec[26] = sk1;
       sc[0] = sqrt(head);
     }
   }
