@@ -212,42 +212,120 @@ tna_status env_right(int k, int chr, int d, int D, const double *R, const double
 }
 
 // ---------------------------------------------------------------- tridiagonal eigenpair
-// Lowest eigenvalue of the symmetric tridiagonal (a, b) by Sturm-count
-// bisection, eigenvector by two steps of inverse iteration (Gaussian
-// elimination with partial pivoting on T - lambda I).
-double tridiag_lowest_host(int n, const double *a, const double *b, double *y) {
+// One sequence of pivots q_i = (a_i - x) - b_{i-1}^2 / q_{i-1} of T - x.  Returns whether T has an
+// eigenvalue below x; while the leading pivots are positive, q and dq receive the last pivot and its
+// derivative (dq = 0 otherwise).  Below the lowest eigenvalue of the leading block the last pivot is
+// decreasing and concave with its root at T's lowest eigenvalue.
+static bool last_pivot(int n, const double *a, const double *b, double x, double &q, double &dq) {
+  q = a[0] - x;
+  dq = -1.0;
+  for (int i = 1; i < n; ++i) {
+    if (!(q > 0.0)) {
+      dq = 0.0;
+      return true;
+    }
+    const double inv = 1.0 / q, f = b[i - 1] * b[i - 1] * inv;
+    dq = f * (dq * inv) - 1.0;
+    q = (a[i] - x) - f;
+  }
+  return q < 0.0;
+}
+
+// Newton steps on the last pivot from x (a Ritz value from a subspace lies right of the root and left
+// of the leading block's eigenvalues, from where they close in monotonically).  True when they
+// settled: x is the lowest eigenvalue to rounding, dq the derivative there.
+static bool newton_lowest(int n, const double *a, const double *b, double scale, double &x, double &dq) {
+  for (int it = 0; it < 8; ++it) {
+    double q = 0.0;
+    (void)last_pivot(n, a, b, x, q, dq);
+    if (!(dq < 0.0) || !std::isfinite(dq) || !std::isfinite(q)) return false;
+    const double step = -q / dq;
+    x += step;
+    if (std::fabs(step) <= 4.0 * std::numeric_limits<double>::epsilon() * scale) return true;
+  }
+  return false;
+}
+
+static double tridiag_scale(int n, const double *a, const double *b) {
+  double m = 0.0;
+  for (int i = 0; i < n; ++i)
+    m = std::max(m, std::fabs(a[i]) + (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i < n - 1 ? std::fabs(b[i]) : 0.0));
+  return m;
+}
+
+// Estimate of the lowest Ritz value theta of the leading n x n block and of its residual b_{n-1} |y_{n-1}|
+// (the derivative of the last pivot at the root is -1 / y_{n-1}^2), from a starting value x0.  False when
+// the Newton steps give none, or a residual below 1e-6 of the matrix norm: the last pivots then cancel
+// to rounding and the derivative loses its digits.
+bool tridiag_estimate(int n, const double *a, const double *b, double x0, double *theta, double *resid) {
+  const double scale = tridiag_scale(n, a, b);
+  double x = x0, dq = 0.0;
+  if (!std::isfinite(x0) || !newton_lowest(n, a, b, scale, x, dq)) return false;
+  const double r = b[n - 1] / std::sqrt(-dq);
+  if (!(r > 1e-6 * scale)) return false;
+  *theta = x;
+  *resid = r;
+  return true;
+}
+
+// Lowest eigenvalue of the symmetric tridiagonal (a, b): the point where T - x gets its first negative pivot,
+// bisected to the last bit; eigenvector by inverse iteration (Gaussian elimination with partial pivoting
+// on T - lambda I).  x0 (any finite value, NaN for none) is where the bracket is looked for: Newton steps
+// from it, then a bracket opened around the result until it holds the flip.  With a good x0 that is about
+// ten pivot sequences, where bisection of the Gershgorin interval takes 60: with 16 chains a step those
+// were most of the Lanczos phase (590 us a step at chi = 8).
+double tridiag_lowest_host(int n, const double *a, const double *b, double *y, double x0) {
   if (n == 1) {
     y[0] = 1.0;
     return a[0];
   }
-  double lo = std::numeric_limits<double>::infinity(), hi = -lo, amax = 0.0;
+  double lo = std::numeric_limits<double>::infinity(), hi = -lo;
   for (int i = 0; i < n; ++i) {
     double r = (i > 0 ? std::fabs(b[i - 1]) : 0.0) + (i < n - 1 ? std::fabs(b[i]) : 0.0);
     lo = std::min(lo, a[i] - r);
     hi = std::max(hi, a[i] + r);
-    amax = std::max(amax, std::fabs(a[i]) + r);
   }
-  const double tiny = std::numeric_limits<double>::min() / std::numeric_limits<double>::epsilon();
-  auto count_below = [&](double x) {
-    int c = 0;
+  const double amax = tridiag_scale(n, a, b);
+  const double tiny = std::numeric_limits<double>::min() / std::numeric_limits<double>::epsilon();  // in the elimination
+  auto below = [&](double x) {  // last_pivot without the derivative
     double q = a[0] - x;
-    if (q < 0) ++c;
     for (int i = 1; i < n; ++i) {
-      if (q == 0.0) q = -tiny;
+      if (!(q > 0.0)) return true;
       q = (a[i] - x) - b[i - 1] * b[i - 1] / q;
-      if (q < 0) ++c;
     }
-    return c;
+    return q < 0.0;
   };
+  if (std::isfinite(x0)) {
+    double x = x0, dq = 0.0;
+    (void)newton_lowest(n, a, b, amax, x, dq);
+    x = std::isfinite(x) ? std::min(std::max(x, lo), hi) : std::min(std::max(x0, lo), hi);
+    // at most 14 openings span the interval from its rounding level up
+    double d = 8.0 * std::numeric_limits<double>::epsilon() * amax;
+    for (int k = 0; k < 16 && x - d > lo; ++k, d *= 32.0) {
+      if (!below(x - d)) {
+        lo = x - d;
+        break;
+      }
+      hi = std::min(hi, x - d);
+    }
+    d = 8.0 * std::numeric_limits<double>::epsilon() * amax;
+    for (int k = 0; k < 16 && x + d < hi; ++k, d *= 32.0) {
+      if (below(x + d)) {
+        hi = x + d;
+        break;
+      }
+      lo = std::max(lo, x + d);
+    }
+  }
   for (int it = 0; it < 200; ++it) {
     const double mid = 0.5 * (lo + hi);
     if (mid <= lo || mid >= hi) break;
-    if (count_below(mid) >= 1) hi = mid;
+    if (below(mid)) hi = mid;
     else lo = mid;
   }
   const double lam = 0.5 * (lo + hi);
   // inverse iteration
-  std::vector<double> dl(n), dd(n), du(n), du2(n), x(n, 1.0);
+  std::vector<double> dl(n), dd(n), du(n), du2(n), x(n, 1.0), rhs(n);
   const double shift = lam - 4.0 * std::numeric_limits<double>::epsilon() * std::max(amax, 1.0);
   for (int rep = 0; rep < 3; ++rep) {
     for (int i = 0; i < n; ++i) {
@@ -255,8 +333,7 @@ double tridiag_lowest_host(int n, const double *a, const double *b, double *y) {
       if (i < n - 1) { du[i] = b[i]; dl[i] = b[i]; }
     }
     // LU with partial pivoting of a tridiagonal matrix (dgtsv-like), solving in place
-    std::vector<double> rhs = x;
-    std::vector<int> swp(n, 0);
+    rhs = x;
     for (int i = 0; i < n; ++i) du2[i] = 0.0;
     for (int i = 0; i < n - 1; ++i) {
       if (std::fabs(dd[i]) >= std::fabs(dl[i])) {

@@ -28,10 +28,6 @@
 
 using namespace tna;
 
-namespace tna {
-double tridiag_lowest_host(int n, const double *a, const double *b, double *y);
-}
-
 namespace {
 
 // ------------------------------------------------------------------ autotuner
@@ -237,6 +233,7 @@ struct tna_engine_s {
   double *h_ident = nullptr;  // pinned, per slot 2 IDENT_G: identity-channel deviations, stored by their kernel
   int *h_j = nullptr;
   std::vector<int> lz_last;  // per slot: Lanczos iterations of the previous visit (launch sizing)
+  std::vector<double> e_last;  // per slot: energy of the previous visit (where the next one is looked for)
   long small_launches = 0;
   long graph_launches = 0, lanczos_iters = 0;
   long heff_f32_iters = 0;  // Lanczos iterations whose H_eff ran on FP32 operands
@@ -267,6 +264,7 @@ tna_status engine_create(int nslot, tna_engine *out) {
   TNA_TRY(e->y_d.ensure(sizeof(float) * 4 * nslot));
   e->hflags.assign(2 * (size_t)nslot, 0);
   e->lz_last.assign(nslot, 0);
+  e->e_last.assign(nslot, std::nan(""));
   TNA_HIP(hipHostMalloc((void **)&e->h_dbl, sizeof(double) * (SPEC * nslot + 2 * nslot + 16), hipHostMallocDefault));
   TNA_HIP(hipHostMalloc((void **)&e->h_feat, sizeof(float) * 32 * nslot, hipHostMallocDefault));
   TNA_HIP(hipHostMalloc((void **)&e->h_ident, sizeof(double) * 2 * IDENT_G * nslot, hipHostMallocDefault));
@@ -622,6 +620,14 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
   std::vector<std::vector<double>> al(nc), be(nc), yv(nc);
   std::vector<int> conv(nc, 0), nkeep(nc, 0), iters(nc, 0), restart(nc, 0), act(nc, 0);
   std::vector<double> Ec(nc, 0.0);
+  // per chain: lowest Ritz value and residual of the last record solved for (the next record's starting value)
+  std::vector<double> ritz(nc, std::nan("")), rres(nc, 0.0);
+  // lowest eigenvalue of the Ritz pair (theta, residual r) and the next basis vector's diagonal a: the
+  // projection on that plane, an upper bound of the next Ritz value
+  auto next_ritz = [](double theta, double r, double a) {
+    const double m = 0.5 * (theta + a), d = 0.5 * (a - theta);
+    return m - std::hypot(d, r);
+  };
   tna_status lst = TNA_OK;
   // returns true when chain q stops (converged, breakdown or kmax)
   auto take = [&](int q, double a, double b2) -> bool {
@@ -630,8 +636,11 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
     iters[q] += 1;
     const int nn = (int)al[q].size();
     yv[q].assign(nn, 0.0);
-    Ec[q] = tridiag_lowest_host(nn, al[q].data(), be[q].data(), yv[q].data());
+    Ec[q] = tridiag_lowest_host(nn, al[q].data(), be[q].data(), yv[q].data(),
+                                nn > 1 ? next_ritz(ritz[q], rres[q], a) : std::nan(""));
     const double resid = std::fabs(be[q][nn - 1] * yv[q][nn - 1]);
+    ritz[q] = Ec[q];
+    rres[q] = resid;
     bool stop = false;
     if (vs[q].fixed > 0) {
       if (nn >= vs[q].kmax || be[q][nn - 1] < 1e-14) stop = conv[q] = 1;
@@ -664,25 +673,44 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
         break;
       }
     }
-    auto solve = [&](int nn) {
+    const double tol = tol_of(ch[q]);
+    double resid = 0.0;
+    auto solve = [&](int nn, double x0) {
       yv[q].assign(nn, 0.0);
-      Ec[q] = tridiag_lowest_host(nn, al[q].data(), be[q].data(), yv[q].data());
-      return std::fabs(be[q][nn - 1] * yv[q][nn - 1]) <= tol_of(ch[q]) * std::max(1.0, std::fabs(Ec[q]));
+      Ec[q] = tridiag_lowest_host(nn, al[q].data(), be[q].data(), yv[q].data(), x0);
+      resid = std::fabs(be[q][nn - 1] * yv[q][nn - 1]);
+      return resid <= tol * std::max(1.0, std::fabs(Ec[q]));
     };
+    // the record before the new ones (the first record is its own Ritz pair); the newest record is
+    // looked for around the chain's last energy
+    double th = ritz[q], rr = rres[q];
+    const double guess = base > 0 ? th : en->e_last[slot[q]];
     int stop_at = 0;
     bool converged = false;
+    const bool met = solve(last, guess);
+    ritz[q] = Ec[q];
+    rres[q] = resid;
     if (fixed) {
-      solve(last);
       if (cheap) stop_at = last, converged = true;
-    } else if (solve(last)) {
+    } else if (met) {
       stop_at = last;
       converged = true;
-      for (int nn = base + 1; nn < last; ++nn)
-        if (solve(nn)) {
+      for (int nn = base + 1; nn < last; ++nn) {
+        const double x0 = nn > 1 ? next_ritz(th, rr, al[q][nn - 1]) : al[q][0];
+        // most records are far from converged: an estimate well above the tolerance settles that without
+        // the eigenvector
+        if (tridiag_estimate(nn, al[q].data(), be[q].data(), x0, &th, &rr) &&
+            rr > std::max(1e3 * tol, 1e-6) * std::max(1.0, std::fabs(th)))
+          continue;
+        const bool ok = solve(nn, x0);
+        th = Ec[q];
+        rr = resid;
+        if (ok) {
           stop_at = nn;
           break;
         }
-      if (stop_at == last) solve(last);  // the earlier trial solves overwrote Ec / yv
+      }
+      if (stop_at == last) solve(last, ritz[q]);  // the earlier trial solves overwrote Ec / yv
     } else if (cheap) {
       stop_at = last;
       converged = be[q][last - 1] < 1e-14;
@@ -722,6 +750,8 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
       restart[q] += 1;
       al[q].clear();
       be[q].clear();
+      ritz[q] = std::nan("");
+      rres[q] = 0.0;
       nkeep[q] = 0;
       act[q] = 1;
       en->hflags[slot[q]] = 0;
@@ -813,7 +843,10 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
         if (act[q] && al[q].empty()) jdev[q] = 0;  // restarted: j reset on the device
       chunk = 4;
     }
-    for (int q : sq) en->lz_last[slot[q]] = iters[q];
+    for (int q : sq) {
+      en->lz_last[slot[q]] = iters[q];
+      en->e_last[slot[q]] = Ec[q];
+    }
   }
   // ---- lockstep grouped path: replay, read every chain's (alpha_j, beta_j^2), decide on the host
   for (int q = 0; q < nc; ++q) act[q] = !small[q];

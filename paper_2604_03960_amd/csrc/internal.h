@@ -298,7 +298,8 @@ void engine_stats(tna_engine e, tna_batch_stats *st);
 tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std::vector<int> &slot,
                        const std::vector<int> &bond, const std::vector<int> &half, std::vector<double> &E_out,
                        std::vector<tna_visit_log *> &logs, tna_status *worst);
-double tridiag_lowest_host(int n, const double *a, const double *b, double *y);
+double tridiag_lowest_host(int n, const double *a, const double *b, double *y, double x0);
+bool tridiag_estimate(int n, const double *a, const double *b, double x0, double *theta, double *resid);
 
 // ------------------------------------------------------------------ stand-alone H_eff (api.cpp)
 struct HeffOp {
