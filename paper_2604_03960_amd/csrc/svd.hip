@@ -675,18 +675,17 @@ __device__ inline void apply_tile(double *X, int ld, int c0, double (*As)[65], d
     }
 }
 
-// grid (pairs, groups of APPLY_TPW column tiles of B then of Jt, matrices).  Each wave
+// grid (pairs, groups of tpw column tiles of B then of Jt, matrices).  Each wave
 // keeps its 16 rows of the pair's rotation Qt as MFMA A-operands in registers (read once);
 // the 64 x 64 tile of X passes through LDS, and the next tile of the group is loaded into
 // registers while the current one is multiplied and written back, so one workgroup keeps
 // a tile's loads in flight at all times.  33 KB of LDS: four workgroups per CU.
-constexpr int APPLY_TPW = 4;
-__global__ __launch_bounds__(256) void apply_kernel(const SvdMat *mats, int step) {
+__global__ __launch_bounds__(256) void apply_kernel(const SvdMat *mats, int step, int tpw) {
   __shared__ double Xs[64][65];  // Xs[k][j] = X[row(k)][c0 + j]
   const SvdMat &a = mats[blockIdx.z];
   const int pair = blockIdx.x;
   const int ntile_b = (a.C + 63) / 64, ntile_j = (a.R + 63) / 64;
-  const int t0 = blockIdx.y * APPLY_TPW;
+  const int t0 = blockIdx.y * tpw;
   if (!a.active || a.fused || step >= a.nb - 1 || pair >= a.nb / 2 || t0 >= ntile_b + ntile_j) return;
   if (a.skip[pair]) return;
   int p, q;
@@ -701,7 +700,7 @@ __global__ __launch_bounds__(256) void apply_kernel(const SvdMat *mats, int step
   double aq[16];
 #pragma unroll
   for (int kk = 0; kk < 16; ++kk) aq[kk] = Qt[4 * kk];
-  const int t1 = t0 + APPLY_TPW < ntile_b + ntile_j ? t0 + APPLY_TPW : ntile_b + ntile_j;
+  const int t1 = t0 + tpw < ntile_b + ntile_j ? t0 + tpw : ntile_b + ntile_j;
   // thread tid loads rows (tid >> 6) + 4u, u < 16, at column tid & 63 of a tile
   const int lrow = tid >> 6, lcol = tid & 63;
   auto tile_of = [&](int tile, double *&X, int &ld, int &c0) {
@@ -1110,8 +1109,7 @@ __global__ void status_kernel(const SvdMat *mats, int nmat, int *hctr, double *h
 // lower the sweep count; cperm / pinv keep the (identity) column order explicit.
 constexpr int QR_MIN_ROWS_DEV = 256;
 // The products of a block reflector with 32 rows (S = V V^T and W = V X) are long in K and short
-// in M: K is cut into QR_SPLIT pieces that run as one batched launch, and the pieces are summed in
-// order afterwards.
+// in M: K is cut into up to QR_SPLIT pieces, and the pieces are summed in order afterwards.
 constexpr int QR_SPLIT = 8;
 
 // grid (column blocks, 1, matrices): the identity column order
@@ -1130,18 +1128,30 @@ __global__ __launch_bounds__(256) void qr_init_kernel(const SvdMat *mats) {
 // physical index first, so half of its columns by weight sit at the end).
 __device__ inline bool qr_sorts_columns(const SvdMat &a) { return a.active && a.precond && a.rows_scaled; }
 
-// grid (column blocks, 1, matrices): squared column norms of B into qws[2048 ..) (free until the QR)
+// grid (32-column blocks, 1, matrices): squared column norms of B into qws[2048 ..) (free until the QR);
+// eight threads a column, each every eighth row (with one thread a column and 256 columns a block, four
+// blocks walked 1024 rows one after the other: 226 us at 1024 x 1024)
 __global__ __launch_bounds__(256) void colnorm_kernel(const SvdMat *mats) {
+  __shared__ double part[8][33];
   const SvdMat &a = mats[blockIdx.z];
   if (!qr_sorts_columns(a)) return;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= a.C) return;
+  const int cl = threadIdx.x & 31, g = threadIdx.x >> 5, c = blockIdx.x * 32 + cl;
   double ss = 0.0;
-  for (int r = 0; r < a.R; ++r) {
-    const double v = a.bw[(int64_t)r * a.C + c];
-    ss += v * v;
+  if (c < a.C) {
+#pragma unroll 8
+    for (int r = g; r < a.R; r += 8) {
+      const double v = a.bw[(int64_t)r * a.C + c];
+      ss = fma(v, v, ss);
+    }
   }
-  a.qws[2048 + c] = ss;
+  part[g][cl] = ss;
+  __syncthreads();
+  if (g == 0 && c < a.C) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t += part[k][cl];
+    a.qws[2048 + c] = t;
+  }
 }
 
 // one block per matrix: cperm <- columns by decreasing norm (bitonic sort of (norm, index))
@@ -1464,36 +1474,265 @@ __global__ __launch_bounds__(256) void qr_panel_coop_kernel(const SvdMat *mats, 
   }
 }
 
-// T of the compact form H_k0 ... H_k0+nb-1 = I - V T V^T (T upper triangular) from
-// S = V^T V and the betas: T_ii = beta_i, T[0:i, i] = -beta_i T[0:i, 0:i] S[0:i, i].
-// One workgroup per matrix; S at qws[0..1024), T at qws[1024..2048), 32 x 32 row-major.
-__global__ __launch_bounds__(64) void qr_tfactor_kernel(const SvdMat *mats, int k0) {
-  const SvdMat &a = mats[blockIdx.x];
-  if (!a.active || !a.precond || k0 >= a.Ra) return;
-  __shared__ double Ss[32][33], Ts[32][33], bs[32];
-  const int nb = a.R - k0 < 32 ? a.R - k0 : 32;
-  const double *S = a.qws;
-  double *T = a.qws + 1024;
-  const double *beta = a.qws + 2048 + 64 * (int64_t)a.C + k0;
-  const int r = threadIdx.x;
-  // S, beta into LDS once; the recurrence runs in LDS and T goes out at the end
-  for (int e = r; e < 1024; e += 64) {
-    Ss[e >> 5][e & 31] = S[e];
-    Ts[e >> 5][e & 31] = 0.0;
+// The same panel factorisation for at most 1024 rows below k0, in one workgroup: no grid barriers, the
+// whole panel in registers.  Wave w holds the rows 64 w + 4 m + lk (m < 16, lk = lane / 16) at the columns
+// lr and lr + 16 (lr = lane % 16); a column's entries reach the other columns of their rows by a
+// DPP row broadcast, the dots with the other columns are summed over lk and the waves through LDS,
+// and the first wave forms the reflector's scalars.  After column k the registers hold R above the diagonal
+// and the reflectors on and below it; both are written out at the end.
+// Bound by its instructions on one compute unit: per column 16 x (broadcast, two products, two updates) a
+// wave and two barriers.  grid (1, 1, matrices), 64 x waves threads.
+constexpr int QP_M = 16, QP_ROWS = 1024;
+template <int N>
+__device__ inline double row_bcast16(double v) {  // lane N of every 16-lane row to the whole row
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + N, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + N, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+template <int NT>
+__global__ __launch_bounds__(NT) void qr_panel_wg_kernel(const SvdMat *mats, int k0) {
+  __shared__ double red[NT / 64][4][33];
+  __shared__ double rowk[32], ws[32];
+  __shared__ double alphas[32], sc_vk;
+  const SvdMat &a = mats[blockIdx.z];
+  if (!a.active || !a.precond || k0 >= a.Ra || k0 >= a.R) return;
+  const int R = a.R, C = a.C, K = R - k0;
+  const int ncol = C - k0 < 32 ? C - k0 : 32, nref = K < 32 ? K : 32;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  double *B = a.bw + (int64_t)k0 * C + k0;
+  double *betas = a.qws + 2048 + 64 * (int64_t)C + k0;
+  if (tid == 0) a.fro2[1] = 0.0;  // trailing-row maximum of this panel (qr_tail_kernel)
+  double val[QP_M][2];
+#pragma unroll
+  for (int m = 0; m < QP_M; ++m) {
+    const int i = 64 * wave + 4 * m + lk;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) val[m][h] = (i < K && lr + 16 * h < ncol) ? B[(int64_t)i * C + lr + 16 * h] : 0.0;
   }
-  if (r < 32) bs[r] = r < nb ? beta[r] : 0.0;
-  __syncthreads();
-  for (int i = 0; i < nb; ++i) {
-    if (r < i) {
-      double acc = 0.0;
-      for (int c = r; c < i; ++c) acc += Ts[r][c] * Ss[c][i];
-      Ts[r][i] = -bs[i] * acc;
-    } else if (r == i) {
-      Ts[i][i] = bs[i];
+  static_for<0, 32>([&](auto kc_c) {
+    constexpr int kc = kc_c, kh = kc / 16, kl = kc % 16, km = kc / 4, kk = kc % 4;
+    if (kc < nref) {  // uniform
+      // x: column kc's entries of this lane's rows, zero above row kc
+      double x[QP_M];
+      double s0 = 0.0, s1 = 0.0;
+      static_for<0, QP_M>([&](auto m) {
+        double v = row_bcast16<kl>(val[m][kh]);
+        if constexpr (m < 8) v = (wave == 0 && 4 * m + lk < kc) ? 0.0 : v;
+        x[m] = v;
+        s0 = fma(v, val[m][0], s0);
+        s1 = fma(v, val[m][1], s1);
+      });
+      red[wave][lk][lr] = s0;
+      red[wave][lk][lr + 16] = s1;
+      if (wave == 0 && lk == kk) {
+        rowk[lr] = val[km][0];
+        rowk[lr + 16] = val[km][1];
+      }
+      __syncthreads();
+      if (wave == 0) {  // lanes: column lane % 32, halves of the partials
+        const int c = lane & 31, half = lane >> 5;
+        double t = 0.0;
+        for (int w = 0; w < nw; ++w) t += red[w][2 * half][c] + red[w][2 * half + 1][c];
+        t += __shfl_xor(t, 32, 64);
+        const double nx = sqrt(__shfl(t, kc, 64)), xn = rowk[kc];
+        const double al = xn >= 0.0 ? -nx : nx;
+        const double be = nx > 0.0 ? 1.0 / (nx * (nx + fabs(xn))) : 0.0;
+        if (lane < 32) ws[c] = c > kc ? be * (t - al * rowk[c]) : 0.0;
+        if (lane == 0) {
+          alphas[kc] = be != 0.0 ? al : xn;
+          sc_vk = xn - al;
+          betas[kc] = be;
+        }
+      }
+      __syncthreads();
+      const double w0 = ws[lr], w1 = ws[lr + 16], vk = sc_vk;
+      static_for<0, QP_M>([&](auto m) {
+        double v = x[m];
+        if constexpr (m == km) v = (wave == 0 && lk == kk) ? vk : v;  // the reflector's own entry of row kc
+        val[m][0] = fma(-w0, v, val[m][0]);
+        val[m][1] = fma(-w1, v, val[m][1]);
+        if constexpr (m == km) val[m][kh] = (wave == 0 && lk == kk && lr == kl) ? vk : val[m][kh];
+      });
     }
-    __syncthreads();
+  });
+  // R on and above the diagonal to B, the reflectors as rows to qv (from column k0 on, which is all
+  // their readers look at)
+  double *qv = a.qv + (int64_t)k0 * R;
+#pragma unroll
+  for (int m = 0; m < QP_M; ++m) {
+    const int i = 64 * wave + 4 * m + lk;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c = lr + 16 * h;
+      if (i < K && c < ncol) {
+        const double v = val[m][h];
+        B[(int64_t)i * C + c] = i < c ? v : i == c ? alphas[c] : 0.0;
+        if (c < nref) qv[(int64_t)c * R + k0 + i] = i < c ? 0.0 : v;
+      }
+    }
   }
-  for (int e = r; e < 1024; e += 64) T[e] = Ts[e >> 5][e & 31];
+}
+
+// ---- the panel's block reflector I - V T V^T applied from the left, X <- X - V^T W2 with V as 32 rows
+// of length K, in three launches over all matrices: W = V X and S = V V^T in pieces of K (qr_wy_kernel),
+// the pieces summed in order and W2 = T^T W by forward substitution (qr_wy_solve_kernel: T^-1 has 1 / beta on
+// its diagonal and S above it, so W2_i = beta_i (W_i - sum_{j<i} S_ji W2_j) and T is never formed),
+// and the update (qr_wy_update_kernel).  X is the trailing columns of B (on_b) or all of Jt.
+// MFMA operands come straight from L2, where V, W2 and a tile of X stay.  Scratch in qws: S pieces at
+// [2048 ..), W2 (32 x N) at [2048 + 32 C ..), W pieces (32 x N each) behind the betas.
+// Measured at 331 x 517: 58 us a panel in seven launches per matrix with T formed column by column,
+// about 15 us in this form.
+struct WyX {
+  double *X;
+  int ld, N, K, nref;
+  const double *V;
+};
+__device__ inline bool wy_operands(const SvdMat &a, int k0, bool on_b, WyX &o) {
+  if (!a.active || !a.precond || k0 >= a.Ra || (on_b && k0 + 32 >= a.C)) return false;
+  o.K = a.R - k0;
+  o.nref = o.K < 32 ? o.K : 32;
+  o.V = a.qv + (int64_t)k0 * a.R + k0;
+  o.X = on_b ? a.bw + (int64_t)k0 * a.C + k0 + 32 : a.jt + (int64_t)k0 * a.R;
+  o.ld = on_b ? a.C : a.R;
+  o.N = on_b ? a.C - k0 - 32 : a.R;
+  return true;
+}
+// grid (64-column tiles of X and, last, the S tile, pieces, matrices), 256 threads: a wave 16 columns
+__global__ __launch_bounds__(256) void qr_wy_kernel(const SvdMat *mats, int k0, int on_b, int kc) {
+  const SvdMat &a = mats[blockIdx.z];
+  WyX o;
+  if (!wy_operands(a, k0, on_b != 0, o)) return;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, wave = threadIdx.x >> 6;
+  const int nt = (o.N + 63) / 64, piece = blockIdx.y;
+  const bool is_s = blockIdx.x == gridDim.x - 1;
+  if (!is_s && (int)blockIdx.x >= nt) return;
+  if (is_s && wave >= 2) return;
+  const int kb = piece * kc, ke = kb + kc < o.K ? kb + kc : o.K;
+  const int c = is_s ? 16 * wave + lr : 64 * blockIdx.x + 16 * wave + lr;
+  const int R = a.R, r0 = lr < o.nref ? lr : 0, r1 = lr + 16 < o.nref ? lr + 16 : 0;  // rows past nref: discarded
+  const int cc = is_s ? (c < o.nref ? c : 0) : (c < o.N ? c : o.N - 1);
+  v4d acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+  constexpr int UN = 8;
+  for (int k = kb; k < ke; k += 4 * UN) {
+    double v0[UN], v1[UN], x[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int kk = k + 4 * u + lk;
+      const bool in = kk < ke;
+      v0[u] = in ? o.V[(int64_t)r0 * R + kk] : 0.0;
+      v1[u] = in ? o.V[(int64_t)r1 * R + kk] : 0.0;
+      x[u] = in ? (is_s ? o.V[(int64_t)cc * R + kk] : o.X[(int64_t)kk * o.ld + cc]) : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      acc0 = mfma16(v0[u], x[u], acc0);
+      acc1 = mfma16(v1[u], x[u], acc1);
+    }
+  }
+  const int N = is_s ? 32 : o.N;
+  double *out = is_s ? a.qws + 2048 + (int64_t)piece * 1024
+                     : a.qws + 2048 + 64 * (int64_t)a.C + 2 * (int64_t)R + (int64_t)piece * 32 * o.N;
+  if (c < N) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      out[(int64_t)(4 * r + lk) * N + c] = acc0[r];
+      out[(int64_t)(16 + 4 * r + lk) * N + c] = acc1[r];
+    }
+  }
+}
+// grid (64-column tiles, 1, matrices), 256 threads
+__global__ __launch_bounds__(256) void qr_wy_solve_kernel(const SvdMat *mats, int k0, int on_b, int kc) {
+  __shared__ double St[32][34];  // St[i][j] = S[j][i]
+  __shared__ double Ws[32][65];
+  const SvdMat &a = mats[blockIdx.z];
+  WyX o;
+  if (!wy_operands(a, k0, on_b != 0, o)) return;
+  const int c0 = 64 * blockIdx.x, tid = threadIdx.x;
+  if (c0 >= o.N) return;
+  const int np = (o.K + kc - 1) / kc;
+  const double *sp = a.qws + 2048, *wp = a.qws + 2048 + 64 * (int64_t)a.C + 2 * (int64_t)a.R;
+  // every piece's loads are in flight before the first sum
+  const int col = tid & 63;
+  const int cn = c0 + col < o.N ? c0 + col : o.N - 1;
+  double sv[QR_SPLIT][4], wv[QR_SPLIT][8];
+#pragma unroll
+  for (int p = 0; p < QR_SPLIT; ++p) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sv[p][u] = p < np ? sp[p * 1024 + tid + 256 * u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) wv[p][u] = p < np ? wp[((int64_t)p * 32 + (tid >> 6) + 4 * u) * o.N + cn] : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int e = tid + 256 * u;
+    double v = 0.0;
+#pragma unroll
+    for (int p = 0; p < QR_SPLIT; ++p) v += sv[p][u];
+    St[e & 31][e >> 5] = v;
+  }
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    double v = 0.0;
+#pragma unroll
+    for (int p = 0; p < QR_SPLIT; ++p) v += wv[p][u];
+    Ws[(tid >> 6) + 4 * u][col] = v;
+  }
+  __syncthreads();
+  if (tid >= 64) return;
+  const double *betas = a.qws + 2048 + 64 * (int64_t)a.C + k0;
+  double *W2 = a.qws + 2048 + 32 * (int64_t)a.C;
+  double w[32], be[32];
+  static_for<0, 32>([&](auto i) { be[i] = i < o.nref ? betas[i] : 0.0; });
+  static_for<0, 32>([&](auto i) {
+    double v = Ws[i][tid];
+    static_for<0, i>([&](auto j) { v = fma(-St[i][j], w[j], v); });
+    w[i] = be[i] * v;
+    if (c0 + tid < o.N) W2[(int64_t)i * o.N + c0 + tid] = w[i];
+  });
+}
+// grid (64-column tiles, 64-row tiles, matrices), 256 threads: a wave 16 rows
+__global__ __launch_bounds__(256) void qr_wy_update_kernel(const SvdMat *mats, int k0, int on_b) {
+  const SvdMat &a = mats[blockIdx.z];
+  WyX o;
+  if (!wy_operands(a, k0, on_b != 0, o)) return;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, wave = threadIdx.x >> 6;
+  const int c0 = 64 * blockIdx.x, i0 = 64 * blockIdx.y + 16 * wave;
+  if (c0 >= o.N || i0 >= o.K) return;
+  const double *W2 = a.qws + 2048 + 32 * (int64_t)a.C;
+  const int i = i0 + lr < o.K ? i0 + lr : o.K - 1;
+  double av[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int r = 4 * u + lk;
+    av[u] = r < o.nref ? o.V[(int64_t)r * a.R + i] : 0.0;
+  }
+  double bv[4][8];
+  v4d acc[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int c = c0 + 16 * t + lr, cn = c < o.N ? c : o.N - 1;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) bv[t][u] = W2[(int64_t)(4 * u + lk) * o.N + cn];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = i0 + 4 * r + lk;
+      acc[t][r] = (row < o.K && c < o.N) ? -o.X[(int64_t)row * o.ld + c] : 0.0;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc[t] = mfma16(av[u], bv[t][u], acc[t]);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int c = c0 + 16 * t + lr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = i0 + 4 * r + lk;
+      if (row < o.K && c < o.N) o.X[(int64_t)row * o.ld + c] = -acc[t][r];
+    }
+  }
 }
 
 // grid (ceil((R - k1) / 4), 1, matrices): fro2[1] <- the largest squared norm of the rows k1.. of B
@@ -1511,17 +1750,6 @@ __global__ __launch_bounds__(256) void qr_tail_kernel(const SvdMat *mats, int k1
   ss = wave_sum_d(ss);
   if (lane == 0)
     atomicMax(reinterpret_cast<unsigned long long *>(a.fro2 + 1), (unsigned long long)__double_as_longlong(ss));
-}
-
-// out[r * ldo + c] = sum over p < np of part[p * M N + r N + c] (split order), r < M, c < N; grid-stride
-__global__ __launch_bounds__(256) void splitk_sum_kernel(const double *part, int np, int M, int N, double *out,
-                                                         int ldo) {
-  const int64_t n = (int64_t)M * N;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-    double v = 0.0;
-    for (int p = 0; p < np; ++p) v += part[(int64_t)p * n + e];
-    out[(e / N) * ldo + e % N] = v;
-  }
 }
 
 // grid (column blocks, 1, matrices)
@@ -2021,8 +2249,8 @@ void svd_bind_work(SvdMat *a, double *dw, int *iw) {
   if (a->precond) {
     a->qv = dw;
     dw += (size_t)a->R * a->R;
-    a->qws = dw;  // S (32 x 32), T (32 x 32), W and W2 (32 x C each), betas (R), spare (R), then the
-                  // split-K partial products (QR_SPLIT x 32 x C)
+    a->qws = dw;  // [2048 ..) S pieces (QR_SPLIT x 32 x 32, at most 32 C), W2 (32 x C); betas (R), scalars of
+                  // the per-column panels (R), then the pieces of W (QR_SPLIT x 32 x C)
     a->cperm = iw;
     iw += a->C;
     a->pinv = iw;
@@ -2054,60 +2282,26 @@ static tna_status upload(const std::vector<SvdMat> &mats, SvdGroup &g, hipStream
   return TNA_OK;
 }
 
-// C (M x N, row stride ldc) = A B over K cut into up to QR_SPLIT pieces: A is M x K (rows, lda; transA 0),
-// B is K x N (transB 0: rows of ldb) or N x K (transB 1); pieces go to `part` (one M x N block
-// each), then are summed into C in piece order.
-static tna_status splitk_gemm(int M, int N, int K, const double *A, int lda, const double *B, int ldb, int transB,
-                              double *C, int ldc, double *part, hipStream_t s) {
-  const int kc = std::max(32, ceil_div(ceil_div(K, QR_SPLIT), 16) * 16);
-  const int full = K / kc, rem = K - full * kc;
-  const int64_t mn = (int64_t)M * N;
-  if (full > 0)
-    TNA_TRY(gemm(GemmArgs{M, N, kc, A, lda, 0, G_F64, B, ldb, transB, G_F64, part, N, G_F64, 1.0, 0.0, full, kc,
-                          transB ? (int64_t)kc : (int64_t)kc * ldb, mn, G_F64, 0}, s));
-  if (rem > 0)
-    TNA_TRY(gemm(GemmArgs{M, N, rem, A + (int64_t)full * kc, lda, 0, G_F64,
-                          B + (transB ? (int64_t)full * kc : (int64_t)full * kc * ldb), ldb, transB, G_F64,
-                          part + (int64_t)full * mn, N, G_F64, 1.0, 0.0, 1, 0, 0, 0, G_F64, 0}, s));
-  const int np = full + (rem > 0 ? 1 : 0);
-  hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(mn, 256), 1024)), dim3(256), 0, s,
-                     part, np, M, N, C, ldc);
-  TNA_LAUNCHED("svd.splitk");
-  return TNA_OK;
-}
-
-// X[k0:, :] <- (I - V T^T V^T) X[k0:, :] for the 32 reflectors k0.. of every QR-started
-// matrix, X the trailing columns of B (on_b) or all of Jt; V as rows in qv, T from
-// S = V^T V by qr_tfactor_kernel; scratch in qws.
+// X[k0:, :] <- (I - V T^T V^T) X[k0:, :] for the 32 reflectors k0.. of every QR-started matrix, X the
+// trailing columns of B (on_b) or all of Jt.  K is cut into at most QR_SPLIT pieces, as many as bring
+// the first launch to about two workgroups per compute unit.
 static tna_status qr_block_apply(const std::vector<SvdMat> &mats, const SvdMat *d, int nm, int k0, bool on_b,
                                  hipStream_t s) {
-  bool any = false;
+  int maxk = 0, maxn = 0;
   for (auto &a : mats) {
-    if (!a.precond || k0 >= a.Ra) continue;
-    if (on_b && k0 + 32 >= a.C) continue;
-    any = true;
-    const int R = a.R, nbk = std::min(32, R - k0), K = R - k0;
-    const double *Vb = a.qv + (int64_t)k0 * R + k0;
-    double *part = a.qws + 2048 + 64 * (int64_t)a.C + 2 * (int64_t)R;
-    TNA_TRY(splitk_gemm(nbk, nbk, K, Vb, R, Vb, R, 1, a.qws, 32, part, s));  // S = V V^T, row stride 32
+    if (!a.precond || k0 >= a.Ra || (on_b && k0 + 32 >= a.C)) continue;
+    maxk = std::max(maxk, a.R - k0);
+    maxn = std::max(maxn, on_b ? a.C - k0 - 32 : a.R);
   }
-  if (!any) return TNA_OK;
-  hipLaunchKernelGGL(qr_tfactor_kernel, dim3(nm), dim3(64), 0, s, d, k0);
-  TNA_LAUNCHED("svd.qr_tfactor");
-  for (auto &a : mats) {
-    if (!a.precond || k0 >= a.Ra) continue;
-    if (on_b && k0 + 32 >= a.C) continue;
-    const int R = a.R, nbk = std::min(32, R - k0), K = R - k0;
-    const double *Vb = a.qv + (int64_t)k0 * R + k0;
-    double *T = a.qws + 1024, *W = a.qws + 2048, *W2 = a.qws + 2048 + 32 * (int64_t)a.C;
-    double *X = on_b ? a.bw + (int64_t)k0 * a.C + k0 + 32 : a.jt + (int64_t)k0 * R;
-    const int ldx = on_b ? a.C : R, N = on_b ? a.C - k0 - 32 : R;
-    TNA_TRY(splitk_gemm(nbk, N, K, Vb, R, X, ldx, 0, W, N, a.qws + 2048 + 64 * (int64_t)a.C + 2 * (int64_t)R, s));
-    TNA_TRY(gemm(GemmArgs{nbk, N, nbk, T, 32, 1, G_F64, W, N, 0, G_F64, W2, N, G_F64, 1.0, 0.0, 1, 0, 0, 0, G_F64, 0},
-                 s));
-    TNA_TRY(gemm(GemmArgs{K, N, nbk, Vb, R, 1, G_F64, W2, N, 0, G_F64, X, ldx, G_F64, -1.0, 1.0, 1, 0, 0, 0, G_F64,
-                          0}, s));
-  }
+  if (maxk == 0) return TNA_OK;
+  const int nt = ceil_div(maxn, 64);
+  int np = std::min(QR_SPLIT, std::max(1, ceil_div(512, (int64_t)nt * nm)));
+  np = std::min(np, ceil_div(maxk, 64));
+  const int kc = ceil_div(ceil_div(maxk, np), 32) * 32;
+  hipLaunchKernelGGL(qr_wy_kernel, dim3(nt + 1, ceil_div(maxk, kc), nm), dim3(256), 0, s, d, k0, on_b ? 1 : 0, kc);
+  hipLaunchKernelGGL(qr_wy_solve_kernel, dim3(nt, 1, nm), dim3(256), 0, s, d, k0, on_b ? 1 : 0, kc);
+  hipLaunchKernelGGL(qr_wy_update_kernel, dim3(nt, ceil_div(maxk, 64), nm), dim3(256), 0, s, d, k0, on_b ? 1 : 0);
+  TNA_LAUNCHED("svd.qr_apply");
   return TNA_OK;
 }
 
@@ -2192,7 +2386,7 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
         ptiles = std::max(ptiles, ceil_div(a.R, 32) * ceil_div(a.C, 32));
       }
     if (sorted > 0) {
-      hipLaunchKernelGGL(colnorm_kernel, dim3(qr_cblk, 1, nm), dim3(256), 0, s, d);
+      hipLaunchKernelGGL(colnorm_kernel, dim3(8 * qr_cblk, 1, nm), dim3(256), 0, s, d);
       hipLaunchKernelGGL(colsort_kernel, dim3(nm), dim3(1024), 0, s, d);
       hipLaunchKernelGGL(permute_load_kernel, dim3(ptiles, 1, nm), dim3(256), 0, s, d);
       TNA_LAUNCHED("svd.qr_order");
@@ -2213,9 +2407,10 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
         watch[z] = 1;
         ++nwatch;
       }
-    // the panel factorisation: one cooperative launch per panel where the runtime admits the
-    // grid (all workgroups resident), else one launch per column.  TNA_QR_PANEL=col forces the
-    // per-column launches; TNA_QR_PANEL=coop makes a refused cooperative launch an error.
+    // the panel factorisation: one workgroup per matrix for at most 1024 rows; above, one cooperative
+    // launch per panel where the runtime admits the grid (all workgroups resident), else one launch
+    // per column.  TNA_QR_PANEL=col forces the per-column launches and TNA_QR_PANEL=coop the cooperative
+    // ones, whose refusal is then an error.
     const char *qp = std::getenv("TNA_QR_PANEL");
     const bool force_coop = qp && std::strcmp(qp, "coop") == 0;
     bool coop = !(qp && std::strcmp(qp, "col") == 0);
@@ -2223,7 +2418,12 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     for (int k0 = 0; k0 < qr_rows; k0 += 32) {
       const int chunks = ceil_div(qr_rows - k0, QC_ROWS);
       bool panel_done = false;
-      if (coop) {
+      if (!qp && qr_rows - k0 <= QP_ROWS) {
+        const int nw = ceil_div(qr_rows - k0, 64);
+        if (nw <= 8) hipLaunchKernelGGL(qr_panel_wg_kernel<512>, dim3(1, 1, nm), dim3(64 * nw), 0, s, d, k0);
+        else hipLaunchKernelGGL(qr_panel_wg_kernel<1024>, dim3(1, 1, nm), dim3(64 * nw), 0, s, d, k0);
+        panel_done = true;
+      } else if (coop) {
         int kk0 = k0;
         void *args[] = {(void *)&d, (void *)&kk0};
         const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(qr_panel_coop_kernel),
@@ -2278,21 +2478,33 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     for (int k0 = 0; k0 < qr_rows; k0 += 32) TNA_TRY(qr_block_apply(mats, d, nm, k0, false, s));
     timer_end("svd.qr_form", 0.0, 0.0, s);
     TNA_LAUNCHED("svd.qr");
-    // the sweeps of a stopped matrix pair blocks of its Ra rows; the Gram partial sums keep
-    // within the slots planned for all R rows
+    // The sweeps of a stopped matrix pair blocks of its Ra rows.  A group too small for the chip (under one
+    // Gram workgroup per compute unit with 256 columns each) cuts its Grams finer, down to 64 columns
+    // (six pairs of 331 x 517: 10.8 us a launch in three pieces, 6.3 in six); the pieces then go where
+    // the QR start's blocked products were, if that holds more of them than the area planned for them.
     bool replan = false;
     for (auto &a : mats) {
-      if (!a.precond || a.Ra >= a.R) continue;
-      const int slots = (a.nb / 2) * a.ksplit;
-      int nb = ceil_div(a.Ra, BS);
-      if (nb < 2) nb = 2;
-      if (nb & 1) ++nb;
-      a.nb = nb;
-      int ks = ceil_div(1024, (int64_t)(nb / 2) * nm);
-      ks = std::min(ks, ceil_div(a.C, 256));
-      ks = std::min(ks, slots / (nb / 2));
-      a.ksplit = std::max(ks, 1);
-      replan = true;
+      if (!a.precond) continue;
+      const int nb0 = a.nb, ks0 = a.ksplit;
+      int slots = (a.nb / 2) * a.ksplit;
+      if (a.Ra < a.R) {
+        a.nb = std::max(2, ceil_div(a.Ra, BS));
+        a.nb += a.nb & 1;
+      }
+      const int pairs = a.nb / 2;
+      const size_t wy = 2048 + 64 * (size_t)a.C + 2 * (size_t)a.R + QR_SPLIT * 32 * (size_t)a.C;
+      int ks = std::min(ceil_div(1024, (int64_t)pairs * nm), ceil_div(a.C, 256));
+      if ((int64_t)pairs * nm * ks < 256) {
+        ks = std::min(ceil_div(256, (int64_t)pairs * nm), ceil_div(a.C, 64));
+        if (ks * pairs > slots && (int)(wy / 4096) > slots) {
+          slots = (int)(wy / 4096);
+          a.gram = a.qws;
+        }
+      }
+      ks = std::max(std::min(ks, slots / pairs), 1);
+      const int chunk = ceil_div(ceil_div(a.C, ks), GBK) * GBK;  // as the kernel cuts it
+      a.ksplit = ceil_div(a.C, chunk);
+      replan = replan || a.nb != nb0 || a.ksplit != ks0;
     }
     if (replan) TNA_TRY(upload(mats, g, s));
   }
@@ -2316,6 +2528,11 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     timer_end("svd.fused", 0.0, 0.0, s);
     TNA_LAUNCHED("svd.fused");
   }
+  // column tiles per workgroup of the apply: four keep a tile's loads in flight behind another's products,
+  // where that still leaves two workgroups per compute unit; one spreads a small group (331 x 517, six
+  // pairs: 17.5 us a launch with four, 8.2 with one; 16 x 512 x 512: 33 against 39)
+  int tpw = 4;
+  while (tpw > 1 && (int64_t)max_pairs * nm * ceil_div(max_tiles, tpw) < 512) tpw /= 2;
   std::vector<int> live(nm);
   int active = 0;
   max_steps = 0;
@@ -2336,8 +2553,7 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
       hipLaunchKernelGGL(eigen_kernel, dim3(max_pairs, nm), dim3(EIG_NT), 0, s, d, step);
       timer_end("svd.eigen", 0.0, 0.0, s);
       timer_begin("svd.apply", s);
-      hipLaunchKernelGGL(apply_kernel, dim3(max_pairs, ceil_div(max_tiles, APPLY_TPW), nm), dim3(256), 0, s, d,
-                         step);
+      hipLaunchKernelGGL(apply_kernel, dim3(max_pairs, ceil_div(max_tiles, tpw), nm), dim3(256), 0, s, d, step, tpw);
       timer_end("svd.apply", apply_flops, apply_bytes, s);
     }
     TNA_LAUNCHED("svd.sweep");

@@ -36,3 +36,24 @@ def test_svd_path_edges(m, n, ratio):
     assert np.abs((U * S) @ Vt - A).max() <= tol * So[0]
     assert np.abs(U.T @ U - np.eye(k)).max() <= tol
     assert np.abs(Vt @ Vt.T - np.eye(k)).max() <= tol
+
+
+@pytest.mark.parametrize("m,n", [(256, 256), (513, 511), (544, 520), (1023, 1030), (1060, 1057)])
+def test_svd_qr_start_edges(m, n):
+    """The QR start's panel forms (one workgroup of up to 8 or 16 waves, more than 1024 rows) and the last
+    columns of its blocked products, alone and as a batch with the same numbers; tolerances as above."""
+    As = np.stack([synth.random_matrix(m, n, 900 + m + 7 * i) for i in range(2)])
+    k = min(m, n) // 2
+    c = ctx()
+    S, U, Vt, spec, sw, st = c.svd_truncate_batched(to_dev(As), k)
+    assert st == 0
+    tol = 64 * max(m, n) * EPS
+    for i in range(2):
+        s, u, v = S[i].cpu().numpy(), U[i].cpu().numpy(), Vt[i].cpu().numpy()
+        ref = np.linalg.svd(As[i], compute_uv=False)
+        assert np.abs(s - ref).max() <= tol * ref[0]
+        assert np.abs(u.T @ u - np.eye(k)).max() <= tol
+        assert np.abs(v @ v.T - np.eye(k)).max() <= tol
+        assert np.abs(u.T @ As[i] - s[:k, None] * v).max() <= tol * ref[0]
+        s1 = c.svd_truncate(to_dev(As[i]), k)[0].cpu().numpy()
+        assert np.abs(s1 - s).max() <= tol * ref[0]
