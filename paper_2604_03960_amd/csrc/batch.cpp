@@ -31,7 +31,7 @@ using namespace tna;
 namespace {
 
 // ------------------------------------------------------------------ autotuner
-// Picks the GEMM tile (64 or 128) per (operation, log2 flops) bucket by
+// Picks the GEMM tile (32, 64 or 128) per (operation, log2 flops) bucket by
 // timing both candidates on the live operands the first time a bucket is met.
 struct Autotune {
   std::map<std::pair<int, int>, int> table;
@@ -161,7 +161,7 @@ tna_status tuned_gemm(int kind, GemmGroup g, std::vector<GemmProb> probs, Arena 
   if (it != g_tune.table.end()) tile = it->second;
   else if (measure) {
     float best = 1e30f;
-    for (int cand : {64, 128}) {
+    for (int cand : {32, 64, 128}) {
       std::vector<GemmProb> pr = probs;
       const int total = gemm_group_tiles(pr, cand, &g.pairs);
       const GemmProb *d = nullptr;
@@ -1248,7 +1248,7 @@ tna_status tna_autotune_load(const char *path) {
   }
   int a, b, t;
   while (std::fscanf(f, "%d %d %d", &a, &b, &t) == 3)
-    if (t == 64 || t == 128) g_tune.table[std::make_pair(a, b)] = t;
+    if (t == 32 || t == 64 || t == 128) g_tune.table[std::make_pair(a, b)] = t;
   std::fclose(f);
   return TNA_OK;
 }

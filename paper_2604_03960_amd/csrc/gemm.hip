@@ -48,19 +48,33 @@ struct GemmDev {
   int64_t sA, sB, sC;
 };
 
-constexpr int BK = 16;
-
-template <typename T, int BM, int BN> struct TileLds {
-  T As[2][BK][BM + 1];
-  T Bs[2][BK][BN + 1];
-};
+// f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>): register arrays indexed by constants
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
 
 // threads of the workgroup that owns a BM x BN tile, and its waves along M
 template <int BM> struct TileShape;
 // (MINW: waves per SIMD the register allocation must leave room for; two 128 x 128
-// workgroups per compute unit need four)
-template <> struct TileShape<64> { static constexpr int NT = 256, WR = 2, MINW = 4; };
-template <> struct TileShape<128> { static constexpr int NT = 512, WR = 4, MINW = 4; };
+// workgroups per compute unit need four.  BK: depth of a slab of operands in LDS.  PD: slabs on their
+// way in registers.  The 32 x 32 and 64 x 64 tiles serve products with few tiles, often one workgroup
+// per compute unit, whose one wave per SIMD has nothing else to hide a slab's load latency (about 2000
+// cycles against the 512 of its products) behind: they keep four slabs in flight.  H_eff of
+// 512 x 512 with 5 MPO channels in FP32, one slab and then four: 246 -> 181 us.  A slab of the
+// 32 x 32 tile is 32 deep, as a 16 deep one leaves its waves two products between barriers (203 x 331, 32
+// channels: 152 us with 16 deep and eight in flight, 126 us with 32 deep and four).)
+template <> struct TileShape<32> { static constexpr int NT = 256, WR = 2, MINW = 4, PD = 4, BK = 32; };
+template <> struct TileShape<64> { static constexpr int NT = 256, WR = 2, MINW = 2, PD = 4, BK = 16; };
+template <> struct TileShape<128> { static constexpr int NT = 512, WR = 4, MINW = 4, PD = 1, BK = 16; };
+
+template <typename T, int BM, int BN> struct TileLds {
+  T As[2][TileShape<BM>::BK][BM + 1];
+  T Bs[2][TileShape<BM>::BK][BN + 1];
+};
 
 // Device-memory pointers in the global address space: operand pointers read from a descriptor in
 // memory are generic to the compiler, whose flat accesses count against the LDS waits as well and so
@@ -72,7 +86,7 @@ template <typename T, typename TA, typename TB, typename TC, int BM, int BN, boo
 __device__ __forceinline__ void gemm_tile(gp<const TA> __restrict__ A, int lda, gp<const TB> __restrict__ B, int ldb,
                                           gp<TC> __restrict__ C, int ldc, int M, int N, int K, double alpha,
                                           double beta, int m0, int n0, TileLds<T, BM, BN> &L) {
-  constexpr int NT = TileShape<BM>::NT, WR = TileShape<BM>::WR, WC = NT / 64 / WR;
+  constexpr int NT = TileShape<BM>::NT, WR = TileShape<BM>::WR, WC = NT / 64 / WR, BK = TileShape<BM>::BK;
   constexpr int WM = BM / WR, WN = BN / WC;
   constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int LA = BM * BK / NT;  // A elements per thread per slab
@@ -200,16 +214,8 @@ __device__ __forceinline__ void gemm_tile(gp<const TA> __restrict__ A, int lda, 
     for (int b = 0; b < TN; ++b) acc[a][b] = typename Acc<T>::type{0, 0, 0, 0};
 
   const int nk = (K + BK - 1) / BK;
-  load(0);
-  store(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load((kt + 1) * BK);
-    // this wave's MFMA block at raised issue priority (the next slab's loads are out; the LDS store
-    // and the barrier follow it), with the compiler's MFMA / LDS-read interleaving strategy 0
-    __builtin_amdgcn_s_setprio(1);
-    __builtin_amdgcn_iglp_opt(0);
+  // the products of the slab in LDS buffer buf
+  auto products = [&](int buf) {
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 4) {
       T av[TM], bv[TN];
@@ -222,9 +228,112 @@ __device__ __forceinline__ void gemm_tile(gp<const TA> __restrict__ A, int lda, 
 #pragma unroll
         for (int b = 0; b < TN; ++b) acc[a][b] = mfma16(av[a], bv[b], acc[a][b]);
     }
+  };
+  constexpr int PD = TileShape<BM>::PD;
+  if constexpr (PD > 1) {
+    // PD slabs in registers, loaded without branches: indices past the matrix are clamped into it (rows
+    // and columns past the edge are not stored, the k tail is zeroed on its way to LDS)
+    static_assert(PD % 2 == 0, "the LDS buffer of a slab must follow from its register set");
+    T qa[PD][LA], qb[PD][LB];
+    auto fetch = [&](auto set, int kt) {
+      const int k0 = kt * BK;
+      if constexpr (pairs) {
+        static_for<0, LA / 2>([&](auto p) {
+          int i, k;
+          a_pair(p, i, k);
+          const int gi = min(m0 + i, TRA ? M - 2 : M - 1), gk = min(k0 + k, TRA ? K - 1 : K - 2);
+          const v2d v = *(gp<const v2d>)((gp<const double>)A + (TRA ? (int64_t)gk * lda + gi : (int64_t)gi * lda + gk));
+          qa[set][2 * p] = v.x;
+          qa[set][2 * p + 1] = v.y;
+        });
+        static_for<0, LB / 2>([&](auto p) {
+          int k, j;
+          b_pair(p, k, j);
+          const int gk = min(k0 + k, TRB ? K - 2 : K - 1), gj = min(n0 + j, TRB ? N - 1 : N - 2);
+          const v2d v = *(gp<const v2d>)((gp<const double>)B + (TRB ? (int64_t)gj * ldb + gk : (int64_t)gk * ldb + gj));
+          qb[set][2 * p] = v.x;
+          qb[set][2 * p + 1] = v.y;
+        });
+      } else {
+        static_for<0, LA>([&](auto p) {
+          int i, k;
+          a_coord(p, i, k);
+          const int gi = min(m0 + i, M - 1), gk = min(k0 + k, K - 1);
+          qa[set][p] = T(TRA ? A[(int64_t)gk * lda + gi] : A[(int64_t)gi * lda + gk]);
+        });
+        static_for<0, LB>([&](auto p) {
+          int k, j;
+          b_coord(p, k, j);
+          const int gk = min(k0 + k, K - 1), gj = min(n0 + j, N - 1);
+          qb[set][p] = T(TRB ? B[(int64_t)gj * ldb + gk] : B[(int64_t)gk * ldb + gj]);
+        });
+      }
+    };
+    auto put = [&](auto set, int kt) {
+#pragma unroll
+      for (int p = 0; p < LA; ++p) ra[p] = qa[set][p];
+#pragma unroll
+      for (int p = 0; p < LB; ++p) rb[p] = qb[set][p];
+      if ((kt + 1) * BK > K) {  // the last slab's tail: both operands zero past K
+#pragma unroll
+        for (int p = 0; p < LA; ++p) {
+          int i, k;
+          if constexpr (pairs) {
+            a_pair(p / 2, i, k);
+            k += TRA ? 0 : p & 1;
+          } else {
+            a_coord(p, i, k);
+          }
+          if (kt * BK + k >= K) ra[p] = T(0);
+        }
+#pragma unroll
+        for (int p = 0; p < LB; ++p) {
+          int k, j;
+          if constexpr (pairs) {
+            b_pair(p / 2, k, j);
+            k += TRB ? p & 1 : 0;
+          } else {
+            b_coord(p, k, j);
+          }
+          if (kt * BK + k >= K) rb[p] = T(0);
+        }
+      }
+      store(set & 1);
+    };
+    if (nk > 0) {
+      static_for<0, PD>([&](auto set) { fetch(set, set); });
+      put(std::integral_constant<int, 0>{}, 0);
+      __syncthreads();
+      for (int kb = 0; kb < nk; kb += PD) {
+        static_for<0, PD>([&](auto u) {
+          const int kt = kb + u;
+          if (kt < nk) {  // uniform
+            fetch(u, kt + PD);  // set u has gone to LDS; past the end the clamped loads repeat the last entries
+            __builtin_amdgcn_s_setprio(1);
+            products(u & 1);
+            __builtin_amdgcn_s_setprio(0);
+            if (kt + 1 < nk) put(std::integral_constant<int, (u + 1) % PD>{}, kt + 1);
+            __syncthreads();
+          }
+        });
+      }
+    }
+  } else {
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; ++kt) {
+    const int buf = kt & 1;
+    if (kt + 1 < nk) load((kt + 1) * BK);
+    // this wave's MFMA block at raised issue priority (the next slab's loads are out; the LDS store
+    // and the barrier follow it), with the compiler's MFMA / LDS-read interleaving strategy 0
+    __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_iglp_opt(0);
+    products(buf);
     __builtin_amdgcn_s_setprio(0);
     if (kt + 1 < nk) store(buf ^ 1);
     __syncthreads();
+  }
   }
 
 #pragma unroll
@@ -334,12 +443,18 @@ tna_status launch_tile(const GemmArgs &a, const GemmDev &d, hipStream_t s) {
   return TNA_OK;
 }
 
-// Tile choice: the 128 x 128 tile when the grid still has >= 2 waves of
-// workgroups on 256 CUs, else 64 x 64 to spread small problems.
+// Tile choice: the 128 x 128 tile when the grid still has >= 2 waves of workgroups on 256 CUs, else
+// 64 x 64, and 32 x 32 (each operand read twice as often, four times the workgroups) where that would
+// leave the chip with less than two 64 x 64 workgroups per CU.  H_eff with the 64 x 64 and the 32 x 32 tile
+// below the line: J1-J2 96 x 96 60.0 / 35.8 us, 203 x 331 200 / 126 us, 400 x 380 254 / 216 us, 512 x 512
+// 378 / 359 us; at 640 x 600, where few products are left below it, 651 / 632 us.
+constexpr int GEMM_MID_TILES = 512;
 template <typename T, typename TA, typename TB, typename TC>
 tna_status launch_types(const GemmArgs &a, const GemmDev &d, hipStream_t s) {
   int64_t big = (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
   if (big >= 512) return launch_tile<T, TA, TB, TC, 128, 128>(a, d, s);
+  const int64_t mid = (int64_t)((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch;
+  if (mid < GEMM_MID_TILES) return launch_tile<T, TA, TB, TC, 32, 32>(a, d, s);
   return launch_tile<T, TA, TB, TC, 64, 64>(a, d, s);
 }
 
@@ -384,6 +499,7 @@ tna_status launch_grouped(const GemmGroup &g, const GemmProb *d, int nprob, int 
 template <typename T, typename TA, typename TB, typename TC>
 tna_status grouped_types(const GemmGroup &g, const GemmProb *d, int nprob, int total, hipStream_t s) {
   if (g.tile == 128) return launch_grouped<T, TA, TB, TC, 128, 128>(g, d, nprob, total, s);
+  if (g.tile == 32) return launch_grouped<T, TA, TB, TC, 32, 32>(g, d, nprob, total, s);
   return launch_grouped<T, TA, TB, TC, 64, 64>(g, d, nprob, total, s);
 }
 

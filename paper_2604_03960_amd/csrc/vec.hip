@@ -48,19 +48,26 @@ struct MixDev {
 // constant address space those are scalar loads shared by the wave.  The channel counts are template
 // constants for the MPOs in use (CI1 = 0: runtime counts, at most 32 channels): with runtime counts the
 // 32 x 32 guarded products and their loads of M took 34 us for the 256 elements of a chi = 16 bond.
-template <typename T, int CI1, int CI2, int CJ1, int CJ2>
+// SPLIT: one j1 per grid row instead of all (CJ1 times the threads, x read as often): a launch with fewer
+// blocks than keep the chip busy is bound by each thread's walk over M (203 x 331, 32 channels: 33 us
+// without, 20 us with).
+template <typename T, int CI1, int CI2, int CJ1, int CJ2, bool SPLIT>
 __global__ __launch_bounds__(NT) void mix_kernel(MixDev a) {
   constexpr bool fixed = CI1 > 0;
+  static_assert(fixed || !SPLIT, "split needs the channel counts");
   const int I2 = fixed ? CI2 : a.I2, J2 = fixed ? CJ2 : a.J2;
   const int I = fixed ? CI1 * CI2 : a.I1 * a.I2, J = fixed ? CJ1 * CJ2 : a.J1 * a.J2;
-  constexpr int IM = fixed ? CI1 * CI2 : 32, JM = fixed ? CJ1 * CJ2 : 32;
+  constexpr int IM = fixed ? CI1 * CI2 : 32, JM = SPLIT ? CJ2 : fixed ? CJ1 * CJ2 : 32;
+  const int j1 = SPLIT ? blockIdx.y : 0;
   const int64_t idx = (int64_t)blockIdx.x * NT + threadIdx.x;
   const int64_t total = (int64_t)a.n0 * a.n1;
   if (idx >= total) return;
   const int64_t o0 = idx / a.n1, o1 = idx - o0 * a.n1;
   const T *in = static_cast<const T *>(a.in) + o0 * a.is0 + o1 * a.is1;
   T *out = static_cast<T *>(a.out) + o0 * a.os0 + o1 * a.os1;
-  const double __attribute__((address_space(4))) *M = (const double __attribute__((address_space(4))) *)a.M;
+  const double __attribute__((address_space(4))) *M =
+      (const double __attribute__((address_space(4))) *)a.M + (SPLIT ? j1 * J2 * I : 0);
+  if (SPLIT) out += (int64_t)j1 * a.och1;
   T x[IM];
 #pragma unroll
   for (int i = 0; i < IM; ++i) x[i] = (fixed || i < I) ? in[(i / I2) * a.ich1 + (i % I2) * a.ich2] : T(0);
@@ -266,21 +273,24 @@ tna_status mix(const MixArgs &a, hipStream_t s) {
     set_error("mix: type combination not built");
     return TNA_ERR_UNSUPPORTED;
   }
-  auto launch = [&](auto kd, auto kf) {
-    if (a.type_in == G_F64) hipLaunchKernelGGL(kd, grid, dim3(NT), 0, s, d);
-    else hipLaunchKernelGGL(kf, grid, dim3(NT), 0, s, d);
+  const bool split = grid.x < 1024;  // fewer than four blocks per compute unit
+  auto launch = [&](auto kd, auto kf, bool rows) {
+    const dim3 g(grid.x, rows ? a.J1 : 1);
+    if (a.type_in == G_F64) hipLaunchKernelGGL(kd, g, dim3(NT), 0, s, d);
+    else hipLaunchKernelGGL(kf, g, dim3(NT), 0, s, d);
   };
-#define TNA_MIX_CASE(b, c, e, f)                                                              \
-  if (a.I1 == b && a.I2 == c && a.J1 == e && a.J2 == f)                                     \
-    launch(mix_kernel<double, b, c, e, f>, mix_kernel<float, b, c, e, f>);                  \
-  else
+#define TNA_MIX_CASE(b, c, e, f)                                                                        \
+  if (a.I1 == b && a.I2 == c && a.J1 == e && a.J2 == f) {                                             \
+    if (split) launch(mix_kernel<double, b, c, e, f, true>, mix_kernel<float, b, c, e, f, true>, true); \
+    else launch(mix_kernel<double, b, c, e, f, false>, mix_kernel<float, b, c, e, f, false>, false);    \
+  } else
   TNA_MIX_CASE(5, 4, 4, 5)
   TNA_MIX_CASE(5, 2, 2, 5)
   TNA_MIX_CASE(8, 4, 4, 8)
   TNA_MIX_CASE(8, 2, 2, 8)
   TNA_MIX_CASE(3, 4, 4, 3)
   TNA_MIX_CASE(3, 2, 2, 3)
-  launch(mix_kernel<double, 0, 0, 0, 0>, mix_kernel<float, 0, 0, 0, 0>);
+  launch(mix_kernel<double, 0, 0, 0, 0, false>, mix_kernel<float, 0, 0, 0, 0, false>, false);
 #undef TNA_MIX_CASE
   const int es = a.type_in == G_F64 ? 8 : 4;
   timer_end(name, 2.0 * I * J * (double)total, (double)total * (I + J) * es, s);
