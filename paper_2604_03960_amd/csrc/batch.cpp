@@ -458,7 +458,7 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
   };
   // ---- which visits run whole Lanczos iterations inside one workgroup (short theta, all of
   // H_eff's operands in LDS); the rest go through the grouped GEMM/mixing/CGS2 launches
-  std::vector<int> small(nc, 0), sm_ac(nc, 1);
+  std::vector<int> small(nc, 0), sm_ac(nc, 1), sm_keep(nc, 0);
   int nsmall = 0;
   size_t lds_small = 0;
   if (d == 2 && D * d * d <= 64) {
@@ -466,9 +466,12 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
       const Visit &v = vs[q];
       if (v.nv > LZ_SMALL_N) continue;
       int ac = std::max(1, std::min(v.chl, NT_SMALL / std::max(1, v.chr)));
-      while (ac > 1 && lz_small_lds(v.chl, v.chr, d, D, ac, f32) > LZ_SMALL_LDS_MAX) ac /= 2;
-      const size_t need = lz_small_lds(v.chl, v.chr, d, D, ac, f32);
+      while (ac > 1 && lz_small_lds(v.chl, v.chr, d, D, ac, f32, 0) > LZ_SMALL_LDS_MAX) ac /= 2;
+      size_t need = lz_small_lds(v.chl, v.chr, d, D, ac, f32, 0);
       if (need > LZ_SMALL_LDS_MAX) continue;
+      const size_t need_keep = lz_small_lds(v.chl, v.chr, d, D, ac, f32, 1);
+      sm_keep[q] = v.nv <= LZ_KEEP_N && need_keep <= LZ_SMALL_LDS_MAX;
+      if (sm_keep[q]) need = need_keep;
       small[q] = 1;
       sm_ac[q] = ac;
       lds_small = std::max(lds_small, need);
@@ -769,7 +772,7 @@ tna_status engine_step(tna_engine en, const std::vector<tna_dmrg> &ch, const std
       const Visit &v = vs[q];
       const int sl = slot[q];
       tna_dmrg dm = ch[q];
-      sp.push_back(LzSmall{v.chl, v.chr, v.kmax, sm_ac[q], D, 0, dm->Le[v.b].as<double>(), dm->Re[v.b + 1].as<double>(),
+      sp.push_back(LzSmall{v.chl, v.chr, v.kmax, sm_ac[q], D, sm_keep[q], dm->Le[v.b].as<double>(), dm->Re[v.b + 1].as<double>(),
                            dm->M12.as<double>() + (size_t)I2 * I2 * v.b, lp[q].V, j_dev + sl, act_dev + sl,
                            rec_small + (size_t)2 * LZ_HMAX * sl});
       sq.push_back(q);

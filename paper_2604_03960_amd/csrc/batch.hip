@@ -505,8 +505,7 @@ __global__ __launch_bounds__(NT) void lz_ritz1_kernel(const LzProb *probs) {
 // The operand type T is double (v_mfma_f64_16x16x4_f64) or float (the
 // mixed-precision form: L, R, M and theta rounded to FP32 in LDS, products on
 // v_mfma_f32_16x16x4_f32 with FP32 accumulation, the result stored as FP64).
-// CGS2 against the FP64 basis in global memory follows (dot products eight at
-// a time); alpha_j, beta_j^2 of every iteration go to rec[2j], rec[2j+1].  A
+// CGS2 against the FP64 basis, in registers or in global memory, follows; alpha_j, beta_j^2 of every iteration go to rec[2j], rec[2j+1].  A
 // workgroup stops at kmax, after `iters` iterations, or when beta_j is
 // negligible.
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -646,11 +645,47 @@ __device__ inline double block_total(double v, double *sh) {
   return r;
 }
 
-template <class T>
-__global__ __launch_bounds__(NTS) void lz_small_kernel(const LzSmall *probs, int iters) {
-  extern __shared__ double lds[];
-  const LzSmall &p = probs[blockIdx.x];
-  if (!*p.active) return;
+// The basis of a short theta held in registers for the CGS2 passes: wave i % 8 holds V_i, EL pairs of
+// consecutive elements a lane, up to KR vectors a wave (the rest is read from memory).  A wave then has all
+// of its projections h_i by itself, subtracts nothing but writes its sum of h_i V_i to LDS, and one thread
+// per element pair adds the eight sums: two barriers a pass and no memory in between.  Read from memory four
+// times an iteration (one compute unit's path to L2: 156 KB a time at 20 vectors of 16 x 16), the basis took
+// 19000 of 38000 cycles of an iteration there, in registers 9900; at 8 x 8, 10700 and 5900.  KR: what two waves
+// a SIMD leave room for beside the H_eff products.
+template <int EL> struct LzKeep {
+  static constexpr int KR = EL == 8 ? 5 : EL == 4 ? 10 : 16;
+  double2 x[KR][EL];
+};
+template <> struct LzKeep<0> {};
+
+// (address space of device memory: loads of the basis need not wait for LDS)
+typedef const double2 __attribute__((address_space(1))) *LzBasis;
+
+// f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>): register arrays indexed by constants
+template <int B, int E, class F>
+__device__ __forceinline__ void lz_static_for(F &&f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    lz_static_for<B + 1, E>(f);
+  }
+}
+
+// the same, ended by the first f that returns false: one jump past the rest of the code
+template <int B, int E, class F>
+__device__ __forceinline__ void lz_static_while(F &&f) {
+  if constexpr (B < E) {
+    if (f(std::integral_constant<int, B>{})) lz_static_while<B + 1, E>(f);
+  }
+}
+
+__device__ inline double lane63(double v) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                          __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// EL: element pairs a lane holds of a basis vector (0: the basis stays in memory)
+template <class T, int EL>
+__device__ __forceinline__ void lz_small_body(const LzSmall &p, int iters, double *lds) {
   constexpr int dd = 4;  // d^2, d = 2
   constexpr int NW = NTS / 64;
   const int D = p.D, DD = D * dd;
@@ -674,16 +709,45 @@ __global__ __launch_bounds__(NTS) void lz_small_kernel(const LzSmall *probs, int
   T *Ms = Rs + (size_t)chr * ldr;                    // M[o][i], rows o of stride ldm
   T *Xc = Ms + DD * ldm;                             // X[al][i][c'] of a chunk
   T *Zc = Xc + (size_t)ac * DD * chr;                // Z[al][s t][w''][c'], rows (al, s t) of stride ldz
+  // EL > 0: per-wave sums of the CGS2 updates, 8 x n, over X and Z
+  double2 *const part = reinterpret_cast<double2 *>(lds) + ((reinterpret_cast<char *>(Xc) - reinterpret_cast<char *>(lds) + 15) >> 4);
+  LzKeep<EL> keep;
   for (int e = tid; e < chl * D * chl; e += NTS) Ls[(e / chl) * ldl + e % chl] = (T)p.L[e];
   for (int e = tid; e < chr * D * chr; e += NTS) Rs[(e / (D * chr)) * ldr + e % (D * chr)] = (T)p.R[e];
   for (int e = tid; e < DD * DD; e += NTS) Ms[(e / DD) * ldm + e % DD] = (T)p.M[e];
-  int j = *p.j;
+  int j = __builtin_amdgcn_readfirstlane(*p.j);
+  // the records of this launch, iteration `it` in thread it < 64, until it ends: a store to the host's
+  // memory in the loop would hold up every later wait for a load until the host has answered
+  const int j0 = j;
+  double rec_a = 0.0, rec_b = 0.0;
+  const int n2 = n >> 1, uwave = __builtin_amdgcn_readfirstlane(wave);
+  if constexpr (EL > 0) {
+    // vectors 0..j as they are at the start of this launch, V_j as the first operand
+    lz_static_for<0, LzKeep<EL>::KR>([&](auto k) {
+      const int i = uwave + NW * k;
+      const LzBasis v = (LzBasis)(V + (int64_t)min(i, j) * n);
+#pragma unroll
+      for (int u = 0; u < EL; ++u) {
+        const int e = lane + 64 * u;
+        keep.x[k][u] = double2{0.0, 0.0};
+        if (i <= j && e < n2) {
+          keep.x[k][u].x = v[e].x;
+          keep.x[k][u].y = v[e].y;
+        }
+      }
+    });
+    const double *vj = V + (int64_t)j * n;
+    for (int e = tid; e < n; e += NTS) th[e] = (T)vj[e];
+    __syncthreads();
+  }
   for (int it = 0; it < iters && j < kmax; ++it) {
     const double *vj = V + (int64_t)j * n;
     double *vn = V + (int64_t)(j + 1) * n;
-    __syncthreads();  // previous iteration done with th, wv and hb
-    for (int e = tid; e < n; e += NTS) th[e] = (T)vj[e];
-    __syncthreads();
+    if constexpr (EL == 0) {
+      __syncthreads();  // previous iteration done with th, wv and hb
+      for (int e = tid; e < n; e += NTS) th[e] = (T)vj[e];
+      __syncthreads();
+    }
     for (int a0 = 0; a0 < chl; a0 += ac) {
       const int na = chl - a0 < ac ? chl - a0 : ac;
       block_gemm<T>(na * D, nr, chl, [&](int i, int k) { return Ls[(a0 * D + i) * ldl + k]; },
@@ -714,11 +778,145 @@ __global__ __launch_bounds__(NTS) void lz_small_kernel(const LzSmall *probs, int
                     [&](int i, int c, T v) { wv[(a0 * dd + i) * chr + c] = (double)v; }, Xc, ac * DD * chr);
       __syncthreads();
     }
+    if constexpr (EL > 0) {
+      constexpr int KR = LzKeep<EL>::KR;
+      double2 *const W2 = reinterpret_cast<double2 *>(wv);
+      const int kc = j >= uwave ? ((j - uwave) >> 3) + 1 : 0;  // this wave's vectors
+      double2 mine = {0.0, 0.0};                               // w of this thread's pair (tid < n2)
+      double b2 = 0.0;
+      for (int pass = 0; pass < 2; ++pass) {
+        double hk[KR];  // h of the vectors in registers, uniform
+        {
+          double2 w[EL];
+#pragma unroll
+          for (int u = 0; u < EL; ++u) {
+            const int e = lane + 64 * u;
+            w[u] = double2{0.0, 0.0};
+            if (e < n2) w[u] = W2[e];
+          }
+          auto dot = [&](const double2(&x)[EL]) {
+            double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+            for (int u = 0; u < EL; ++u) {
+              a0 += x[u].x * w[u].x;
+              a1 += x[u].y * w[u].y;
+            }
+            return a0 + a1;
+          };
+          lz_static_while<0, (KR + 1) / 2>([&](auto g) {  // two vectors at a time: their reductions overlap
+            constexpr int k0 = 2 * g, k1 = 2 * g + 1 < KR ? 2 * g + 1 : 2 * g;
+            if (k0 >= kc) return false;
+            double d0 = dot(keep.x[k0]), d1 = k1 > k0 ? dot(keep.x[k1]) : 0.0;
+            wave_total2(d0, d1);
+            hk[k0] = lane63(d0);
+            if (k1 > k0) hk[k1] = lane63(d1);
+            return true;
+          });
+          for (int k = KR; k < kc; ++k) {
+            const LzBasis v = (LzBasis)(V + (int64_t)(uwave + NW * k) * n);
+            double2 x[EL];
+#pragma unroll
+            for (int u = 0; u < EL; ++u) {
+              x[u] = double2{0.0, 0.0};
+              if (lane + 64 * u < n2) {
+                x[u].x = v[lane + 64 * u].x;
+                x[u].y = v[lane + 64 * u].y;
+              }
+            }
+            const double h = wave_total(dot(x));
+            if (lane == 63) hb[pass * LZ_HMAX + uwave + NW * k] = h;  // read by this wave alone
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        double2 sum[EL];
+#pragma unroll
+        for (int u = 0; u < EL; ++u) sum[u] = double2{0.0, 0.0};
+        double al = 0.0;  // <V_j, w> of the wave that holds V_j
+        lz_static_while<0, (KR + 1) / 2>([&](auto g) {
+          constexpr int k0 = 2 * g, k1 = 2 * g + 1 < KR ? 2 * g + 1 : 2 * g;
+          if (k0 >= kc) return false;
+#pragma unroll
+          for (int u = 0; u < EL; ++u) {
+            sum[u].x += hk[k0] * keep.x[k0][u].x;
+            sum[u].y += hk[k0] * keep.x[k0][u].y;
+          }
+          if (k1 > k0)  // (zero while not yet there)
+#pragma unroll
+            for (int u = 0; u < EL; ++u) {
+              sum[u].x += hk[k1] * keep.x[k1][u].x;
+              sum[u].y += hk[k1] * keep.x[k1][u].y;
+            }
+          al = k1 < kc ? hk[k1] : hk[k0];
+          return true;
+        });
+        for (int k = KR; k < kc; ++k) {
+          const LzBasis v = (LzBasis)(V + (int64_t)(uwave + NW * k) * n);
+          al = hb[pass * LZ_HMAX + uwave + NW * k];
+#pragma unroll
+          for (int u = 0; u < EL; ++u)
+            if (lane + 64 * u < n2) {
+              sum[u].x += al * v[lane + 64 * u].x;
+              sum[u].y += al * v[lane + 64 * u].y;
+            }
+        }
+        if (pass == 0 && uwave == (j & (NW - 1)) && lane == 0) red[NW] = al;  // alpha_j
+#pragma unroll
+        for (int u = 0; u < EL; ++u)
+          if (lane + 64 * u < n2) part[wave * n2 + lane + 64 * u] = sum[u];
+        __syncthreads();
+        double loc = 0.0;
+        if (tid < n2) {
+          double2 s[NW];
+#pragma unroll
+          for (int q = 0; q < NW; ++q) s[q] = part[q * n2 + tid];
+          if (pass == 0) mine = W2[tid];
+          double2 acc = s[0];
+#pragma unroll
+          for (int q = 1; q < NW; ++q) {
+            acc.x += s[q].x;
+            acc.y += s[q].y;
+          }
+          mine.x -= acc.x;
+          mine.y -= acc.y;
+          if (pass == 0) W2[tid] = mine;
+          loc = mine.x * mine.x + mine.y * mine.y;
+        }
+        if (pass == 1) b2 = block_total(loc, red);
+        else __syncthreads();
+      }
+      if (tid == it) {
+        rec_a = red[NW];
+        rec_b = b2;
+      }
+      // the host stops a chain at beta_j < 1e-14 (or a non-finite record): same predicate here
+      const double beta = sqrt(b2);
+      const bool stop = !(beta >= 1e-14);
+      const double f = stop ? 1.0 : 1.0 / beta;
+      if (tid < n2) {
+        mine.x *= f;
+        mine.y *= f;
+        reinterpret_cast<double2 *>(vn)[tid] = mine;
+        W2[tid] = mine;
+        th[2 * tid] = (T)mine.x;
+        th[2 * tid + 1] = (T)mine.y;
+      }
+      ++j;
+      if (stop) break;
+      __syncthreads();
+      if (uwave == (j & (NW - 1)))
+        lz_static_for<0, KR>([&](auto k) {
+          if (k == (j >> 3))
+#pragma unroll
+            for (int u = 0; u < EL; ++u)
+              if (lane + 64 * u < n2) keep.x[k][u] = W2[lane + 64 * u];
+        });
+      continue;
+    }
     // CGS2 against V_0..V_j (n is a multiple of 4: element pairs, 16-byte accesses).  Dot
     // products: one wave per basis vector (vectors wave, wave + 8, ..., two at a time), lanes over
     // the element pairs, a DPP reduction; updates: one thread per element pair, sixteen vectors
     // per batch of loads.
-    const int n2 = n >> 1;
     const double2 *W2 = reinterpret_cast<const double2 *>(wv);
     double b2 = 0.0;
     for (int pass = 0; pass < 2; ++pass) {
@@ -798,9 +996,9 @@ __global__ __launch_bounds__(NTS) void lz_small_kernel(const LzSmall *probs, int
       if (pass == 1) b2 = block_total(loc, red);
       else __syncthreads();
     }
-    if (tid == 0) {
-      rec[2 * j] = hb[j];  // alpha_j from the first pass
-      rec[2 * j + 1] = b2;
+    if (tid == it) {
+      rec_a = hb[j];  // alpha_j from the first pass
+      rec_b = b2;
     }
     // the host stops a chain at beta_j < 1e-14 (or a non-finite record): same predicate here
     const double beta = sqrt(b2);
@@ -810,10 +1008,29 @@ __global__ __launch_bounds__(NTS) void lz_small_kernel(const LzSmall *probs, int
     ++j;
     if (stop) break;
   }
+  if (tid < j - j0) {
+    rec[2 * (j0 + tid)] = rec_a;
+    rec[2 * (j0 + tid) + 1] = rec_b;
+  }
   if (tid == 0) {
     *p.j = j;
     rec[2 * LZ_HMAX - 1] = (double)j;  // read back with the records (they end below 2 LZ_HMAX - 2)
   }
+}
+
+// Register budget of two waves per SIMD.  The form is chosen by theta's length alone: 512 threads own one
+// element pair each up to n = 1024; a lane's share of a vector follows.
+template <class T>
+__global__ __launch_bounds__(NTS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lz_small_kernel(
+    const LzSmall *probs, int iters) {
+  extern __shared__ double lds[];
+  const LzSmall &p = probs[blockIdx.x];
+  if (!*p.active) return;
+  const int n = 4 * p.chl * p.chr;
+  if (!p.keep) lz_small_body<T, 0>(p, iters, lds);
+  else if (n <= 256) lz_small_body<T, 2>(p, iters, lds);
+  else if (n <= 512) lz_small_body<T, 4>(p, iters, lds);
+  else lz_small_body<T, 8>(p, iters, lds);
 }
 
 __global__ __launch_bounds__(NT) void convert_grouped_kernel(const CvtProb *probs) {
@@ -913,13 +1130,14 @@ tna_status lz_ritz(const LzProb *d, int nch, int maxG, hipStream_t s) {
   return TNA_OK;
 }
 
-size_t lz_small_lds(int chl, int chr, int d, int D, int ac, int f32) {
+size_t lz_small_lds(int chl, int chr, int d, int D, int ac, int f32, int keep) {
   const size_t n = (size_t)chl * d * d * chr, DD = (size_t)D * d * d;
   const size_t ldl = chl | 1, ldr = (D * chr) | 1, ldm = DD | 1, ldz = ldr;
   const size_t es = f32 ? sizeof(float) : sizeof(double);
+  const size_t xz = es * ((size_t)ac * DD * chr + (size_t)ac * d * d * ldz);
   return sizeof(double) * (n + 2 * LZ_HMAX + 16 * (NTS / 64)) +
-         es * (n + (size_t)chl * D * ldl + (size_t)chr * ldr + DD * ldm + (size_t)ac * DD * chr +
-               (size_t)ac * d * d * ldz);
+         es * (n + (size_t)chl * D * ldl + (size_t)chr * ldr + DD * ldm) +
+         (keep ? std::max(xz, 16 + sizeof(double) * n * (NTS / 64)) : xz);
 }
 
 tna_status lz_small(const LzSmall *d, int nch, int D, int dsq, int iters, size_t lds, int f32, hipStream_t s) {
@@ -938,6 +1156,10 @@ tna_status lz_small(const LzSmall *d, int nch, int D, int dsq, int iters, size_t
   if (!attr_set[f32 ? 1 : 0]) {
     TNA_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LZ_SMALL_LDS_MAX));
     attr_set[f32 ? 1 : 0] = true;
+  }
+  if (iters > 64) {
+    set_error("lz_small: at most 64 iterations a launch");
+    return TNA_ERR_ARG;
   }
   if (lds > LZ_SMALL_LDS_MAX) {
     set_error("lz_small: LDS need above the limit");

@@ -50,4 +50,21 @@ __device__ inline double wave_total(double v) {
   return v;
 }
 
+// two wave totals, their steps taken in turn
+__device__ inline void wave_total2(double &a, double &b) {
+#define TNA_SUM2(CTRL, ROWS)                                           \
+  {                                                                    \
+    const double x = dpp_d<CTRL, ROWS>(a), y = dpp_d<CTRL, ROWS>(b);    \
+    a += x;                                                            \
+    b += y;                                                            \
+  }
+  TNA_SUM2(0xB1, 0xf)
+  TNA_SUM2(0x4E, 0xf)
+  TNA_SUM2(0x141, 0xf)
+  TNA_SUM2(0x140, 0xf)
+  TNA_SUM2(0x142, 0xa)
+  TNA_SUM2(0x143, 0xc)
+#undef TNA_SUM2
+}
+
 }  // namespace tna

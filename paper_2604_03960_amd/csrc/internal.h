@@ -268,9 +268,12 @@ tna_status lz_ritz(const LzProb *d, int nch, int maxG, hipStream_t s);
 // Single-workgroup Lanczos for short vectors (all of H_eff's operands in LDS).
 constexpr int LZ_HMAX = 128;                       // >= kmax + 1
 constexpr size_t LZ_SMALL_LDS_MAX = 160 * 1024;    // LDS of one gfx950 workgroup
+constexpr int LZ_KEEP_N = 1024;                    // longest theta whose basis is kept in registers: an element
+                                                   // pair per thread, and no more vectors than five fit beyond
 struct LzSmall {
   int chl, chr, kmax, ac;  // ac: left indices per chunk of the three H_eff products
-  int D, pad_;
+  int D;
+  int keep;                // the Krylov basis is held in registers (theta of at most LZ_KEEP_N elements)
   const double *L, *R, *M; // L[a][w][a'], R[c][w''][c'], mixing matrix (D d^2)^2
   double *V;               // Krylov basis, V_0 set
   int *j;
@@ -278,8 +281,9 @@ struct LzSmall {
   double *rec;             // 2 (kmax + 1): alpha_j, beta_j^2
 };
 // LDS bytes of one workgroup; f32: the H_eff operands are held and multiplied in FP32
-size_t lz_small_lds(int chl, int chr, int d, int D, int ac, int f32);
-// Runs up to `iters` iterations for every active chain; lds = max over chains.
+// (keep: with the per-wave update sums of the basis in registers)
+size_t lz_small_lds(int chl, int chr, int d, int D, int ac, int f32, int keep);
+// Runs up to `iters` <= 64 iterations for every active chain; lds = max over chains.
 tna_status lz_small(const LzSmall *d, int nch, int D, int dsq, int iters, size_t lds, int f32, hipStream_t s);
 struct CvtProb {
   const double *src;
