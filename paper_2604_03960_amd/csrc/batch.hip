@@ -500,12 +500,13 @@ __global__ __launch_bounds__(NT) void lz_ritz1_kernel(const LzProb *probs) {
 // three small MFMA products on LDS-resident operands, a chunk of `ac` left
 // indices at a time:
 //   X[(a,w)][(s',t',c')] = sum_a' L[(a,w)][a'] theta[a'][(s',t',c')]
-//   Z[o=(s,t,w'')][(a,c')] = sum_i M[o][i=(w,s',t')] X[a][i][c']
+//   Z[o=(s,t,w'')][(a,c')] = sum_i M[o][i=(w,s',t')] X[a][i][c']  (or on the vector units, mix_columns)
 //   out[(a,s,t)][c] = sum_{(w'',c')} Z[a][(s,t,w'')][c'] R[c][(w'',c')]
 // The operand type T is double (v_mfma_f64_16x16x4_f64) or float (the
 // mixed-precision form: L, R, M and theta rounded to FP32 in LDS, products on
 // v_mfma_f32_16x16x4_f32 with FP32 accumulation, the result stored as FP64).
-// CGS2 against the FP64 basis, in registers or in global memory, follows; alpha_j, beta_j^2 of every iteration go to rec[2j], rec[2j+1].  A
+// CGS2 against the FP64 basis, in registers or in global memory, follows;
+// alpha_j, beta_j^2 of every iteration go to rec[2j], rec[2j+1].  A
 // workgroup stops at kmax, after `iters` iterations, or when beta_j is
 // negligible.
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -645,6 +646,52 @@ __device__ inline double block_total(double v, double *sh) {
   return r;
 }
 
+// Z = M X of a chunk on the vector units: wave w takes the rows (s, t) = w % 4 of M, the same for all its
+// lanes (LDS broadcasts), against two columns (al, c') a lane.  As 16 x 16 tiles of matrix instructions a
+// 20-row M leaves 3/8 of the products unused, and a tile's indexing costs more than its five products: a
+// sweep of 32 sites with D = 5 at 16 x 16 27.0 ms with tiles, 25.0 ms so.  Up to LZ_MIX_COLS columns half of
+// the lanes have no work here and the tiles stay; so do they for D = 8, whose eight rows of sums a column
+// spill next to a basis in registers, as four columns a lane do for D = 5 (5 % slower than two).
+constexpr int LZ_MIX_COLS = 128;
+template <class T, int CD>
+__device__ __forceinline__ void mix_columns(int na, int chr, int ldz, const T *Xc, T *Zc, const T *Ms,
+                                            int ldm, const FastDiv &divC) {
+  constexpr int I = 4 * CD, COLS = 2;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nac = na * chr, st = wave & 3;
+  const T *m = Ms + st * CD * ldm;
+  for (int x0 = (wave >> 2) * 64 * COLS; x0 < nac; x0 += NTS / 256 * 64 * COLS) {
+    T acc[COLS][CD];
+    const T *xi[COLS];
+    int zo[COLS];
+#pragma unroll
+    for (int e = 0; e < COLS; ++e) {
+      const int x = x0 + 64 * e + lane, xc = x < nac ? x : nac - 1, al = divC.div(xc), cc = xc - al * chr;
+      xi[e] = Xc + al * I * chr + cc;
+      zo[e] = x < nac ? (al * 4 + st) * ldz + cc : -1;
+#pragma unroll
+      for (int u = 0; u < CD; ++u) acc[e][u] = T(0);
+    }
+#pragma unroll 2
+    for (int i = 0; i < I; ++i) {
+      T v[COLS];
+#pragma unroll
+      for (int e = 0; e < COLS; ++e) v[e] = xi[e][i * chr];
+#pragma unroll
+      for (int u = 0; u < CD; ++u) {
+        const T mv = m[u * ldm + i];
+#pragma unroll
+        for (int e = 0; e < COLS; ++e) acc[e][u] += mv * v[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < COLS; ++e)
+      if (zo[e] >= 0)
+#pragma unroll
+        for (int u = 0; u < CD; ++u) Zc[zo[e] + u * chr] = acc[e][u];
+  }
+}
+
 // The basis of a short theta held in registers for the CGS2 passes: wave i % 8 holds V_i, EL pairs of
 // consecutive elements a lane, up to KR vectors a wave (the rest is read from memory).  A wave then has all
 // of its projections h_i by itself, subtracts nothing but writes its sum of h_i V_i to LDS, and one thread
@@ -755,7 +802,9 @@ __device__ __forceinline__ void lz_small_body(const LzSmall &p, int iters, doubl
                     [&](int i, int c, T v) { Xc[i * nr + c] = v; });
       __syncthreads();
       // output row o = (s t, w'') goes to Zc row (al, s t) at column w'' chr + c'
-      if (chr >= 16)  // one product per row index al: no division in the operand addressing
+      if (na * chr > LZ_MIX_COLS && D == 5) mix_columns<T, 5>(na, chr, ldz, Xc, Zc, Ms, ldm, divC);
+      else if (na * chr > LZ_MIX_COLS && D == 3) mix_columns<T, 3>(na, chr, ldz, Xc, Zc, Ms, ldm, divC);
+      else if (chr >= 16)  // one product per row index al: no division in the operand addressing
         block_gemm_nb<T>(na, DD, chr, DD, [&](int o, int i) { return Ms[o * ldm + i]; },
                          [&](int al, int i, int c) { return Xc[(al * DD + i) * chr + c]; },
                          [&](int al, int o, int c, T v) {

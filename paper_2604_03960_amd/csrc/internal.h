@@ -268,8 +268,9 @@ tna_status lz_ritz(const LzProb *d, int nch, int maxG, hipStream_t s);
 // Single-workgroup Lanczos for short vectors (all of H_eff's operands in LDS).
 constexpr int LZ_HMAX = 128;                       // >= kmax + 1
 constexpr size_t LZ_SMALL_LDS_MAX = 160 * 1024;    // LDS of one gfx950 workgroup
-constexpr int LZ_KEEP_N = 1024;                    // longest theta whose basis is kept in registers: an element
-                                                   // pair per thread, and no more vectors than five fit beyond
+// Longest theta whose basis is kept in registers: an element pair per thread; a wave has room for five vectors
+// of this length, and one twice as long would leave it two.
+constexpr int LZ_KEEP_N = 1024;
 struct LzSmall {
   int chl, chr, kmax, ac;  // ac: left indices per chunk of the three H_eff products
   int D;

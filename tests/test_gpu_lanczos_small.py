@@ -39,3 +39,21 @@ def test_more_vectors_than_registers(chi, its):
     assert max(g["lanczos_iters"] for g in recs) == its
     amb = _compare_amb(ro, np.array([E]), recs, 1e-10, N)
     assert abs(E - ro["E"][0]) / N <= 1e-10 + amb
+
+
+@pytest.mark.parametrize("model,params", [(0, [1.0, 0.8, 0.0]), (1, [1.0, 0.241]), (2, [1.0, 1.3])])
+@pytest.mark.parametrize("chi", [11, 12, 14])
+def test_mixing_forms(model, params, chi):
+    """Both forms of the mixing (121 columns a chunk and more) at every MPO bond dimension in use, twelve
+    matvecs a visit, at the tolerance of the fixed-iteration sweeps."""
+    import paper_2604_03960_amd as tna
+    N = 10
+    W = oracle.mpo(model, N, params)
+    A, c0, _ = synth.random_mps(N, 2, chi, seed=77)
+    pp = (2.0, 0.1, 0.5, 1.0, 0.3, chi, chi)
+    ro = oracle.dmrg_run(W, A, c0, oracle.pid_params(*pp), 1, fixed_iters=12, fixed_chi=chi)
+    dm = tna.Dmrg(ctx(), W, A, c0, tna.pid_params(*pp), fixed_iters=12, fixed_chi=chi)
+    E, recs, _ = dm.sweep()
+    assert dm.stats()["small_launches"] > 0
+    amb = _compare_amb(ro, np.array([E]), recs, 1e-10, N)
+    assert abs(E - ro["E"][0]) / N <= 1e-10 + amb
