@@ -10,8 +10,8 @@
 // Products run in the order of the general path (k ascending in steps of four, one accumulator; the
 // mixing sum over i ascending), so both give the same bits, in FP64 and in the FP32-operator form.
 // Bound by latency: operand loads of a tile, then few waves for the last product's chr / 16 tiles.
-// D = 5, FP64: 7.5 us a call at chi = 16 (21 us in four launches, 44 us before the mixing had
-// compile-time channel counts), 23 us at 64 (41 us).
+// D = 5, FP64: 7.5 us a call at chi = 16 (15 us in four launches, 44 us before the mixing had
+// compile-time channel counts), 17.5 us at 48 (18.6 us).
 #include <algorithm>
 #include <cstdint>
 
@@ -173,7 +173,7 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb) {
 
 bool heff_small_takes(int chl, int chr, int d, int D, const double *L, const double *W1, const double *W2,
                       const double *R, const double *theta, const double *out, int prec) {
-  if (d != 2 || D < 1 || D > 8 || chl > HEFF_SMALL_CHL || chr > HEFF_SMALL_CHR) return false;
+  if (d != 2 || D < 1 || D > 8 || !heff_small_bond(chl, chr)) return false;
   if (prec != TNA_HEFF_F64 && prec != TNA_HEFF_F32) return false;
   // the general path has read L, W1 and W2 whole before it writes out; a caller may rely on that
   const size_t w = sizeof(double) * 4 * (size_t)D * D, no = sizeof(double) * 4 * (size_t)chl * chr;

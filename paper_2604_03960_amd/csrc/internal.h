@@ -317,10 +317,12 @@ struct HeffOp {
 };
 tna_status heff_device(const HeffOp &h, const double *x, double *out, hipStream_t s);
 // One-launch form for short bonds (heff.hip): whether it takes a call, and the call.
-// Longest bonds it takes: its time grows with chr (the mixing and the last product run on few waves a
-// workgroup), the general path's four launches cost about the same up to there (D = 5, FP64: 33 against
-// 49 us at chi 80, 40 against 50 at 96; D = 3: 24 against 31 and 30 against 31).
-constexpr int HEFF_SMALL_CHL = 192, HEFF_SMALL_CHR = 80;
+// Longest bonds it takes.  Its time grows with chr (the mixing and the last product run on few waves a
+// workgroup), the four launches of the general path cost about the same up to there.  One launch / general,
+// D = 5, FP64: 11.4 / 15.9 us at 32 x 32, 17.8 / 18.7 at 192 x 32, 17.5 / 18.6 at 48 x 48, 23.6 / 19.5 at
+// 64 x 64, 33.6 / 22.8 at 192 x 64; D = 8: 23.1 / 26.5 at 192 x 32, 24.1 / 27.4 at 48 x 48, 31.2 / 28.4 at
+// 64 x 64; FP32 and D = 3 cross over in the same places.
+inline bool heff_small_bond(int chl, int chr) { return (chl <= 192 && chr <= 32) || (chl <= 64 && chr <= 48); }
 bool heff_small_takes(int chl, int chr, int d, int D, const double *L, const double *W1, const double *W2,
                       const double *R, const double *theta, const double *out, int prec);
 tna_status heff_small(int chl, int chr, int D, const double *L, const double *W1, const double *W2, const double *R,

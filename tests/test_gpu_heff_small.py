@@ -36,3 +36,17 @@ def test_result_over_an_input_already_read(prec):
     over = dL.view(-1)[:dth.numel()].view(dth.shape)
     got = ctx().heff_apply(dL, W1, W2, dR, dth, prec=prec, out=over)
     assert (got == want).all()
+
+
+@pytest.mark.parametrize("chl,chr_", [(192, 32), (193, 32), (192, 33), (64, 48), (65, 48), (64, 49)])
+def test_both_sides_of_the_line(chl, chr_):
+    """The longest bonds of the one-launch form and the first of the general one: a result written over an
+    input takes the general path, and both give the same bits."""
+    W, L, R, th = env_pair(1, [1.0, 0.241], chl, chr_, 60)
+    dL, W1, W2, dR, dth = [to_dev(x) for x in (L, W[1], W[2], R, th)]
+    got = ctx().heff_apply(dL, W1, W2, dR, dth).clone()
+    ref = oracle.heff_apply(L, W[1], W[2], R, th)
+    scale = np.abs(L).max() * np.abs(R).max() * np.abs(th).max() * max(chl, chr_) * 8
+    assert np.abs(got.cpu().numpy() - ref).max() <= 1e-14 * scale
+    over = dL.view(-1)[:dth.numel()].view(dth.shape)
+    assert (got == ctx().heff_apply(dL, W1, W2, dR, dth, out=over)).all()
