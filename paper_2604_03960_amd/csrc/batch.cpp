@@ -32,7 +32,7 @@ namespace {
 
 // ------------------------------------------------------------------ autotuner
 // Picks the GEMM tile (32, 64 or 128) per (operation, log2 flops) bucket by
-// timing both candidates on the live operands the first time a bucket is met.
+// timing every candidate on the live operands the first time a bucket is met.
 struct Autotune {
   std::map<std::pair<int, int>, int> table;
   int measured = 0;

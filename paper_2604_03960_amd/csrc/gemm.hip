@@ -319,21 +319,21 @@ __device__ __forceinline__ void gemm_tile(gp<const TA> __restrict__ A, int lda, 
       }
     }
   } else {
-  load(0);
-  store(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load((kt + 1) * BK);
-    // this wave's MFMA block at raised issue priority (the next slab's loads are out; the LDS store
-    // and the barrier follow it), with the compiler's MFMA / LDS-read interleaving strategy 0
-    __builtin_amdgcn_s_setprio(1);
-    __builtin_amdgcn_iglp_opt(0);
-    products(buf);
-    __builtin_amdgcn_s_setprio(0);
-    if (kt + 1 < nk) store(buf ^ 1);
+    load(0);
+    store(0);
     __syncthreads();
-  }
+    for (int kt = 0; kt < nk; ++kt) {
+      const int buf = kt & 1;
+      if (kt + 1 < nk) load((kt + 1) * BK);
+      // this wave's MFMA block at raised issue priority (the next slab's loads are out; the LDS store
+      // and the barrier follow it), with the compiler's MFMA / LDS-read interleaving strategy 0
+      __builtin_amdgcn_s_setprio(1);
+      __builtin_amdgcn_iglp_opt(0);
+      products(buf);
+      __builtin_amdgcn_s_setprio(0);
+      if (kt + 1 < nk) store(buf ^ 1);
+      __syncthreads();
+    }
   }
 
 #pragma unroll
