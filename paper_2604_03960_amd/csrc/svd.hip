@@ -90,27 +90,39 @@ __device__ inline void jacobi_rot(double a, double b, double g, double &c, doubl
 // chain of dependent operations cut into eight stages, so that a caller can issue other work between them;
 // each reciprocal square root takes the hardware estimate y (relative error below 2^-22) and one third-order
 // step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2, which cubes the error.
+// The rotation depends on the ratios of a, b and g alone, so they are first multiplied by the power of two that
+// brings the largest into [1, 2) (exact): the squares of squared norms would underflow for rows of norm
+// 1e-77 (also for a block of such rows in a matrix of norm 1) and overflow at 1e77.
 struct RotChain {
   double a, b, g;  // inputs: the 2 x 2 block [[a, g], [g, b]]
+  double as, bs, gs;  // the block, scaled
   double dl, x, y, e, ir, c2, ic, c, s, tg;
   bool act;
+  // g^2 > tol^2 a b
+  __device__ __forceinline__ bool coupled(double tol2) const { return gs * gs > tol2 * fabs(as * bs); }
   // (TEST off: the caller decides whether the rotation acts)
   template <int K, bool TEST = true>
   __device__ __forceinline__ void stage(double floor2) {
     constexpr double tol_in = 4.0 * 1.1102230246251565e-16;
     if constexpr (K == 0) {
-      dl = b - a;
-      x = fma(dl, dl, 4.0 * g * g);
+      constexpr int EXP = 0x7ff00000;
+      const int m = max(max(__double2hiint(a) & EXP, __double2hiint(b) & EXP), __double2hiint(g) & EXP);
+      const double sc = __hiloint2double(0x7fe00000 - m, 0);  // 2^1023 for an all-zero block
+      as = a * sc;
+      bs = b * sc;
+      gs = g * sc;
+      dl = bs - as;
+      x = fma(dl, dl, 4.0 * gs * gs);
     } else if constexpr (K == 1) {
       y = __builtin_amdgcn_rsq(x);
-      act = TEST ? (a > floor2 && b > floor2 && g * g > tol_in * tol_in * fabs(a * b)) : true;
+      act = TEST ? (a > floor2 && b > floor2 && coupled(tol_in * tol_in)) : true;
     } else if constexpr (K == 2) {
       e = fma(-(x * y), y, 1.0);
     } else if constexpr (K == 3) {
       ir = fma(y * e, fma(0.375, e, 0.5), y);
     } else if constexpr (K == 4) {
       c2 = fma(0.5 * fabs(dl), ir, 0.5);
-      s = (dl >= 0.0 ? g : -g) * ir;
+      s = (dl >= 0.0 ? gs : -gs) * ir;
       y = __builtin_amdgcn_rsq(c2);
     } else if constexpr (K == 5) {
       e = fma(-(c2 * y), y, 1.0);
@@ -487,10 +499,13 @@ __device__ inline int eig_t() { return threadIdx.x & (EigShape::LPG - 1); }
 __device__ inline int eig_rg() { return threadIdx.x / EigShape::LPG; }
 
 // From G in registers: its diagonal (through diag[64]), Q = I, and whether any pair of rows above the
-// floor fails the outer test |g_ij| <= tol sqrt(g_ii g_jj), taken squared.  Contains a barrier.
-__device__ inline int oe_start(const EigRegs &g, EigRegs &q, double &d0, double &d1, double *diag, double tol,
-                               double floor2) {
+// floor fails the outer test |g_ij| <= tol sqrt(g_ii g_jj), with the roots taken one by one (the product
+// of two squared norms leaves the range of FP64 at norms of 1e-81 and 1e77; through L's edge rows, free before
+// a sweep).  Contains barriers.
+__device__ inline int oe_start(OeLds<64, EIG_NW> &L, const EigRegs &g, EigRegs &q, double &d0, double &d1,
+                               double *diag, double tol, double floor2) {
   const int t = eig_t(), rg = eig_rg();
+  double *const root = &L.edge[0][0][0];
 #pragma unroll
   for (int i = 0; i < EigShape::HR; ++i) {
     const int r = EigShape::HR * rg + i;
@@ -498,18 +513,21 @@ __device__ inline int oe_start(const EigRegs &g, EigRegs &q, double &d0, double 
     if (r == 2 * t + 1) diag[r] = g[i][1];
   }
   __syncthreads();
+  if (threadIdx.x < 64) root[threadIdx.x] = sqrt(diag[threadIdx.x]);
+  __syncthreads();
   d0 = diag[2 * t];
   d1 = diag[2 * t + 1];
+  const double t0 = tol * root[2 * t], t1 = tol * root[2 * t + 1];
   int need = 0;
-  const double tol2 = tol * tol, lo2 = fmax(floor2, 0.0);
+  const double lo2 = fmax(floor2, 0.0);
 #pragma unroll
   for (int i = 0; i < EigShape::HR; ++i) {
     const int r = EigShape::HR * rg + i;
-    const double dr = diag[r];
+    const double dr = diag[r], sr = root[r];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const double dc = h ? d1 : d0;
-      need |= (int)(r != 2 * t + h) & (int)(dr > lo2) & (int)(dc > lo2) & (int)(g[i][h] * g[i][h] > tol2 * (dr * dc));
+      const double dc = h ? d1 : d0, tc = h ? t1 : t0;
+      need |= (int)(r != 2 * t + h) & (int)(dr > lo2) & (int)(dc > lo2) & (int)(fabs(g[i][h]) > tc * sr);
       q[i][h] = r == 2 * t + h ? 1.0 : 0.0;
     }
   }
@@ -616,7 +634,7 @@ __global__ __launch_bounds__(EIG_NT) __attribute__((amdgpu_waves_per_eu(1, 2))) 
     }
   const double floor2 = row_floor2(a, *a.fro2);
   double d0, d1;
-  const int need = oe_start(g, v, d0, d1, diag, a.tol, floor2);
+  const int need = oe_start(L, g, v, d0, d1, diag, a.tol, floor2);
   if (!__syncthreads_or(need)) {
     if (tid == 0) *skip = 1;
     return;
@@ -781,7 +799,7 @@ __global__ __launch_bounds__(EIG_NT) __attribute__((amdgpu_waves_per_eu(1, 2))) 
     for (int i = 0; i < EigShape::HR; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h) g[i][h] = Gs[EigShape::HR * rg + i][2 * t + h];
-    const int need = oe_start(g, v, d0, d1, diag, a.tol, floor2);
+    const int need = oe_start(L, g, v, d0, d1, diag, a.tol, floor2);
     if (!__syncthreads_or(need)) {
       conv = 1;
       break;
@@ -891,7 +909,7 @@ __device__ __forceinline__ void jacobi_tiny_rows(const SvdMat &a, int max_sweeps
     r.b = be;
     r.g = ga;
     static_for<0, 8>([&](auto st) { r.template stage<st, false>(floor2); });
-    const bool act = al > floor2 && be > floor2 && ga * ga > tol2 * (al * be);
+    const bool act = al > floor2 && be > floor2 && r.coupled(tol2);
     const double c = act ? r.c : idle ? 0.0 : 1.0, s = act ? r.s : idle ? 1.0 : 0.0;
     rot |= act;
     static_for<0, NR>([&](auto u) {
