@@ -2237,45 +2237,51 @@ tna_status svd_plan_mat(int m, int n, int dtype, int batch_hint, SvdMat *a, int 
   return TNA_OK;
 }
 
+// [2048 ..) S pieces (QR_SPLIT x 32 x 32, at most 32 C), W2 (32 x C); betas (R), scalars of the per-column
+// panels (R), then the pieces of W (QR_SPLIT x 32 x C)
+static size_t qws_doubles(const SvdMat &a) {
+  return 2048 + 64 * (size_t)a.C + 2 * (size_t)a.R + QR_SPLIT * 32 * (size_t)a.C;
+}
 size_t svd_work_doubles(const SvdMat &a) {
   const size_t npairs = a.nb / 2;
   return (size_t)a.R * a.C + (size_t)a.R * a.R + npairs * a.ksplit * 4096 + npairs * 4096 + a.R + 8 +
-         (a.precond ? (size_t)a.R * a.R + 2048 + 64 * (size_t)a.C + 2 * (size_t)a.R + QR_SPLIT * 32 * (size_t)a.C : 0);
+         (a.precond ? (size_t)a.R * a.R + qws_doubles(a) : 0);
 }
 size_t svd_work_ints(const SvdMat &a) { return (size_t)a.nb / 2 + a.R + 4 + (a.precond ? 2 * (size_t)a.C : 0); }
 
+// gram, qt and qws (the Grams of a small group after its QR start) are accessed in 16-byte pairs: they come
+// first, from an aligned address on, each an even number of doubles.  The double that may cost comes out of
+// fro2's eight, of which two are used.
 void svd_bind_work(SvdMat *a, double *dw, int *iw) {
   const size_t npairs = a->nb / 2;
-  a->bw = dw;
-  dw += (size_t)a->R * a->C;
-  a->jt = dw;
-  dw += (size_t)a->R * a->R;
+  dw += (reinterpret_cast<uintptr_t>(dw) / sizeof(double)) & 1;
   a->gram = dw;
   dw += npairs * a->ksplit * 4096;
   a->qt = dw;
   dw += npairs * 4096;
+  if (a->precond) {
+    a->qws = dw;
+    dw += qws_doubles(*a);
+    a->qv = dw;
+    dw += (size_t)a->R * a->R;
+  } else {
+    a->qv = a->qws = nullptr;
+  }
+  a->bw = dw;
+  dw += (size_t)a->R * a->C;
+  a->jt = dw;
+  dw += (size_t)a->R * a->R;
   a->sig = dw;
   dw += a->R;
   a->fro2 = dw;
-  dw += 8;
   a->skip = iw;
   iw += npairs;
   a->perm = iw;
   iw += a->R;
   a->ctr = iw;
   iw += 4;
-  if (a->precond) {
-    a->qv = dw;
-    dw += (size_t)a->R * a->R;
-    a->qws = dw;  // [2048 ..) S pieces (QR_SPLIT x 32 x 32, at most 32 C), W2 (32 x C); betas (R), scalars of
-                  // the per-column panels (R), then the pieces of W (QR_SPLIT x 32 x C)
-    a->cperm = iw;
-    iw += a->C;
-    a->pinv = iw;
-  } else {
-    a->qv = a->qws = nullptr;
-    a->cperm = a->pinv = nullptr;
-  }
+  a->cperm = a->precond ? iw : nullptr;
+  a->pinv = a->precond ? iw + a->C : nullptr;
 }
 
 // The descriptors through one of SvdGroup::NSTAGE pinned buffers in turn: a buffer is written again only
@@ -2510,7 +2516,7 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
         a.nb += a.nb & 1;
       }
       const int pairs = a.nb / 2;
-      const size_t wy = 2048 + 64 * (size_t)a.C + 2 * (size_t)a.R + QR_SPLIT * 32 * (size_t)a.C;
+      const size_t wy = qws_doubles(a);
       int ks = std::min(ceil_div(1024, (int64_t)pairs * nm), ceil_div(a.C, 256));
       if ((int64_t)pairs * nm * ks < 256) {
         ks = std::min(ceil_div(256, (int64_t)pairs * nm), ceil_div(a.C, 64));
