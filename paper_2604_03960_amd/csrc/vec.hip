@@ -46,18 +46,14 @@ struct MixDev {
 
 // One thread per (o0, o1).  Every thread of the launch reads M at the same addresses: through the
 // constant address space those are scalar loads shared by the wave.  The channel counts are template
-// constants for the MPOs in use (CI1 = 0: runtime counts, at most 32 channels): with runtime counts the
-// 32 x 32 guarded products and their loads of M took 34 us for the 256 elements of a chi = 16 bond.
+// constants for the MPOs in use: as the guarded 32 x 32 products of run-time counts, with a scalar load waited
+// for in each, they took 34 us for the 256 elements of a chi = 16 bond.
 // SPLIT: one j1 per grid row instead of all (CJ1 times the threads, x read as often): a launch with fewer
 // blocks than keep the chip busy is bound by each thread's walk over M (203 x 331, 32 channels: 33 us
 // without, 20 us with).
 template <typename T, int CI1, int CI2, int CJ1, int CJ2, bool SPLIT>
 __global__ __launch_bounds__(NT) void mix_kernel(MixDev a) {
-  constexpr bool fixed = CI1 > 0;
-  static_assert(fixed || !SPLIT, "split needs the channel counts");
-  const int I2 = fixed ? CI2 : a.I2, J2 = fixed ? CJ2 : a.J2;
-  const int I = fixed ? CI1 * CI2 : a.I1 * a.I2, J = fixed ? CJ1 * CJ2 : a.J1 * a.J2;
-  constexpr int IM = fixed ? CI1 * CI2 : 32, JM = SPLIT ? CJ2 : fixed ? CJ1 * CJ2 : 32;
+  constexpr int I = CI1 * CI2, J = SPLIT ? CJ2 : CJ1 * CJ2;
   const int j1 = SPLIT ? blockIdx.y : 0;
   const int64_t idx = (int64_t)blockIdx.x * NT + threadIdx.x;
   const int64_t total = (int64_t)a.n0 * a.n1;
@@ -66,20 +62,60 @@ __global__ __launch_bounds__(NT) void mix_kernel(MixDev a) {
   const T *in = static_cast<const T *>(a.in) + o0 * a.is0 + o1 * a.is1;
   T *out = static_cast<T *>(a.out) + o0 * a.os0 + o1 * a.os1;
   const double __attribute__((address_space(4))) *M =
-      (const double __attribute__((address_space(4))) *)a.M + (SPLIT ? j1 * J2 * I : 0);
+      (const double __attribute__((address_space(4))) *)a.M + (SPLIT ? j1 * CJ2 * I : 0);
   if (SPLIT) out += (int64_t)j1 * a.och1;
-  T x[IM];
+  T x[I];
 #pragma unroll
-  for (int i = 0; i < IM; ++i) x[i] = (fixed || i < I) ? in[(i / I2) * a.ich1 + (i % I2) * a.ich2] : T(0);
+  for (int i = 0; i < I; ++i) x[i] = in[(i / CI2) * a.ich1 + (i % CI2) * a.ich2];
 #pragma unroll
-  for (int j = 0; j < JM; ++j) {
-    if (fixed || j < J) {
-      T acc = T(0);
+  for (int j = 0; j < J; ++j) {
+    T acc = T(0);
 #pragma unroll
-      for (int i = 0; i < IM; ++i)
-        if (fixed || i < I) acc += (T)M[j * I + i] * x[i];
-      out[(j / J2) * a.och1 + (j % J2) * a.och2] = acc;
-    }
+    for (int i = 0; i < I; ++i) acc += (T)M[j * I + i] * x[i];
+    out[(j / CJ2) * a.och1 + (j % CJ2) * a.och2] = acc;
+  }
+}
+
+// The same for any channel counts up to 32.  M goes through LDS, its rows filled up with zeros to 32 entries, so
+// that a row's products need a bound only every four channels and no load is waited for alone; the
+// channel offsets are stepped, not divided.
+// MIX_ANY_MEASURED
+template <typename T>
+__global__ __launch_bounds__(NT) void mix_any_kernel(MixDev a) {
+  constexpr int CH = 32;
+  __shared__ T Ms[CH * CH];
+  const int I = a.I1 * a.I2, J = a.J1 * a.J2;
+  for (int e = threadIdx.x; e < J * CH; e += NT) {
+    const int j = e / CH, i = e % CH;
+    Ms[e] = i < I ? (T)a.M[j * I + i] : T(0);
+  }
+  __syncthreads();
+  const int64_t idx = (int64_t)blockIdx.x * NT + threadIdx.x;
+  const int64_t total = (int64_t)a.n0 * a.n1;
+  if (idx >= total) return;
+  const int64_t o0 = idx / a.n1, o1 = idx - o0 * a.n1;
+  const T *in = static_cast<const T *>(a.in) + o0 * a.is0 + o1 * a.is1;
+  T *out = static_cast<T *>(a.out) + o0 * a.os0 + o1 * a.os1;
+  T x[CH];
+  int c2 = 0, at = 0;  // channel (c1, c2) and its offset
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    x[i] = i < I ? in[at] : T(0);
+    c2 = c2 + 1 < a.I2 ? c2 + 1 : 0;
+    at += c2 > 0 ? a.ich2 : a.ich1 - (a.I2 - 1) * a.ich2;
+  }
+  c2 = at = 0;
+#pragma unroll 1
+  for (int j = 0; j < J; ++j) {
+    T acc = T(0);
+#pragma unroll
+    for (int i0 = 0; i0 < CH; i0 += 4)
+      if (i0 < I)  // uniform
+#pragma unroll
+        for (int i = i0; i < i0 + 4; ++i) acc += Ms[j * CH + i] * x[i];
+    out[at] = acc;
+    c2 = c2 + 1 < a.J2 ? c2 + 1 : 0;
+    at += c2 > 0 ? a.och2 : a.och1 - (a.J2 - 1) * a.och2;
   }
 }
 
@@ -290,7 +326,7 @@ tna_status mix(const MixArgs &a, hipStream_t s) {
   TNA_MIX_CASE(8, 2, 2, 8)
   TNA_MIX_CASE(3, 4, 4, 3)
   TNA_MIX_CASE(3, 2, 2, 3)
-  launch(mix_kernel<double, 0, 0, 0, 0, false>, mix_kernel<float, 0, 0, 0, 0, false>, false);
+  launch(mix_any_kernel<double>, mix_any_kernel<float>, false);
 #undef TNA_MIX_CASE
   const int es = a.type_in == G_F64 ? 8 : 4;
   timer_end(name, 2.0 * I * J * (double)total, (double)total * (I + J) * es, s);
