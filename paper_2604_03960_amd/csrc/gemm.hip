@@ -445,10 +445,12 @@ tna_status launch_tile(const GemmArgs &a, const GemmDev &d, hipStream_t s) {
 
 // Tile choice: the 128 x 128 tile when the grid still has >= 2 waves of workgroups on 256 CUs, else
 // 64 x 64, and 32 x 32 (each operand read twice as often, four times the workgroups) where that would
-// leave the chip with less than two 64 x 64 workgroups per CU.  H_eff with the 64 x 64 and the 32 x 32 tile
+// leave part of the chip's two 64 x 64 workgroups per CU idle.  H_eff with the 64 x 64 and the 32 x 32 tile
 // below the line: J1-J2 96 x 96 60.0 / 35.8 us, 203 x 331 200 / 126 us, 400 x 380 254 / 216 us, 512 x 512
-// 378 / 359 us; at 640 x 600, where few products are left below it, 651 / 632 us.
-constexpr int GEMM_MID_TILES = 512;
+// 378 / 359 us (256 tiles in the last product), 640 x 600 (400 tiles) 651 / 632 us.  Above it, 64 x 64 / 32 x 32:
+// TFIM 640 x 768 (480 tiles) 324 / 343 us, 466 x 1050 (510 tiles) 360 / 433 us, in FP32 220 / 248 and 242 / 282 us;
+// Heisenberg 660 x 700 (462 tiles) 550 / 580 us.
+constexpr int GEMM_MID_TILES = 440;
 template <typename T, typename TA, typename TB, typename TC>
 tna_status launch_types(const GemmArgs &a, const GemmDev &d, hipStream_t s) {
   int64_t big = (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
