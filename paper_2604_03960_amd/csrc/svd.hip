@@ -275,9 +275,11 @@ __global__ __launch_bounds__(256) void gram_kernel(const SvdMat *mats, int step)
 // more sweeps (a numerically low-rank matrix can need twice as many), so the floor is
 // used there only when the factor built from the rows leaves scaled by the singular
 // values (rows_scaled): then nothing needs their directions.  An input that carries
-// noise of noise_rel |A|_F (rows_scaled only) raises the floor to that level.
+// noise of noise_rel |A|_F (rows_scaled only) raises the floor to that level.  Without it rows keep
+// their place down to 1e-150 |A|_F (and 1e-150): below, the Gram's entries lose their digits to underflow and the
+// relative test could not settle.
 __device__ inline double row_floor2(const SvdMat &a, double fro2) {
-  if (a.precond && !a.rows_scaled) return 0.0;
+  if (a.precond && !a.rows_scaled) return 1e-300 * fmax(fro2, 1.0);
   const double f = fmax(0.1 * EPS53 * (double)a.C, a.rows_scaled ? a.noise_rel : 0.0);
   return f * f * fro2;
 }
@@ -1172,6 +1174,10 @@ __global__ __launch_bounds__(256) void colnorm_kernel(const SvdMat *mats) {
   }
 }
 
+// A NaN compares with nothing: it would move the entries that fill a sort up to a power of two, whose
+// indices lie past the matrix, among the real ones.
+__device__ inline double sort_key(double v) { return v == v ? v : __builtin_huge_val(); }
+
 // one block per matrix: cperm <- columns by decreasing norm (bitonic sort of (norm, index))
 __global__ __launch_bounds__(1024) void colsort_kernel(const SvdMat *mats) {
   __shared__ double key[4096];
@@ -1181,7 +1187,7 @@ __global__ __launch_bounds__(1024) void colsort_kernel(const SvdMat *mats) {
   int P = 1;
   while (P < a.C) P <<= 1;
   for (int i = threadIdx.x; i < P; i += 1024) {
-    key[i] = i < a.C ? a.qws[2048 + i] : -1.0;
+    key[i] = i < a.C ? sort_key(a.qws[2048 + i]) : -1.0;
     idx[i] = i;
   }
   __syncthreads();
@@ -1234,11 +1240,31 @@ __global__ __launch_bounds__(256) void permute_load_kernel(const SvdMat *mats) {
   }
 }
 
+// The scalars of the reflector that takes a column x, |x|^2 = t, x_0 = xn, to (alpha, 0, ...): v = x - alpha e_0 is
+// stored times the power of two sc that brings |x| into [1, 2), and beta = 2 / |sc v|^2, so that no norm squared
+// twice is formed.  A column below 1e-150, whose squares soon lose their digits, has no reflector (beta = sc = 0):
+// its entries under the diagonal count as zero.
+constexpr double QR_NULL2 = 1e-300;
+struct Reflector {
+  double alpha, beta, v0, sc;
+  __device__ __forceinline__ Reflector(double t, double xn) {
+    const double nx = sqrt(t);
+    const bool null = !(t > QR_NULL2);
+    alpha = xn >= 0.0 ? -nx : nx;
+    v0 = xn - alpha;
+    sc = null ? 0.0 : __hiloint2double(0x7fe00000 - (__double2hiint(nx) & 0x7ff00000), 0);
+    const double ns = nx * sc;
+    beta = null ? 0.0 : 1.0 / (ns * (ns + fabs(xn * sc)));
+  }
+  // coefficient of v in a later column whose product with v is y
+  __device__ __forceinline__ double coef(double y) const { return beta * (y * sc) * sc; }
+};
+
 // Householder QR of the panel of columns k0 .. k0+31 of B (rows k0..), one column after the
 // other: x = B[k:R, k], alpha = -sign(x_0) |x|, v = x - alpha e_0 (stored as row k of qv),
-// beta = 2 / v^T v = 1 / (|x| (|x| + |x_0|)) (stored in qws); B[k:, k] <- (alpha, 0, ...); then
-// every later column c of the panel: B[k:, c] -= beta (v^T B[k:, c]) v.  The trailing columns are
-// updated afterwards with the block reflector (qr_block_apply).
+// beta = 2 / v^T v = 1 / (|x| (|x| + |x_0|)) (stored in qws), both scaled as Reflector says;
+// B[k:, k] <- (alpha, 0, ...); then every later column c of the panel: B[k:, c] -= beta (v^T B[k:, c]) v.
+// The trailing columns are updated afterwards with the block reflector (qr_block_apply).
 //
 // Spread over row chunks of QC_ROWS rows, one launch per column: launch k applies reflector k to
 // the panel columns right of it and forms the chunk partials that reflector k+1 needs
@@ -1270,13 +1296,14 @@ __global__ __launch_bounds__(256) void qr_col_kernel(const SvdMat *mats, int k0,
     for (int64_t e = (int64_t)blk * 256 + tid; e < tot; e += (int64_t)G * 256) a.qv[(int64_t)k0 * R + e] = 0.0;
     if (blk == 0 && tid == 0) a.fro2[1] = 0.0;  // trailing-row maximum of this panel (qr_tail_kernel)
   }
-  double alpha = 0.0, beta = 0.0, vk = 0.0, x0 = 0.0, wc = 0.0;
+  double alpha = 0.0, beta = 0.0, vk = 0.0, x0 = 0.0, vsc = 0.0, wc = 0.0;
   const int kc = k - k0;
   if (!start) {
     alpha = sc[0];
     beta = sc[1];
     vk = sc[2];
     x0 = sc[3];
+    vsc = sc[36];
     wc = (cl > kc && colok) ? sc[4 + cl] : 0.0;
   }
   double val[QC_ROWS / 8];
@@ -1292,7 +1319,7 @@ __global__ __launch_bounds__(256) void qr_col_kernel(const SvdMat *mats, int k0,
           x -= wc * vi;
         } else {
           x = (i == k) ? (beta != 0.0 ? alpha : x0) : 0.0;
-          a.qv[(int64_t)k * R + i] = vi;
+          a.qv[(int64_t)k * R + i] = vi * vsc;
         }
         B[(int64_t)i * C + c] = x;
       }
@@ -1333,18 +1360,16 @@ __global__ __launch_bounds__(256) void qr_col_kernel(const SvdMat *mats, int k0,
   }
   __syncthreads();
   if (tid < 32) {
-    const double nx = sqrt(red[0][nc]);
     const double xn = B[(int64_t)nk * C + nk];
-    const double al = xn >= 0.0 ? -nx : nx;
-    const double be = nx > 0.0 ? 1.0 / (nx * (nx + fabs(xn))) : 0.0;
-    const double v0 = xn - al;
-    if (cl > nc && colok) sc[4 + cl] = be * (red[0][cl] + v0 * B[(int64_t)nk * C + c]);
+    const Reflector h(red[0][nc], xn);
+    if (cl > nc && colok) sc[4 + cl] = h.coef(red[0][cl] + h.v0 * B[(int64_t)nk * C + c]);
     if (cl == 0) {
-      sc[0] = al;
-      sc[1] = be;
-      sc[2] = v0;
+      sc[0] = h.alpha;
+      sc[1] = h.beta;
+      sc[2] = h.v0;
       sc[3] = xn;
-      betas[nk] = be;
+      sc[36] = h.sc;
+      betas[nk] = h.beta;
       a.ctr[2] = 0;
     }
   }
@@ -1366,7 +1391,7 @@ __global__ __launch_bounds__(256) void qr_panel_coop_kernel(const SvdMat *mats, 
   __shared__ double pl[QC_GROUP * 64];
   __shared__ double red[8][33];
   __shared__ double rowv[32];
-  __shared__ double scs[4 + 32];
+  __shared__ double scs[4 + 32 + 1];
   cooperative_groups::grid_group grid = cooperative_groups::this_grid();
   const SvdMat &a = mats[blockIdx.z];
   const int R = a.R, C = a.C;
@@ -1395,7 +1420,7 @@ __global__ __launch_bounds__(256) void qr_panel_coop_kernel(const SvdMat *mats, 
     const int k = k0 - 1 + it;
     if (mine && it > 0 && k < kend) {  // apply reflector k to the chunk
       const int kc = k - k0;
-      const double alpha = scs[0], beta = scs[1], vk = scs[2], x0 = scs[3];
+      const double alpha = scs[0], beta = scs[1], vk = scs[2], x0 = scs[3], vsc = scs[36];
       const double wc = (cl > kc && colok) ? scs[4 + cl] : 0.0;
 #pragma unroll
       for (int m = 0; m < QC_ROWS / 8; ++m) {
@@ -1408,7 +1433,7 @@ __global__ __launch_bounds__(256) void qr_panel_coop_kernel(const SvdMat *mats, 
             x -= wc * vi;
           } else {
             x = (i == k) ? (beta != 0.0 ? alpha : x0) : 0.0;
-            a.qv[(int64_t)k * R + i] = vi;
+            a.qv[(int64_t)k * R + i] = vi * vsc;
           }
         }
         val[m] = x;
@@ -1466,18 +1491,16 @@ __global__ __launch_bounds__(256) void qr_panel_coop_kernel(const SvdMat *mats, 
       }
       __syncthreads();
       if (tid < 32) {
-        const double nx = sqrt(red[0][nc]);
         const double xn = rowv[nc];
-        const double al = xn >= 0.0 ? -nx : nx;
-        const double be = nx > 0.0 ? 1.0 / (nx * (nx + fabs(xn))) : 0.0;
-        const double v0 = xn - al;
-        if (cl > nc && colok) scs[4 + cl] = be * (red[0][cl] + v0 * rowv[cl]);
+        const Reflector h(red[0][nc], xn);
+        if (cl > nc && colok) scs[4 + cl] = h.coef(red[0][cl] + h.v0 * rowv[cl]);
         if (cl == 0) {
-          scs[0] = al;
-          scs[1] = be;
-          scs[2] = v0;
+          scs[0] = h.alpha;
+          scs[1] = h.beta;
+          scs[2] = h.v0;
           scs[3] = xn;
-          if (blk == 0) betas[nk] = be;
+          scs[36] = h.sc;
+          if (blk == 0) betas[nk] = h.beta;
         }
       }
       __syncthreads();
@@ -1511,7 +1534,7 @@ template <int NT>
 __global__ __launch_bounds__(NT) void qr_panel_wg_kernel(const SvdMat *mats, int k0) {
   __shared__ double red[NT / 64][4][33];
   __shared__ double rowk[32], ws[32];
-  __shared__ double alphas[32], sc_vk;
+  __shared__ double alphas[32], vscs[32], sc_vk;
   const SvdMat &a = mats[blockIdx.z];
   if (!a.active || !a.precond || k0 >= a.Ra || k0 >= a.R) return;
   const int R = a.R, C = a.C, K = R - k0;
@@ -1553,14 +1576,14 @@ __global__ __launch_bounds__(NT) void qr_panel_wg_kernel(const SvdMat *mats, int
         double t = 0.0;
         for (int w = 0; w < nw; ++w) t += red[w][2 * half][c] + red[w][2 * half + 1][c];
         t += __shfl_xor(t, 32, 64);
-        const double nx = sqrt(__shfl(t, kc, 64)), xn = rowk[kc];
-        const double al = xn >= 0.0 ? -nx : nx;
-        const double be = nx > 0.0 ? 1.0 / (nx * (nx + fabs(xn))) : 0.0;
-        if (lane < 32) ws[c] = c > kc ? be * (t - al * rowk[c]) : 0.0;
+        const double xn = rowk[kc];
+        const Reflector h(__shfl(t, kc, 64), xn);
+        if (lane < 32) ws[c] = c > kc ? h.coef(t - h.alpha * rowk[c]) : 0.0;
         if (lane == 0) {
-          alphas[kc] = be != 0.0 ? al : xn;
-          sc_vk = xn - al;
-          betas[kc] = be;
+          alphas[kc] = h.beta != 0.0 ? h.alpha : xn;
+          vscs[kc] = h.sc;
+          sc_vk = h.v0;
+          betas[kc] = h.beta;
         }
       }
       __syncthreads();
@@ -1586,7 +1609,7 @@ __global__ __launch_bounds__(NT) void qr_panel_wg_kernel(const SvdMat *mats, int
       if (i < K && c < ncol) {
         const double v = val[m][h];
         B[(int64_t)i * C + c] = i < c ? v : i == c ? alphas[c] : 0.0;
-        if (c < nref) qv[(int64_t)c * R + k0 + i] = i < c ? 0.0 : v;
+        if (c < nref) qv[(int64_t)c * R + k0 + i] = i < c ? 0.0 : v * vscs[c];
       }
     }
   }
@@ -1802,7 +1825,7 @@ __global__ __launch_bounds__(1024) void sort_kernel(const SvdMat *mats) {
   int P = 1;
   while (P < a.R) P <<= 1;
   for (int i = threadIdx.x; i < P; i += 1024) {
-    key[i] = i < a.R ? a.sig[i] : -1.0;
+    key[i] = i < a.R ? sort_key(a.sig[i]) : -1.0;
     idx[i] = i;
   }
   __syncthreads();
@@ -1824,8 +1847,10 @@ __global__ __launch_bounds__(1024) void sort_kernel(const SvdMat *mats) {
   }
   for (int i = threadIdx.x; i < a.R; i += 1024) {
     a.perm[i] = idx[i];
+    key[i] = a.sig[idx[i]];
     a.S[i] = key[i];
   }
+  __syncthreads();
   // Z = sum S^2 and S_vN = -sum p ln p (p = S^2 / Z), fixed-order block sums
   double z2 = 0.0;
   for (int i = threadIdx.x; i < a.R; i += 1024) z2 += key[i] * key[i];
@@ -1946,10 +1971,9 @@ __global__ __launch_bounds__(256) void trunc_kernel(const SvdMat *mats) {
 
 // Kept values at or below this are null: at the rounding level of sigma_0 or under the
 // Jacobi row floor (whose rows were never orthogonalised against the others).  With the
-// QR start and no floor (rows_scaled off) every row with a nonzero norm was
-// orthogonalised, so only rows whose squares underflow count as null there.
+// QR start (rows_scaled off) that floor is where squares are about to underflow.
 __device__ inline double null_threshold(const SvdMat &a) {
-  if (a.precond && !a.rows_scaled) return 1e-150 * a.S[0];
+  if (a.precond && !a.rows_scaled) return 1e-150 * fmax(sqrt(*a.fro2), 1.0);
   const double C = (double)(a.m > a.n ? a.m : a.n);
   return EPS53 * C * fmax(a.S[0], 0.1 * sqrt(*a.fro2));
 }
@@ -2074,7 +2098,8 @@ __device__ void gauge_one(const SvdMat &a, int j, double *bv, int *bi, double *s
     int ii = bi[0];
     for (int w = 1; w < 4; ++w)
       if (bv[w] > b || (bv[w] == b && bi[w] < ii)) { b = bv[w]; ii = bi[w]; }
-    *sgn = ((double)U[(int64_t)ii * a.k + j] < 0.0) ? -1.0 : 1.0;
+    // (a column without a comparable entry has no largest one)
+    *sgn = (ii < a.m && (double)U[(int64_t)ii * a.k + j] < 0.0) ? -1.0 : 1.0;
   }
   __syncthreads();
   const double nk = a.spec[4];
