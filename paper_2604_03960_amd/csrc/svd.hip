@@ -2017,7 +2017,9 @@ __global__ __launch_bounds__(256) void write_kernel(const SvdMat *mats) {
 }
 
 // Gram-Schmidt completion of kept null vectors with unit vectors e_0, e_1, ...
-// (Vt rows when rows of A were orthogonalised, U columns otherwise); one block per matrix
+// (Vt rows when rows of A were orthogonalised, U columns otherwise); one block per matrix.  A unit vector is taken
+// when more than half of its length is left.  A complement of few dimensions may hold no such one, but always one
+// with more than 1 / sqrt(L): when none is left the search starts again with half of that.
 template <typename T>
 __device__ void complete_one(const SvdMat &a, double *vec, double *red, int *ok) {
   const double thr = null_threshold(a);
@@ -2027,10 +2029,17 @@ __device__ void complete_one(const SvdMat &a, double *vec, double *red, int *ok)
   if (a.trans) { base = static_cast<T *>(a.U); es = a.k; vs = 1; }
   else { base = static_cast<T *>(a.Vt); es = 1; vs = a.n; }
   const int tid = threadIdx.x;
-  int e = 0;
+  int e = 0, again = 0;
+  double least = 0.5;
   for (int j = 0; j < a.k; ++j) {
     if (a.S[j] > thr && a.S[j] > 0.0) continue;
-    for (; e < L; ++e) {
+    for (;; ++e) {
+      if (e == L) {
+        if (again) break;
+        again = 1;
+        least = 0.5 / sqrt((double)L);
+        e = 0;
+      }
       for (int i = tid; i < L; i += 256) vec[i] = (i == e) ? 1.0 : 0.0;
       __syncthreads();
       for (int pass = 0; pass < 2; ++pass)
@@ -2046,7 +2055,7 @@ __device__ void complete_one(const SvdMat &a, double *vec, double *red, int *ok)
       double nr = 0.0;
       for (int i = tid; i < L; i += 256) nr += vec[i] * vec[i];
       nr = sqrt(bsum256(nr, red));
-      if (tid == 0) *ok = nr > 0.5;
+      if (tid == 0) *ok = nr > least;
       __syncthreads();
       const int good = *ok;
       __syncthreads();
