@@ -275,11 +275,12 @@ __global__ __launch_bounds__(256) void gram_kernel(const SvdMat *mats, int step)
 // more sweeps (a numerically low-rank matrix can need twice as many), so the floor is
 // used there only when the factor built from the rows leaves scaled by the singular
 // values (rows_scaled): then nothing needs their directions.  An input that carries
-// noise of noise_rel |A|_F (rows_scaled only) raises the floor to that level.  Without it rows keep
-// their place down to 1e-150 |A|_F (and 1e-150): below, the Gram's entries lose their digits to underflow and the
-// relative test could not settle.
+// noise of noise_rel |A|_F (rows_scaled only) raises the floor to that level.  Otherwise rows after the QR start
+// keep their place down to 1e-77 |A|_F: rows at one level that outnumber their columns (what is left of equal
+// rows) have to shrink by a rounding a sweep until they are out of the test, from 1e-77 to the end of the range in
+// more sweeps than the cap.  Below 1e-150 the Gram's entries lose their digits to underflow.
 __device__ inline double row_floor2(const SvdMat &a, double fro2) {
-  if (a.precond && !a.rows_scaled) return 1e-300 * fmax(fro2, 1.0);
+  if (a.precond && !a.rows_scaled) return fmax(1e-154 * fro2, 1e-300);
   const double f = fmax(0.1 * EPS53 * (double)a.C, a.rows_scaled ? a.noise_rel : 0.0);
   return f * f * fro2;
 }
@@ -1971,9 +1972,9 @@ __global__ __launch_bounds__(256) void trunc_kernel(const SvdMat *mats) {
 
 // Kept values at or below this are null: at the rounding level of sigma_0 or under the
 // Jacobi row floor (whose rows were never orthogonalised against the others).  With the
-// QR start (rows_scaled off) that floor is where squares are about to underflow.
+// QR start (rows_scaled off) that floor is far lower.
 __device__ inline double null_threshold(const SvdMat &a) {
-  if (a.precond && !a.rows_scaled) return 1e-150 * fmax(sqrt(*a.fro2), 1.0);
+  if (a.precond && !a.rows_scaled) return sqrt(row_floor2(a, *a.fro2));
   const double C = (double)(a.m > a.n ? a.m : a.n);
   return EPS53 * C * fmax(a.S[0], 0.1 * sqrt(*a.fro2));
 }

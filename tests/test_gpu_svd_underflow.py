@@ -41,3 +41,9 @@ def test_equal_columns_and_rank_one(m, n):
     _check(np.tile(x, (1, n)), 3)
     _check(np.tile(y, (m, 1)), 3)
     _check(x @ y, 3)
+
+
+def test_equal_rows_left_far_below_the_norm():
+    """300 equal entries in each of 257 columns: the QR start leaves some 200 equal rows at 1e-92 of the norm with 43
+    columns between them."""
+    _check(np.tile(synth.random_matrix(300, 257, 557)[:, :1], (1, 257)), 128)
