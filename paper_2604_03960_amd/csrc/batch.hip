@@ -6,6 +6,7 @@
 // launch sequence of one iteration does not change from one iteration to the
 // next and is captured once per sweep step as a HIP graph.
 #include "dev_reduce.h"
+#include "dev_tile.h"
 #include "internal.h"
 
 namespace tna {
@@ -509,8 +510,6 @@ __global__ __launch_bounds__(NT) void lz_ritz1_kernel(const LzProb *probs) {
 // alpha_j, beta_j^2 of every iteration go to rec[2j], rec[2j+1].  A
 // workgroup stops at kmax, after `iters` iterations, or when beta_j is
 // negligible.
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int NTS = 512;  // threads of the single-workgroup Lanczos (8 waves)
 
 // x / d for 0 <= x < 2^16 and 1 <= d < 2^16 with one multiply-high by ceil(2^32 / d) (exact in
@@ -522,28 +521,13 @@ struct FastDiv {
   __device__ int div(int x) const { return d > 1 ? (int)__umulhi((unsigned)x, m) : x; }
 };
 
-// 16 x 16 x 4 MFMA step and result layout per operand type.  Operands: A[i][k] in lane i + 16k,
-// B[k][j] in lane j + 16k.  Result register r of lane group lk = lane / 16 holds row 4r + lk
-// (f64) or 4lk + r (f32), column lane % 16.
-template <class T> struct Mf;
-template <> struct Mf<double> {
-  typedef v4d acc;
-  __device__ static acc step(double a, double b, acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  __device__ static int row(int lk, int r) { return 4 * r + lk; }
-};
-template <> struct Mf<float> {
-  typedef v4f acc;
-  __device__ static acc step(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  __device__ static int row(int lk, int r) { return 4 * lk + r; }
-};
-
 // One 16 x 16 output tile, C(i, j) = sum_{kb <= k < ke} A(i, k) B(k, j).  Rows and columns past
 // the matrix edge read the last valid row/column (their results are discarded by the caller), so
 // only a final partial k-step needs a guard.  The operands of four k-steps are read together and
 // fed to two independent accumulator chains.
 template <class T, class FA, class FB>
-__device__ inline typename Mf<T>::acc tile_mfma(int kb, int ke, int ia, int jb, int lk, FA a_at, FB b_at) {
-  typedef typename Mf<T>::acc A4;
+__device__ inline typename Mma<T>::acc tile_mfma(int kb, int ke, int ia, int jb, int lk, FA a_at, FB b_at) {
+  typedef typename Mma<T>::acc A4;
   A4 c0 = {0, 0, 0, 0}, c1 = {0, 0, 0, 0};
   const int k16 = kb + ((ke - kb) & ~15), k4 = kb + ((ke - kb) & ~3);
   int k0 = kb;
@@ -554,16 +538,16 @@ __device__ inline typename Mf<T>::acc tile_mfma(int kb, int ke, int ia, int jb, 
       av[u] = a_at(ia, k0 + 4 * u + lk);
       bv[u] = b_at(k0 + 4 * u + lk, jb);
     }
-    c0 = Mf<T>::step(av[0], bv[0], c0);
-    c1 = Mf<T>::step(av[1], bv[1], c1);
-    c0 = Mf<T>::step(av[2], bv[2], c0);
-    c1 = Mf<T>::step(av[3], bv[3], c1);
+    c0 = Mma<T>::step(av[0], bv[0], c0);
+    c1 = Mma<T>::step(av[1], bv[1], c1);
+    c0 = Mma<T>::step(av[2], bv[2], c0);
+    c1 = Mma<T>::step(av[3], bv[3], c1);
   }
-  for (; k0 < k4; k0 += 4) c0 = Mf<T>::step(a_at(ia, k0 + lk), b_at(k0 + lk, jb), c0);
+  for (; k0 < k4; k0 += 4) c0 = Mma<T>::step(a_at(ia, k0 + lk), b_at(k0 + lk, jb), c0);
   if (k0 < ke) {
     const bool in = k0 + lk < ke;
     const T av = in ? a_at(ia, k0 + lk) : T(0), bv = in ? b_at(k0 + lk, jb) : T(0);
-    c1 = Mf<T>::step(av, bv, c1);
+    c1 = Mma<T>::step(av, bv, c1);
   }
   return c0 + c1;
 }
@@ -575,7 +559,7 @@ __device__ inline typename Mf<T>::acc tile_mfma(int kb, int ke, int ia, int jb, 
 template <class T, class FA, class FB, class FC>
 __device__ inline void block_gemm(int M, int N, int K, FA a_at, FB b_at, FC c_put, T *part = nullptr,
                                   int part_cap = 0) {
-  typedef typename Mf<T>::acc A4;
+  typedef typename Mma<T>::acc A4;
   const int lane = threadIdx.x & 63, nw = NTS / 64;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
@@ -595,7 +579,7 @@ __device__ inline void block_gemm(int M, int N, int K, FA a_at, FB b_at, FC c_pu
     if (have && !second)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = i0 + Mf<T>::row(lk, r);
+        const int i = i0 + Mma<T>::row(lk, r);
         if (i < M && jb < N) c_put(i, jb, acc[r] + part[(t * 64 + lane) * 4 + r]);
       }
     return;
@@ -606,7 +590,7 @@ __device__ inline void block_gemm(int M, int N, int K, FA a_at, FB b_at, FC c_pu
     const A4 acc = tile_mfma<T>(0, K, ia, jc, lk, a_at, b_at);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = i0 + Mf<T>::row(lk, r);
+      const int i = i0 + Mma<T>::row(lk, r);
       if (i < M && jb < N) c_put(i, jb, acc[r]);
     }
   }
@@ -616,7 +600,7 @@ __device__ inline void block_gemm(int M, int N, int K, FA a_at, FB b_at, FC c_pu
 // waves in turn.
 template <class T, class FA, class FB, class FC>
 __device__ inline void block_gemm_nb(int NB, int M, int N, int K, FA a_at, FB b_at, FC c_put) {
-  typedef typename Mf<T>::acc A4;
+  typedef typename Mma<T>::acc A4;
   const int lane = threadIdx.x & 63, nw = NTS / 64;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
@@ -628,7 +612,7 @@ __device__ inline void block_gemm_nb(int NB, int M, int N, int K, FA a_at, FB b_
     const A4 acc = tile_mfma<T>(0, K, ia, jc, lk, a_at, [&](int k, int j) { return b_at(b, k, j); });
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = i0 + Mf<T>::row(lk, r);
+      const int i = i0 + Mma<T>::row(lk, r);
       if (i < M && jb < N) c_put(b, i, jb, acc[r]);
     }
   }
@@ -708,23 +692,6 @@ template <> struct LzKeep<0> {};
 // (address space of device memory: loads of the basis need not wait for LDS)
 typedef const double2 __attribute__((address_space(1))) *LzBasis;
 
-// f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>): register arrays indexed by constants
-template <int B, int E, class F>
-__device__ __forceinline__ void lz_static_for(F &&f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    lz_static_for<B + 1, E>(f);
-  }
-}
-
-// the same, ended by the first f that returns false: one jump past the rest of the code
-template <int B, int E, class F>
-__device__ __forceinline__ void lz_static_while(F &&f) {
-  if constexpr (B < E) {
-    if (f(std::integral_constant<int, B>{})) lz_static_while<B + 1, E>(f);
-  }
-}
-
 __device__ inline double lane63(double v) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
                           __builtin_amdgcn_readlane(__double2loint(v), 63));
@@ -770,7 +737,7 @@ __device__ __forceinline__ void lz_small_body(const LzSmall &p, int iters, doubl
   const int n2 = n >> 1, uwave = __builtin_amdgcn_readfirstlane(wave);
   if constexpr (EL > 0) {
     // vectors 0..j as they are at the start of this launch, V_j as the first operand
-    lz_static_for<0, LzKeep<EL>::KR>([&](auto k) {
+    static_for<0, LzKeep<EL>::KR>([&](auto k) {
       const int i = uwave + NW * k;
       const LzBasis v = (LzBasis)(V + (int64_t)min(i, j) * n);
 #pragma unroll
@@ -852,7 +819,7 @@ __device__ __forceinline__ void lz_small_body(const LzSmall &p, int iters, doubl
             }
             return a0 + a1;
           };
-          lz_static_while<0, (KR + 1) / 2>([&](auto g) {  // two vectors at a time: their reductions overlap
+          static_while<0, (KR + 1) / 2>([&](auto g) {  // two vectors at a time: their reductions overlap
             constexpr int k0 = 2 * g, k1 = 2 * g + 1 < KR ? 2 * g + 1 : 2 * g;
             if (k0 >= kc) return false;
             double d0 = dot(keep.x[k0]), d1 = k1 > k0 ? dot(keep.x[k1]) : 0.0;
@@ -882,7 +849,7 @@ __device__ __forceinline__ void lz_small_body(const LzSmall &p, int iters, doubl
 #pragma unroll
         for (int u = 0; u < EL; ++u) sum[u] = double2{0.0, 0.0};
         double al = 0.0;  // <V_j, w> of the wave that holds V_j
-        lz_static_while<0, (KR + 1) / 2>([&](auto g) {
+        static_while<0, (KR + 1) / 2>([&](auto g) {
           constexpr int k0 = 2 * g, k1 = 2 * g + 1 < KR ? 2 * g + 1 : 2 * g;
           if (k0 >= kc) return false;
 #pragma unroll
@@ -954,7 +921,7 @@ __device__ __forceinline__ void lz_small_body(const LzSmall &p, int iters, doubl
       if (stop) break;
       __syncthreads();
       if (uwave == (j & (NW - 1)))
-        lz_static_for<0, KR>([&](auto k) {
+        static_for<0, KR>([&](auto k) {
           if (k == (j >> 3))
 #pragma unroll
             for (int u = 0; u < EL; ++u)

@@ -16,28 +16,13 @@
 #include <cstdio>
 #include <type_traits>
 
+#include "dev_tile.h"
 #include "internal.h"
 
 namespace tna {
 namespace {
 
 typedef double v2d __attribute__((ext_vector_type(2)));
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-template <typename T> struct Acc;
-template <> struct Acc<double> { typedef v4d type; };
-template <> struct Acc<float> { typedef v4f type; };
-
-__device__ inline v4d mfma16(double a, double b, v4d c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ inline v4f mfma16(float a, float b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-// row of result register r held by lane group lk (= lane / 16)
-__device__ inline int mfma_row(double, int lk, int r) { return 4 * r + lk; }
-__device__ inline int mfma_row(float, int lk, int r) { return 4 * lk + r; }
 
 struct GemmDev {
   int M, N, K, lda, ldb, ldc;
@@ -47,15 +32,6 @@ struct GemmDev {
   double alpha, beta;
   int64_t sA, sB, sC;
 };
-
-// f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>): register arrays indexed by constants
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
 
 // threads of the workgroup that owns a BM x BN tile, and its waves along M
 template <int BM> struct TileShape;
@@ -207,11 +183,11 @@ __device__ __forceinline__ void gemm_tile(gp<const TA> __restrict__ A, int lda, 
     }
   };
 
-  typename Acc<T>::type acc[TM][TN];
+  typename Mma<T>::acc acc[TM][TN];
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
-    for (int b = 0; b < TN; ++b) acc[a][b] = typename Acc<T>::type{0, 0, 0, 0};
+    for (int b = 0; b < TN; ++b) acc[a][b] = typename Mma<T>::acc{0, 0, 0, 0};
 
   const int nk = (K + BK - 1) / BK;
   // the products of the slab in LDS buffer buf
@@ -226,7 +202,7 @@ __device__ __forceinline__ void gemm_tile(gp<const TA> __restrict__ A, int lda, 
 #pragma unroll
       for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b) acc[a][b] = mfma16(av[a], bv[b], acc[a][b]);
+        for (int b = 0; b < TN; ++b) acc[a][b] = Mma<T>::step(av[a], bv[b], acc[a][b]);
     }
   };
   constexpr int PD = TileShape<BM>::PD;
@@ -342,7 +318,7 @@ __device__ __forceinline__ void gemm_tile(gp<const TA> __restrict__ A, int lda, 
     for (int b = 0; b < TN; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        int row = m0 + wr * WM + a * 16 + mfma_row(T(0), lk, r);
+        int row = m0 + wr * WM + a * 16 + Mma<T>::row(lk, r);
         int col = n0 + wc * WN + b * 16 + lr;
         if (row < M && col < N) {
           double v = alpha * (double)acc[a][b][r];

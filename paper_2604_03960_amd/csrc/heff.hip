@@ -15,26 +15,13 @@
 #include <algorithm>
 #include <cstdint>
 
+#include "dev_tile.h"
 #include "internal.h"
 
 namespace tna {
 namespace {
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int NT = 512;  // eight waves: their operand loads in flight hide each other's latency
-
-template <class T> struct Mma;
-template <> struct Mma<double> {
-  typedef v4d acc;
-  __device__ static acc step(double a, double b, acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  __device__ static int row(int lk, int r) { return 4 * r + lk; }
-};
-template <> struct Mma<float> {
-  typedef v4f acc;
-  __device__ static acc step(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  __device__ static int row(int lk, int r) { return 4 * lk + r; }
-};
 
 struct HeffSmall {
   int chl, chr, D, ac;

@@ -23,9 +23,9 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <type_traits>
 
 #include "dev_reduce.h"
+#include "dev_tile.h"
 #include "internal.h"
 
 namespace tna {
@@ -57,39 +57,13 @@ void DevBuf::release() {
 
 namespace {
 
-// Jacobi rotation zeroing the off-diagonal g of a symmetric 2 x 2 block [[a, g], [g, b]] (g != 0):
-// t = sign(b - a) 2 g / (|b - a| + sqrt((b - a)^2 + 4 g^2)), c = 1 / sqrt(1 + t^2), s = c t.  The
-// square roots and the quotient come from the hardware reciprocal and reciprocal-square-root
-// estimates refined by two Newton steps each (the relative error squares per step), which keeps
-// c^2 + s^2 = 1 to a few ulp while avoiding the long correctly rounded division and square-root
-// sequences.
-__device__ inline double rsqrt_nr(double x) {  // x > 0, finite
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(-(x * y), y, 1.0);
-    y = fma(0.5 * y, e, y);
-  }
-  return y;
-}
-__device__ inline double rcp_nr(double x) {  // x > 0, finite
-  double r = __builtin_amdgcn_rcp(x);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) r = fma(r, fma(-x, r, 1.0), r);
-  return r;
-}
-__device__ inline void jacobi_rot(double a, double b, double g, double &c, double &s) {
-  const double dl = b - a, q = fma(dl, dl, 4.0 * g * g);
-  const double t = (dl >= 0.0 ? 2.0 : -2.0) * g * rcp_nr(fabs(dl) + q * rsqrt_nr(q));
-  c = rsqrt_nr(fma(t, t, 1.0));
-  s = c * t;
-}
-// The same rotation by its half angle (cos 2u = |b - a| / sqrt((b - a)^2 + 4 g^2), c = sqrt((1 + cos 2u) / 2)),
-// two reciprocal square roots long, with tg = (s / c) g for the new diagonal (a - tg, b + tg).  Identity
-// (c, s, tg = 1, 0, 0) where a row is at or below floor2 or the coupling is at the rounding level.  It is a
-// chain of dependent operations cut into eight stages, so that a caller can issue other work between them;
-// each reciprocal square root takes the hardware estimate y (relative error below 2^-22) and one third-order
-// step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2, which cubes the error.
+// Jacobi rotation (c, s) zeroing the off-diagonal g of a symmetric 2 x 2 block [[a, g], [g, b]], by its half angle:
+// cos 2u = |b - a| / sqrt((b - a)^2 + 4 g^2), c = sqrt((1 + cos 2u) / 2), two reciprocal square roots long, with
+// tg = (s / c) g for the new diagonal (a - tg, b + tg).  Identity (c, s, tg = 1, 0, 0) where a row is at or below
+// floor2 or the coupling is at the rounding level.  It is a chain of dependent operations cut into eight stages, so
+// that a caller can issue other work between them; each reciprocal square root takes the hardware estimate y
+// (relative error below 2^-22) and one third-order step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2, which cubes the
+// error: c^2 + s^2 = 1 to a few ulp without the long correctly rounded division and square-root sequences.
 // The rotation depends on the ratios of a, b and g alone, so they are first multiplied by the power of two that
 // brings the largest into [1, 2) (exact): the squares of squared norms would underflow for rows of norm
 // 1e-77 (also for a block of such rows in a matrix of norm 1) and overflow at 1e77.
@@ -137,7 +111,6 @@ struct RotChain {
   }
 };
 
-typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr double EPS53 = 1.1102230246251565e-16;
 constexpr int BS = 32;  // rows per block
 
@@ -300,15 +273,6 @@ __device__ inline double row_floor2(const SvdMat &a, double fro2) {
 // b + t g), so a round needs one coupling per pair, read in place by the lanes that hold it.  Per
 // round: the owners form their pairs' rotations and put them in LDS, one barrier, and every lane
 // reads its columns' and its rows' rotations and updates HR x 2 elements of G and of Q.
-// f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>): register arrays indexed by constants
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
 constexpr int OE_QD = 4;  // of eight rows of Q, those updated behind a round's LDS reads (2, 6, 8: within 3 %)
 template <int N, int NW>
 struct OeShape {
