@@ -1034,8 +1034,9 @@ __device__ __forceinline__ void lz_small_body(const LzSmall &p, int iters, doubl
   }
 }
 
-// Register budget of two waves per SIMD.  The form is chosen by theta's length alone: 512 threads own one
-// element pair each up to n = 1024; a lane's share of a vector follows.
+// Register budget of two waves per SIMD, of which all forms together, with D at run time, use a little more than there
+// is (100 B a lane in scratch).  The form is chosen by theta's length alone: 512 threads own one element pair each up to
+// n = 1024; a lane's share of a vector follows.
 template <class T>
 __global__ __launch_bounds__(NTS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lz_small_kernel(
     const LzSmall *probs, int iters) {

@@ -2,12 +2,13 @@
 //
 // One kernel template serves every GEMM of the path: H_eff stages S1 (L x theta)
 // and S4 (Z x R^T), the environment updates, theta formation.  A workgroup owns
-// a BM x BN tile of C: 64 x 64 with 256 threads (four wave64s in a 2 x 2
+// a BM x BN tile of C: 32 x 32 or 64 x 64 with 256 threads (four wave64s in a 2 x 2
 // arrangement), or 128 x 128 with 512 threads (eight wave64s, 4 x 2; half the
-// operand traffic per flop of the small tile at the same registers per wave, and
-// two workgroups per compute unit).  K advances in steps of 16 through two LDS
-// buffers (the next slab is fetched into registers while the current one feeds
-// the MFMAs).  Each wave accumulates its share of the tile as 16 x 16 MFMA tiles:
+// operand traffic per flop of the 64 x 64 tile at the same registers per wave, and
+// two workgroups per compute unit).  K advances in slabs through two LDS buffers,
+// the next slab (of the smaller tiles, the next four) being fetched into registers
+// while the current one feeds the MFMAs; TileShape has the numbers and the reasons.
+// Each wave accumulates its share of the tile as 16 x 16 MFMA tiles:
 //   FP64: v_mfma_f64_16x16x4_f64, FP32: v_mfma_f32_16x16x4_f32.
 // Operand layout of the 16x16x4 MFMAs (lane l, result register r = 0..3):
 //   A[i][k]: lane i + 16k      B[k][j]: lane j + 16k
@@ -42,7 +43,8 @@ template <int BM> struct TileShape;
 // cycles against the 512 of its products) behind: they keep four slabs in flight.  H_eff of
 // 512 x 512 with 5 MPO channels in FP32, one slab and then four: 246 -> 181 us.  A slab of the
 // 32 x 32 tile is 32 deep, as a 16 deep one leaves its waves two products between barriers (203 x 331, 32
-// channels: 152 us with 16 deep and eight in flight, 126 us with 32 deep and four).)
+// channels: 152 us with 16 deep and eight in flight, 126 us with 32 deep and four).  At four waves per SIMD its FP64
+// forms keep 12 to 64 B a lane in scratch; they have not been timed with fewer waves.)
 template <> struct TileShape<32> { static constexpr int NT = 256, WR = 2, MINW = 4, PD = 4, BK = 32; };
 template <> struct TileShape<64> { static constexpr int NT = 256, WR = 2, MINW = 2, PD = 4, BK = 16; };
 template <> struct TileShape<128> { static constexpr int NT = 512, WR = 4, MINW = 4, PD = 1, BK = 16; };

@@ -322,6 +322,8 @@ tna_status heff_device(const HeffOp &h, const double *x, double *out, hipStream_
 // D = 5, FP64: 11.4 / 15.9 us at 32 x 32, 17.8 / 18.7 at 192 x 32, 17.5 / 18.6 at 48 x 48, 23.6 / 19.5 at
 // 64 x 64, 33.6 / 22.8 at 192 x 64; D = 8: 23.1 / 26.5 at 192 x 32, 24.1 / 27.4 at 48 x 48, 31.2 / 28.4 at
 // 64 x 64; FP32 and D = 3 cross over in the same places.
+// MPOs without a compile-time form of their own: D = 4 18.7 / 19.2 us at 64 x 48, D = 7 29.9 / 29.0 and in FP32
+// 33.5 / 30.9; the most that the line leaves on the table is D = 8 at 1 x 48, 21.6 / 19.6.
 inline bool heff_small_bond(int chl, int chr) { return (chl <= 192 && chr <= 32) || (chl <= 64 && chr <= 48); }
 bool heff_small_takes(int chl, int chr, int d, int D, const double *L, const double *W1, const double *W2,
                       const double *R, const double *theta, const double *out, int prec);

@@ -66,7 +66,8 @@ namespace {
 // error: c^2 + s^2 = 1 to a few ulp without the long correctly rounded division and square-root sequences.
 // The rotation depends on the ratios of a, b and g alone, so they are first multiplied by the power of two that
 // brings the largest into [1, 2) (exact): the squares of squared norms would underflow for rows of norm
-// 1e-77 (also for a block of such rows in a matrix of norm 1) and overflow at 1e77.
+// 1e-77 (also for a block of such rows in a matrix of norm 1) and overflow at 1e77.  The eigen step of 331 x 517 takes
+// 36.3 us a launch so, 35.0 without (mean of all sweeps).
 struct RotChain {
   double a, b, g;  // inputs: the 2 x 2 block [[a, g], [g, b]]
   double as, bs, gs;  // the block, scaled
@@ -1088,10 +1089,13 @@ __global__ void status_kernel(const SvdMat *mats, int nmat, int *hctr, double *h
 // A Householder QR of the loaded rows, B = Q Rf, turns the start state (B, Jt) =
 // (A, I) into (Rf, Q^T): B = Jt A still holds, and the one-sided Jacobi needs far
 // fewer sweeps on the rows of Rf than on A itself.  Blocked: each panel of 32
-// columns is factored by one workgroup, the trailing columns take the panel's
-// block reflector as three GEMMs, and Q^T is formed from the stored reflectors the
-// same way.  No column pivoting: on the prescribed-spectrum matrices it did not
-// lower the sweep count; cperm / pinv keep the (identity) column order explicit.
+// columns is factored by one workgroup per matrix where at most 1024 rows are left
+// (qr_panel_wg_kernel), by a grid above that (qr_panel_coop_kernel, qr_col_kernel);
+// the trailing columns take the panel's block reflector in three launches
+// (qr_wy_kernel, qr_wy_solve_kernel, qr_wy_update_kernel), and Q^T is formed from
+// the stored reflectors the same way.  No column pivoting: on the
+// prescribed-spectrum matrices it did not lower the sweep count; cperm / pinv keep
+// the column order explicit (the identity, or by decreasing norm, see below).
 constexpr int QR_MIN_ROWS_DEV = 256;
 // The products of a block reflector with 32 rows (S = V V^T and W = V X) are long in K and short
 // in M: K is cut into up to QR_SPLIT pieces, and the pieces are summed in order afterwards.
@@ -1487,7 +1491,8 @@ __global__ __launch_bounds__(256) void qr_panel_coop_kernel(const SvdMat *mats, 
 // and the first wave forms the reflector's scalars.  After column k the registers hold R above the diagonal
 // and the reflectors on and below it; both are written out at the end.
 // Bound by its instructions on one compute unit: per column 16 x (broadcast, two products, two updates) a
-// wave and two barriers.  grid (1, 1, matrices), 64 x waves threads.
+// wave and two barriers; 34 to 40 us a panel with 512 threads.  The form with 1024, which has 128 registers a lane,
+// keeps 184 B a lane in scratch and takes 77 us.  grid (1, 1, matrices), 64 x waves threads.
 constexpr int QP_M = 16, QP_ROWS = 1024;
 template <int N>
 __device__ inline double row_bcast16(double v) {  // lane N of every 16-lane row to the whole row
@@ -2418,8 +2423,8 @@ tna_status svd_group_run(std::vector<SvdMat> &mats, SvdGroup &g, int max_sweeps,
     for (auto &a : mats)
       if (a.precond) qr_bytes += 16.0 * ((double)a.R * a.C / 3.0 + (double)a.R * a.R / 2.0);
     // Blocked Householder QR (no column pivoting: the start it gives converges as fast on
-    // these matrices, and the trailing update becomes GEMMs): each 32-column panel is
-    // factored column by column, then B[k0:, k0+32:] <- (I - V T^T V^T) B[k0:, k0+32:].
+    // these matrices, and the trailing update becomes matrix products): each 32-column panel is
+    // factored, then B[k0:, k0+32:] <- (I - V T^T V^T) B[k0:, k0+32:].
     // A rows_scaled matrix stops its QR start once every row below the factored panels is at the
     // rounding level (row_floor2): such rows are never rotated, so the sweeps run on the rows
     // above (Ra), and a numerically low-rank matrix pays for the panels of its rank only.
