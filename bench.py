@@ -87,8 +87,9 @@ def copy_probe():
 # what the counter reads for a 1 GiB device copy); valid only while the kernel's source file
 # is unchanged since the counters were taken (sha256 recorded next to the figure)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-# the H_eff products' kernel is in gemm.hip, their launch shapes (problem lists) in batch.cpp
-_HEFF_SRC = ["paper_2604_03960_amd/csrc/gemm.hip", "paper_2604_03960_amd/csrc/batch.cpp"]
+# the H_eff products' kernel is in gemm.hip and dev_tile.h, their launch shapes (problem lists) in batch.cpp
+_HEFF_SRC = ["paper_2604_03960_amd/csrc/gemm.hip", "paper_2604_03960_amd/csrc/dev_tile.h",
+             "paper_2604_03960_amd/csrc/batch.cpp"]
 KERNEL_SOURCE = {"lz.small": ["paper_2604_03960_amd/csrc/batch.hip"], "svd.fused": ["paper_2604_03960_amd/csrc/svd.hip"],
                  "heff.f64": _HEFF_SRC, "heff.f32": _HEFF_SRC,
                  "svd.apply": ["paper_2604_03960_amd/csrc/svd.hip"], "svd.eigen": ["paper_2604_03960_amd/csrc/svd.hip"]}
